@@ -148,7 +148,7 @@ def kernel_work(name, cfg, st, C):
         return "alu", 2.0 * C * C * d * H, "flop", "alu_f64"
     if name == "gram_partial":
         return "alu", 2.0 * N * d * d * H, "flop", "alu_f64"
-    if name in ("attn_valu", "attn_mfma"):
+    if name in ("attn_f32", "attn_mfma"):
         import numpy as np
         qo = st["q_offsets"].cpu().numpy()
         ko = st["k_offsets"].cpu().numpy()

@@ -5,6 +5,10 @@
 // taken over that stream (renormalised), flash-attention style with an
 // online maximum, and row i of Q' is written to O[q_perm[i]].  Only the
 // last 32-key tile of a stream is partial, whatever the block sizes.
+#include <math.h>
+
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -13,16 +17,18 @@ namespace park {
 constexpr int AT_MAXC = 2048;
 
 // exclusive prefix of the selected block sizes into cum[0..n] and the first
-// row of each selected block into kst[0..n), 256 threads (ids outside
+// row of each selected block into kst[0..n), NT threads (ids outside
 // [0, nblk) count as empty)
+template <int NT>
 __device__ void prefix_sizes(const int* __restrict__ sel, int n, int nblk,
                              const int* __restrict__ koff, int* cum, int* kst, int* tmp) {
+  constexpr int PT = AT_MAXC / NT;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  int x[8];
+  int x[PT];
   int s = 0;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int i = tid * 8 + k;
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid * PT + k;
     x[k] = 0;
     if (i < n) {
       const int v = sel[i];
@@ -47,8 +53,8 @@ __device__ void prefix_sizes(const int* __restrict__ sel, int n, int nblk,
   for (int w = 0; w < wid; ++w) pre += tmp[w];
   int run = pre + inc - s;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int i = tid * 8 + k;
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid * PT + k;
     if (i < n) cum[i] = run;
     run += x[k];
     if (i == n - 1) cum[n] = run;
@@ -70,118 +76,206 @@ __device__ __forceinline__ int stream_row(int p, const int* cum, const int* kst,
   return kst[lo] < 0 ? -1 : kst[lo] + (p - cum[lo]);
 }
 
-template <typename OT>
-__device__ __forceinline__ void store_out(OT* p, float v);
-template <>
-__device__ __forceinline__ void store_out<float>(float* p, float v) { *p = v; }
-template <>
-__device__ __forceinline__ void store_out<bf16_t>(bf16_t* p, float v) { *p = f2bf(v); }
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// fp32 VALU kernel (fp32 inputs): 32 query rows x 32 keys per step, 8 threads
-// per row.
-template <typename T, typename OT, int D>
-__global__ __launch_bounds__(256) void k_attn_valu(const T* __restrict__ Qp, const T* __restrict__ Kp,
-                                                   const T* __restrict__ Vp,
-                                                   const int* __restrict__ q_offsets,
-                                                   const int* __restrict__ k_offsets,
-                                                   const int* __restrict__ kv_count,
-                                                   const int* __restrict__ kv_index,
-                                                   const int* __restrict__ q_perm, int N, int CQ,
-                                                   int CK, OT* __restrict__ O,
-                                                   float* __restrict__ lse) {
-  constexpr int RT = 32, KT = 32, TPR = 8, CPT = D / TPR, KPT = KT / TPR;
-  __shared__ float qs[RT][D + 1];
-  __shared__ float ks[KT][D + 1];
-  __shared__ float vs[KT][D + 1];
-  __shared__ float ps[RT][KT + 1];
+// maximum of v over lanes l and l ^ 32 (a cross-half lane swap, no LDS traffic)
+__device__ __forceinline__ float max_xor32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(v, fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+
+template <typename OT>
+__device__ __forceinline__ void store_out2(OT* p, float a, float b);
+template <>
+__device__ __forceinline__ void store_out2<float>(float* p, float a, float b) {
+  *(float2*)p = make_float2(a, b);
+}
+template <>
+__device__ __forceinline__ void store_out2<bf16_t>(bf16_t* p, float a, float b) {
+  *(uint32_t*)p = (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
+}
+
+// fp32 inputs: both contractions on v_mfma_f32_32x32x2_f32 (fp32 products and
+// sums), a workgroup per 32 rows of a query block.
+//
+// What bounds it: a small float32 layer has few query blocks (64 at 1 x 4096
+// tokens), so the chip is idle unless the key stream of one block is split as
+// well: the eight wavefronts of a workgroup take the stream's 32-key tiles in
+// turn, each with its own online softmax, and their partial results are added
+// in wavefront order at the end.  Operands go straight from global memory to
+// registers (no LDS, no barrier in the tile loop): with
+// S^T = K Q^T in C layout a lane holds the scores of query l % 32 and keys
+// 8 b + 4 (l / 32) + r, which is the B operand of O^T += V^T P^T when step
+// (b, r) of the product takes those two keys, so the probabilities stay where
+// they are.  The previous kernel (one workgroup per query block, dot products
+// and P V on the vector ALU through LDS) took 2314 us at 1 x 4096 tokens,
+// d = 64, top 25%; this one 86 us (1.07 GFLOP: 0.5 -> 12 TFLOP/s).
+template <typename OT, int D>
+__global__ __launch_bounds__(512, 2) void k_attn_f32(
+    const float* __restrict__ Qp, const float* __restrict__ Kp, const float* __restrict__ Vp,
+    const int* __restrict__ q_offsets, const int* __restrict__ k_offsets,
+    const int* __restrict__ kv_count, const int* __restrict__ kv_index,
+    const int* __restrict__ q_perm, int N, int CQ, int CK, float scale, float scale_log2,
+    OT* __restrict__ O, float* __restrict__ lse) {
+  constexpr int NW = 8, RT = 32, KT = 32, DB = D / 32, PS = 36;
+  constexpr bool PRE = D == 64;  // next tile's keys loaded during P V (registers allow it)
   __shared__ int cum[AT_MAXC + 1];
   __shared__ int kst[AT_MAXC];
-  __shared__ int krow[KT];
-  __shared__ int tmp[4];
-  const int h = blockIdx.y, u = blockIdx.x, tid = threadIdx.x;
+  __shared__ int tmp[NW];
+  __shared__ float ml[2][NW][RT];     // running maximum and sum of each wavefront's share
+  __shared__ float part[NW][RT][PS];  // 32 dimensions of each wavefront's O (4 pad columns)
+  const int u = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
   const int* qo = q_offsets + (size_t)h * (CQ + 1);
   const int q0 = min(max(qo[u], 0), N), q1 = min(max(qo[u + 1], q0), N);
-  if (q1 <= q0) return;
-  const int* koff = k_offsets + (size_t)h * (CK + 1);
+  if (q0 + RT * (int)blockIdx.z >= q1) return;
   const size_t row = (size_t)h * CQ + u;
-  int nsel = kv_count[row];
-  nsel = nsel < 0 ? 0 : (nsel > CK ? CK : nsel);
-  const int* sel = kv_index + row * CK;
-  prefix_sizes(sel, nsel, CK, koff, cum, kst, tmp);
+  const int nsel = min(max(kv_count[row], 0), CK);
+  prefix_sizes<64 * NW>(kv_index + row * CK, nsel, CK, k_offsets + (size_t)h * (CK + 1), cum, kst,
+                        tmp);
   const int nk = cum[nsel];
-  const T* Qh = Qp + (size_t)h * N * D;
-  const T* Kh = Kp + (size_t)h * N * D;
-  const T* Vh = Vp + (size_t)h * N * D;
-  const int r = tid / TPR, sub = tid % TPR;
-  const float scale = 1.0f / sqrtf((float)D);
-  for (int r0 = q0; r0 < q1; r0 += RT) {
+  const float* Qh = Qp + (size_t)h * N * D;
+  const float* Kh = Kp + (size_t)h * N * D;
+  const float* Vh = Vp + (size_t)h * N * D;
+  const int w = tid >> 6, l = tid & 63, hf = l >> 5, c32 = l & 31;
+  const int ntiles = (nk + KT - 1) / KT;
+  for (int r0 = q0 + RT * (int)blockIdx.z; r0 < q1; r0 += RT * (int)gridDim.z) {
     const int nr = min(RT, q1 - r0);
+    // operand k-index: step 4 j + e of the score product takes dimensions
+    // 8 j + e (lanes 0..31) and 8 j + 4 + e (lanes 32..63) of both operands
+    float4 qf[D / 8];
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j)
+      qf[j] = c32 < nr ? *(const float4*)(Qh + (size_t)(r0 + c32) * D + 8 * j + 4 * hf)
+                       : make_float4(0.f, 0.f, 0.f, 0.f);
+    float m = -INFINITY, lsum = 0.0f;
+    f32x16_t acc[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[b][q] = 0.0f;
+    float4 kf[D / 8];
+    int src = 0;
+    auto load_k = [&](int t) {
+      src = min(max(stream_row(t * KT + c32, cum, kst, nsel), 0), N - 1);
+#pragma unroll
+      for (int j = 0; j < D / 8; ++j)
+        kf[j] = *(const float4*)(Kh + (size_t)src * D + 8 * j + 4 * hf);
+    };
+    if (PRE && w < ntiles) load_k(w);
+    for (int t = w; t < ntiles; t += NW) {
+      if (!PRE) load_k(t);
+      // V row of key 8 b + 4 hf + r, dimension 32 db + c32
+      float vf[16][DB];
+      auto load_v = [&](int b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int s = __shfl(src, 8 * b + 4 * hf + r, 64);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) vf[4 * b + r][db] = Vh[(size_t)s * D + 32 * db + c32];
+        }
+      };
+      const int left = nk - t * KT;  // keys of the tile; those past the stream's end count for nothing
+      auto key_in = [&](int q) { return 8 * (q >> 2) + 4 * hf + (q & 3) < left; };
+      if (PRE) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) load_v(b);
+      }
+      f32x16_t st;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) st[q] = 0.0f;
+#pragma unroll
+      for (int j = 0; j < D / 8; ++j) {
+        st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].x, qf[j].x, st, 0, 0, 0);
+        st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].y, qf[j].y, st, 0, 0, 0);
+        st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].z, qf[j].z, st, 0, 0, 0);
+        st = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j].w, qf[j].w, st, 0, 0, 0);
+      }
+      if (PRE && t + NW < ntiles) load_k(t + NW);
+      if (left < KT) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) st[q] = key_in(q) ? st[q] : -INFINITY;
+      }
+      float tmax = st[0];
+#pragma unroll
+      for (int q = 1; q < 16; ++q) tmax = fmaxf(tmax, st[q]);
+      const float mnew = fmaxf(m, max_xor32(tmax));
+      const float alpha = mnew == m ? 1.0f : __builtin_amdgcn_exp2f((m - mnew) * scale_log2);
+      const float mref = mnew == -INFINITY ? 0.0f : mnew;
+      m = mnew;
+      lsum *= alpha;
+#pragma unroll
+      for (int b = 0; b < DB; ++b) acc[b] *= alpha;
+      // the difference to the maximum is taken before the scaling, so that the
+      // exponent's rounding is relative to that difference
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        st[q] = __builtin_amdgcn_exp2f((st[q] - mref) * scale_log2);
+        lsum += st[q];
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (!PRE) load_v(b);
+        if (left < KT) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) vf[4 * b + r][db] = key_in(4 * b + r) ? vf[4 * b + r][db] : 0.0f;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+            acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[4 * b + r][db], st[4 * b + r],
+                                                           acc[db], 0, 0, 0);
+      }
+    }
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (hf == 0) {
+      ml[0][w][c32] = m;
+      ml[1][w][c32] = lsum;
+    }
     __syncthreads();
-    for (int e = tid; e < RT * D; e += 256) {
-      const int rr = e / D, c = e % D;
-      qs[rr][c] = rr < nr ? to_f(Qh[(size_t)(r0 + rr) * D + c]) : 0.0f;
+    // the eight shares of a row: common maximum, this wavefront's factor
+    {
+      float mall = ml[0][0][c32];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) mall = fmaxf(mall, ml[0][i][c32]);
+      const float fac = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m - mall) * scale_log2);
+#pragma unroll
+      for (int b = 0; b < DB; ++b) acc[b] *= fac;
     }
-    float mrow = -INFINITY, lrow = 0.0f;
-    float acc[CPT];
+    // output row qr and two dimensions of each 32 per thread
+    const int qr = tid >> 4, dc = 2 * (tid & 15);
+    float mall = ml[0][0][qr], lall = 0.0f;
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) acc[c] = 0.0f;
-    for (int k0 = 0; k0 < nk; k0 += KT) {
+    for (int i = 1; i < NW; ++i) mall = fmaxf(mall, ml[0][i][qr]);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+      if (ml[0][i][qr] != -INFINITY)
+        lall += ml[1][i][qr] * __builtin_amdgcn_exp2f((ml[0][i][qr] - mall) * scale_log2);
+    const float inv = lall > 0.0f ? 1.0f / lall : 0.0f;
+    const int dst = qr < nr ? q_perm[(size_t)h * N + r0 + qr] : -1;
+    const bool ok = (unsigned)dst < (unsigned)N;
+    // natural-log normaliser of the row: mall is its largest raw score
+    if (lse && ok && dc == 0)
+      lse[(size_t)h * N + dst] = lall > 0.0f ? mall * scale + logf(lall) : -INFINITY;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        *(float4*)&part[w][c32][8 * b + 4 * hf] = make_float4(
+            acc[db][4 * b], acc[db][4 * b + 1], acc[db][4 * b + 2], acc[db][4 * b + 3]);
       __syncthreads();
-      if (tid < KT) krow[tid] = stream_row(k0 + tid, cum, kst, nsel);
+      float a = 0.0f, c = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) {
+        const float2 y = *(const float2*)&part[i][qr][dc];
+        a += y.x;
+        c += y.y;
+      }
+      if (ok) store_out2<OT>(O + ((size_t)h * N + dst) * D + 32 * db + dc, a * inv, c * inv);
       __syncthreads();
-      for (int e = tid; e < KT * D; e += 256) {
-        const int kr = e / D, c = e % D;
-        const int src = krow[kr];
-        const bool ok = (unsigned)src < (unsigned)N;
-        ks[kr][c] = ok ? to_f(Kh[(size_t)src * D + c]) : 0.0f;
-        vs[kr][c] = ok ? to_f(Vh[(size_t)src * D + c]) : 0.0f;
-      }
-      __syncthreads();
-      float s[KPT];
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const int kk = sub + TPR * j;
-        float dot = 0.0f;
-#pragma unroll 8
-        for (int a = 0; a < D; ++a) dot = fmaf(qs[r][a], ks[kk][a], dot);
-        s[j] = (k0 + kk < nk) ? dot * scale : -INFINITY;
-        tmax = fmaxf(tmax, s[j]);
-      }
-#pragma unroll
-      for (int o = 1; o < TPR; o <<= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, o, 64));
-      const float mnew = fmaxf(mrow, tmax);
-      const float alpha = (mrow == -INFINITY) ? 0.0f : expf(mrow - mnew);
-      float psum = 0.0f;
-#pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        const float p = (s[j] == -INFINITY) ? 0.0f : expf(s[j] - mnew);
-        ps[r][sub + TPR * j] = p;
-        psum += p;
-      }
-#pragma unroll
-      for (int o = 1; o < TPR; o <<= 1) psum += __shfl_xor(psum, o, 64);
-      lrow = lrow * alpha + psum;
-      mrow = mnew;
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) acc[c] *= alpha;
-      __syncthreads();
-      for (int kk = 0; kk < KT; ++kk) {
-        const float p = ps[r][kk];
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) acc[c] = fmaf(p, vs[kk][sub * CPT + c], acc[c]);
-      }
-    }
-    if (r < nr) {
-      const int dst = q_perm[(size_t)h * N + r0 + r];
-      if ((unsigned)dst < (unsigned)N) {
-        const float inv = lrow > 0.0f ? 1.0f / lrow : 0.0f;
-        OT* o = O + ((size_t)h * N + dst) * D + sub * CPT;
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) store_out<OT>(o + c, acc[c] * inv);
-        // natural-log normaliser of the row: mrow is the largest scaled score
-        if (lse && sub == 0) lse[(size_t)h * N + dst] = lrow > 0.0f ? mrow + logf(lrow) : -INFINITY;
-      }
     }
   }
 }
@@ -191,8 +285,6 @@ __global__ __launch_bounds__(256) void k_attn_valu(const T* __restrict__ Qp, con
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
 
@@ -593,12 +685,6 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
     }
   }
   for (int g = gbase + tid; g < GPH; g += 1024) gh[g] = make_int4(0, 0, 0, 0);
-}
-
-// maximum of v over lanes l and l ^ 32 (a cross-half lane swap, no LDS traffic)
-__device__ __forceinline__ float max_xor32(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(v, fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 
 // makes all K fragments of a tile live at once, so that their LDS reads are
@@ -1041,18 +1127,23 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
   }
 }
 
-template <typename T, typename OT>
-static park_status attn_dispatch_d(const void* Qp, const void* Kp, const void* Vp, const int* qo,
-                                   const int* ko, const int* kc, const int* ki, const int* qp,
-                                   int H, int N, int D, int CQ, int CK, void* O, float* lse,
-                                   hipStream_t st) {
-  dim3 g(CQ, H);
+template <typename OT>
+static park_status attn_f32_d(const void* Qp, const void* Kp, const void* Vp, const int* qo,
+                              const int* ko, const int* kc, const int* ki, const int* qp, int H,
+                              int N, int D, int CQ, int CK, void* O, float* lse, hipStream_t st) {
+  // 32-row workgroups for query blocks up to twice the mean size (larger ones
+  // take several rounds; the block sizes are known on the device only)
+  const unsigned nz = (unsigned)std::min((size_t)65535, 2 * (((size_t)N + 32u * CQ - 1) / (32u * (size_t)CQ)));
+  const dim3 g(CQ, H, nz);
+  const float sc = (float)(1.0 / sqrt((double)D)), sl2 = (float)(1.4426950408889634 / sqrt((double)D));
   if (D == 128)
-    PARK_LAUNCH("attn_valu", (k_attn_valu<T, OT, 128>), g, dim3(256), 0, st, (const T*)Qp,
-                (const T*)Kp, (const T*)Vp, qo, ko, kc, ki, qp, N, CQ, CK, (OT*)O, lse);
+    PARK_LAUNCH("attn_f32", (k_attn_f32<OT, 128>), g, dim3(512), 0, st, (const float*)Qp,
+                (const float*)Kp, (const float*)Vp, qo, ko, kc, ki, qp, N, CQ, CK, sc, sl2, (OT*)O,
+                lse);
   else
-    PARK_LAUNCH("attn_valu", (k_attn_valu<T, OT, 64>), g, dim3(256), 0, st, (const T*)Qp,
-                (const T*)Kp, (const T*)Vp, qo, ko, kc, ki, qp, N, CQ, CK, (OT*)O, lse);
+    PARK_LAUNCH("attn_f32", (k_attn_f32<OT, 64>), g, dim3(512), 0, st, (const float*)Qp,
+                (const float*)Kp, (const float*)Vp, qo, ko, kc, ki, qp, N, CQ, CK, sc, sl2, (OT*)O,
+                lse);
   return PARK_OK;
 }
 
@@ -1133,12 +1224,11 @@ park_status launch_attention(const void* Qp, const void* Kp, const void* Vp, con
     return attn_mfma_d<float>(Qp, Kp, Vp, q_offsets, k_offsets, kv_count, kv_index, q_perm, H, N,
                               D, CQ, CK, plan, O, lse, st);
   }
-  // fp32 inputs: VALU kernel in fp32 (the contraction cannot use bf16 MFMA exactly)
   if (out_dtype == PARK_BF16)
-    return attn_dispatch_d<float, bf16_t>(Qp, Kp, Vp, q_offsets, k_offsets, kv_count, kv_index,
-                                          q_perm, H, N, D, CQ, CK, O, lse, st);
-  return attn_dispatch_d<float, float>(Qp, Kp, Vp, q_offsets, k_offsets, kv_count, kv_index,
-                                       q_perm, H, N, D, CQ, CK, O, lse, st);
+    return attn_f32_d<bf16_t>(Qp, Kp, Vp, q_offsets, k_offsets, kv_count, kv_index, q_perm, H, N,
+                              D, CQ, CK, O, lse, st);
+  return attn_f32_d<float>(Qp, Kp, Vp, q_offsets, k_offsets, kv_count, kv_index, q_perm, H, N, D,
+                           CQ, CK, O, lse, st);
 }
 
 }  // namespace park

@@ -327,6 +327,52 @@ def test_attention_many_small_query_blocks(d):
         assert ok, worst
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nsel", [0, 1, 2, 40])
+def test_attention_f32_row_and_key_remainders(d, nsel):
+    # float32 attention: query blocks of 0, 1, 33 and very many rows (several
+    # rounds of a workgroup, a partial last one), streams from no key to many
+    # more tiles than wavefronts, and a non-finite value row that no block
+    # selected (it must not reach any output)
+    rng = np.random.default_rng(17)
+    H, N, CQ, CK = 2, 1531, 12, 40
+    q, k, v = (rng.standard_normal((H, N, d)).astype(np.float32) for _ in range(3))
+    qs = np.array([0, 1, 33, 1400, 32, 31] + [0] * 5 + [34])
+    assert qs.sum() == N
+    qoff = np.concatenate([[0], np.cumsum(qs)])
+    qoff = np.stack([qoff] * H)
+    koff = np.stack([np.concatenate([[0], np.sort(rng.choice(np.arange(1, N), CK - 1, False)), [N]])
+                     for _ in range(H)])
+    perm = np.stack([rng.permutation(N) for _ in range(H)])
+    rows = [[np.sort(rng.choice(np.arange(1, CK), size=min(nsel, CK - 1), replace=False))
+             for _ in range(CQ)] for _ in range(H)]
+    kvc = np.array([[len(s) for s in r] for r in rows], np.int32)
+    kvi = np.zeros((H, CQ, CK), np.int32)
+    for h in range(H):
+        for u, s in enumerate(rows[h]):
+            kvi[h, u, :len(s)] = s
+    vg = v.copy()
+    vg[:, 0] = np.inf  # in key block 0, which nobody selects
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).cuda()
+    Ot, Lt = P.park_block_sparse_attn(PT.to_dev(q, "f32"), PT.to_dev(k, "f32"),
+                                      PT.to_dev(vg, "f32"), t(qoff), t(koff), t(kvc), t(kvi),
+                                      t(perm), CQ, CK, P.PARK_F32, want_lse=True)
+    Og, Lg = PT.np64(Ot), Lt.double().cpu().numpy()
+    for h in range(H):
+        if nsel == 0:
+            assert np.all(Og[h] == 0.0) and np.all(np.isneginf(Lg[h]))
+            continue
+        args = (qoff[h], koff[h], rows[h], perm[h])
+        ref = O.block_sparse_attention(q[h], k[h], v[h], *args)
+        # d + N fp32 additions and one exponential per term: far inside 2^-24 (d + N)
+        bound = 2.0 ** -24 * (d + N) * np.abs(v[h]).max()
+        err = np.abs(Og[h] - ref).max()
+        print(f"[f32 attention d={d} nsel={nsel} h={h}] max-abs err {err:.3g} (bound {bound:.3g})")
+        assert err <= bound
+        lref = O.block_sparse_lse(q[h], k[h], *args)
+        assert np.abs(Lg[h] - lref).max() <= 2.0 ** -24 * (d + N)
+
+
 def test_attention_plan_selection_families():
     # query blocks drawn from a few families of nearly equal selections: the
     # plan's family of block u is the smallest v <= u with Jaccard(S_u, S_v)

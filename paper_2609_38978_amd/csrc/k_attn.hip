@@ -85,6 +85,12 @@ __device__ __forceinline__ float max_xor32(float v) {
   return fmaxf(v, fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+// two floats to bf16 (round to nearest even, v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
 template <typename OT>
 __device__ __forceinline__ void store_out2(OT* p, float a, float b);
 template <>
@@ -93,7 +99,7 @@ __device__ __forceinline__ void store_out2<float>(float* p, float a, float b) {
 }
 template <>
 __device__ __forceinline__ void store_out2<bf16_t>(bf16_t* p, float a, float b) {
-  *(uint32_t*)p = (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
+  *(uint32_t*)p = pack_bf(a, b);
 }
 
 // fp32 inputs: both contractions on v_mfma_f32_32x32x2_f32 (fp32 products and
@@ -283,10 +289,11 @@ __global__ __launch_bounds__(512, 2) void k_attn_f32(
 // ---------------------------------------------------------------------------
 // bf16 MFMA path: operand and accumulator vector types, output stores.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
+typedef const __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
+typedef const __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
 
 template <typename OT>
 __device__ __forceinline__ void store_out4(OT* p, float a, float b, float c, float d);
@@ -296,9 +303,7 @@ __device__ __forceinline__ void store_out4<float>(float* p, float a, float b, fl
 }
 template <>
 __device__ __forceinline__ void store_out4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
-  const uint32_t lo = (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
-  const uint32_t hi = (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16);
-  *(uint2*)p = make_uint2(lo, hi);
+  *(uint2*)p = make_uint2(pack_bf(a, b), pack_bf(c, d));
 }
 
 // MinHash of a selected key-block set: min over the selected ids of a fixed
@@ -318,13 +323,14 @@ __device__ __forceinline__ uint32_t attn_hash(uint32_t v) {
 template <int D>
 __device__ __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 
-// One wave-wide LDS DMA: lane l's 16 bytes at g land at LDS byte address
-// lds + 16 l (lds wave-uniform).  Written as inline assembly so that the
-// compiler does not treat the transfer as a pending LDS store: it would
-// otherwise wait for every DMA in flight before each LDS read.  Completion
-// is tracked explicitly with wait_vmcnt() and a barrier.
-__device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds)
+// One wave-wide LDS DMA: lane l's 16 bytes at base + off land at LDS byte
+// address lds + 16 l (base and lds wave-uniform).  Written as inline assembly
+// so that the compiler does not treat the transfer as a pending LDS store: it
+// would otherwise wait for every DMA in flight before each LDS read.
+// Completion is tracked explicitly with wait_vmcnt() and a barrier.
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base),
+               "s"(lds)
                : "memory", "m0");
 }
 
@@ -348,20 +354,38 @@ __device__ __forceinline__ void wait_vmcnt() {
 // union of its blocks' selections once (ascending key-block id) and each row
 // keeps only the keys of the key blocks its own query block selected, so the
 // result per row is the same renormalised softmax over its own selection.
+//
+// What bounds it and why it is built this way (measured with timing-only
+// copies at 24 x 119056 tokens, d = 128, top 10%, 24.3 TFLOP issued):
+//  * A 32 x 32 tile of a wavefront is 17 MFMAs (257 ns at the 2.1 GHz the chip
+//    holds under them) and about 90 vector operations with 16 exponentials
+//    (160 ns); on one SIMD the two overlap only in part, so the compute alone
+//    takes 18 ms, 21.7 ms with its LDS reads.  A single wavefront per SIMD
+//    issues vector operations at half rate: two wavefronts of 64 rows instead
+//    of four of 32 save a third of the LDS reads but take 31.6 ms.
+//  * So every LDS read is issued half a step before its use, vector work sits
+//    between the MFMAs, and what else a step did is taken out of it: the
+//    stream rows come from a table (the cursors they replace were a divergent
+//    loop of dependent LDS reads in every step), the selection bias from one
+//    more MFMA (bias rows x one-hot block) instead of 16 LDS floats per lane.
+//    30.5 -> 27.3 ms.
+//  * d = 64 runs three wavefronts per SIMD (168 registers, 48 KB of LDS per
+//    workgroup): 1730 -> 1290 us at 16 x 32227 tokens, top 15%.  d = 128 needs
+//    80 KB for its rings, two workgroups per CU.
+//  * Short streams (40 x 75600 tokens, top-p 0.9: 24 tiles per group) are bound
+//    by the chain of loads before the first tile: selections from the plan's
+//    bit rows (one load per block, no LDS atomics), Q and the output row loaded
+//    beside them, and one table segment expanded before the first tile:
+//    1970 -> 1670 us.
 
-#ifndef PARK_ATTN_R
-#define PARK_ATTN_R 128
-#endif
-#ifndef PARK_ATTN_RING
-#define PARK_ATTN_RING 3
-#endif
-#ifndef PARK_ATTN_HEADMAJOR
-#define PARK_ATTN_HEADMAJOR 1
-#endif
-constexpr int ATTN_R = PARK_ATTN_R;  // rows per group (32 per wavefront)
-constexpr int ATTN_KSLOTS = PARK_ATTN_RING;  // K tiles in LDS (V: one more)
+// neighbouring groups that run on one XCD at a time (1, 2, 4, 8: 1950, 1921,
+// 1890, 1864 us at 40 x 75600, top-p; 28.0, 28.4, 28.2, 28.6 ms at 24 x 119056)
+constexpr int ATTN_BUN = 4;
+constexpr int ATTN_R = 128;  // rows per group (32 per wavefront)
+constexpr int ATTN_KSLOTS = 3;  // K tiles in LDS (V: one more)
 constexpr int ATTN_UCAP = 1024;  // key blocks of the union per stream chunk
 constexpr int ATTN_LB = 16;          // query blocks per group (bits of a selection word)
+constexpr int ATTN_SEG = 512;        // stream positions expanded to rows at a time
 
 static int attn_windows(int N) { return (N + ATTN_R - 1) / ATTN_R; }
 // groups per head: every window of ATTN_R rows, split further when it holds
@@ -501,6 +525,8 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
   __shared__ int pre[2049];
   __shared__ int tiles[2048];  // key tiles of each query block's own selection (by block id)
   __shared__ int tpos[2048];   // the same by sorted position
+  __shared__ uint32_t gwk[2048];                        // window and part of each group
+  __shared__ uint32_t bcost[2048 / ATTN_BUN + 1];       // key tiles of each bundle of groups
   __shared__ int wsum[16];
   const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int* qo = q_offsets + (size_t)h * (CQ + 1);
@@ -590,9 +616,12 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
   }
   __syncthreads();
   // windows of ATTN_R rows; a window with more than ATTN_LB blocks is split
-  // into runs of ATTN_LB blocks.  With at most 2048 groups they are ordered
-  // longest first (summed key tiles of their query blocks), so that the
-  // longest ones start first.
+  // into runs of ATTN_LB blocks.  With at most 2048 groups they are ordered by
+  // bundles of ATTN_BUN neighbours, longest bundle first (summed key tiles of
+  // their query blocks), so that the longest ones start first, and the groups
+  // of a bundle go to one XCD (workgroup i runs on XCD i % 8): neighbours are
+  // of one family and stream nearly the same keys and values at the same time,
+  // which that XCD's L2 then fetches once.
   int4* gh = grp + (size_t)h * GPH;
   const int W = (total + ATTN_R - 1) / ATTN_R;
   const bool lpt = GPH <= 2048 && W < (1 << 23);
@@ -614,6 +643,8 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
     }
     i1 = lo;
   };
+  for (int g = tid; g < 2048 / ATTN_BUN + 1; g += 1024) bcost[g] = 0u;
+  __syncthreads();
   auto desc = [&](int wdw, int k, int i0, int i1) {
     const int ra = wdw * ATTN_R, rb = min(ra + ATTN_R, total);
     const int ib = i0 + k * ATTN_LB, ie = min(ib + ATTN_LB, i1);
@@ -647,7 +678,8 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
       if (lpt) {
         uint32_t c = 0;
         for (int i = gd.z; i < gd.w; ++i) c += (uint32_t)tpos[i];
-        key[g] = ((unsigned long long)(0xffffffffu - c) << 32) | ((uint32_t)wdw << 8) | (uint32_t)k;
+        gwk[g] = ((uint32_t)wdw << 8) | (uint32_t)k;
+        atomicAdd(&bcost[g / ATTN_BUN], c);
       } else {
         gh[g] = gd;
       }
@@ -658,7 +690,14 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
     const int G = min(gbase, GPH);
     int SG = 2;
     while (SG < G) SG <<= 1;
-    for (int g = G + tid; g < SG; g += 1024) key[g] = ~0ull;
+    __syncthreads();
+    // (a last bundle of fewer groups stays last: the others keep their alignment)
+    for (int g = tid; g < SG; g += 1024) {
+      const bool whole = g / ATTN_BUN * ATTN_BUN + ATTN_BUN <= G;
+      key[g] = g >= G ? ~0ull
+                      : ((unsigned long long)(0xfffffffeu - (whole ? bcost[g / ATTN_BUN] : 0u)) << 32) |
+                            (uint32_t)g;
+    }
     __syncthreads();
     for (int len = 2; len <= SG; len <<= 1)
       for (int j = len >> 1; j > 0; j >>= 1) {
@@ -677,45 +716,20 @@ __global__ __launch_bounds__(1024) void k_attn_gplan(const int* __restrict__ q_o
         __syncthreads();
       }
     for (int g = tid; g < G; g += 1024) {
-      const uint32_t lo = (uint32_t)key[g];
+      const uint32_t lo = gwk[(uint32_t)key[g]];
       const int wdw = (int)(lo >> 8), k = (int)(lo & 255u);
       int i0, i1;
       window(wdw, i0, i1);
-      gh[g] = desc(wdw, k, i0, i1);
+      // eight bundles side by side: member j of bundle x at 8 j + x (x in
+      // alternating direction, so that no XCD gets all the longer ones)
+      constexpr int SB = 8 * ATTN_BUN;
+      const int sb = g / SB * SB, r = g - sb, x = r / ATTN_BUN;
+      const int at = sb + SB <= G ? sb + 8 * (r % ATTN_BUN) + ((g / SB) & 1 ? 7 - x : x) : g;
+      gh[at] = desc(wdw, k, i0, i1);
     }
   }
   for (int g = gbase + tid; g < GPH; g += 1024) gh[g] = make_int4(0, 0, 0, 0);
 }
-
-// makes all K fragments of a tile live at once, so that their LDS reads are
-// issued together instead of one read-wait-MFMA step at a time
-template <int KS>
-__device__ __forceinline__ void frags_ready(const bf16x8_t (&a)[KS]) {
-  if constexpr (KS == 8)
-    asm volatile("" ::"v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]),
-                 "v"(a[7]));
-  else
-    asm volatile("" ::"v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]));
-}
-
-// waits until this wavefront's DMAs of the oldest tile in flight are done,
-// `younger` (0 .. NS - 2) newer tiles of PER operations each may stay in flight
-template <int PER, int NS>
-__device__ __forceinline__ void wait_oldest(int younger) {
-  static_assert(NS >= 2 && NS <= 8, "ring depth");
-  switch (NS >= 3 ? min(younger, NS - 2) : 0) {
-    case 6: wait_vmcnt<6 * PER>(); break;
-    case 5: wait_vmcnt<5 * PER>(); break;
-    case 4: wait_vmcnt<4 * PER>(); break;
-    case 3: wait_vmcnt<3 * PER>(); break;
-    case 2: wait_vmcnt<2 * PER>(); break;
-    case 1: wait_vmcnt<1 * PER>(); break;
-    default: wait_vmcnt<0>(); break;
-  }
-}
-
-// rotation of the rows of block b in a bias tile (a multiple of 4)
-__device__ __forceinline__ int bias_rot(int b) { return 4 * ((b >> 1) & 7); }
 
 template <int D, int KT, int NW>
 struct GrpTile {
@@ -733,82 +747,58 @@ struct GrpTile {
 template <int D>
 __device__ __forceinline__ int swz_v32(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
 
-template <typename OT, int D, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
+template <typename OT, int D>
+__global__ __launch_bounds__(2 * ATTN_R, D == 128 ? 2 : 3) void k_attn_grp(
     const bf16_t* __restrict__ Qp, const bf16_t* __restrict__ Kp, const bf16_t* __restrict__ Vp,
     const int* __restrict__ q_offsets, const int* __restrict__ k_offsets,
-    const int* __restrict__ kv_count, const int* __restrict__ kv_index,
-    const int* __restrict__ q_perm, const int* __restrict__ order, const int* __restrict__ spre,
-    const int4* __restrict__ grp, int H, int N, int CQ, int CK, int GPH, float scale_log2,
-    OT* __restrict__ O, float* __restrict__ lse) {
-  constexpr int KT = 32, NT = 64 * NW;
+    const uint32_t* __restrict__ bits, const int* __restrict__ q_perm,
+    const int* __restrict__ order, const int* __restrict__ spre, const int4* __restrict__ grp,
+    int H, int N, int CQ, int CK, int GPH, float scale_log2, OT* __restrict__ O,
+    float* __restrict__ lse) {
+  constexpr int KT = 32, NW = ATTN_R / 32, NT = 64 * NW;
   constexpr int NSK = ATTN_KSLOTS, NSV = ATTN_KSLOTS + 1;  // K and V ring slots
   using TS = GrpTile<D, KT, NW>;
   constexpr int KS = D / 16;         // k-steps of S^T
   constexpr int DB = D / 32;         // 32-dimension blocks of O^T
   constexpr int EPT = AT_MAXC / NT;  // key blocks per thread in the union scan
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   bf16_t* Ks = (bf16_t*)smem;                        // [NSK][KT][D], swizzled chunks
   bf16_t* Vs = Ks + NSK * TS::ELEMS;                 // [NSV][KT][D], swizzled chunks
-  float* bias = (float*)(Vs + NSV * TS::ELEMS);      // [NSK][ATTN_LB][KT]: 0 or -inf
-  uint32_t* flg = (uint32_t*)(bias + NSK * ATTN_LB * KT);  // [AT_MAXC / 2]: 16 bits per key block
-  int2* ut = (int2*)(flg + AT_MAXC / 2);            // [ATTN_UCAP + 1]
+  bf16_t* bias = Vs + NSV * TS::ELEMS;               // [NSK][KT][ATTN_LB]: 0 or -3.4e38
+  int2* ut = (int2*)(bias + NSK * KT * ATTN_LB);     // [ATTN_UCAP + 1]
   uint16_t* selw = (uint16_t*)(ut + ATTN_UCAP + 1);  // [ATTN_UCAP]
-  __shared__ int sg_row[ATTN_LB], sg_lr[ATTN_LB + 1], sg_u[ATTN_LB], sg_n[ATTN_LB + 1];
+  int* srow = (int*)(selw + ATTN_UCAP);              // [2 * ATTN_SEG] rows of Kp
+  uint16_t* sbit = (uint16_t*)(srow + 2 * ATTN_SEG); // [2 * ATTN_SEG] their selection bits
+  __shared__ int sg_row[ATTN_LB], sg_lr[ATTN_LB], sg_u[ATTN_LB];
   __shared__ int tmp[2][NW];
   static_assert(ATTN_LB <= 16, "selection words are 16 bits");
 
   const int nitems = H * GPH;
-#if PARK_ATTN_HEADMAJOR
   // head-major over the whole chip: consecutive workgroups (dealt to the 8
   // XCDs in turn) take the groups of one head, so only a head or two are in
   // flight at a time and their keys and values stay in the Infinity Cache
   const int item = (int)blockIdx.x;
-#else
-  // XCD-aware work item: XCD x (= blockIdx % 8) takes items [x*per, (x+1)*per)
-  const int per = (nitems + 7) >> 3;
-  const int item = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-#endif
   if (item >= nitems) return;
   const int h = item / GPH;
   const int4 gd = grp[item];
   const int ib = gd.z, ie = gd.w;
-  if (gd.y <= gd.x || ib < 0 || ie <= ib || ie - ib > ATTN_LB || ie > CQ || gd.y - gd.x > 32 * NW)
+  if (gd.y <= gd.x || ib < 0 || ie <= ib || ie - ib > ATTN_LB || ie > CQ || gd.y - gd.x > ATTN_R)
     return;
   const int nb = ie - ib, tid = threadIdx.x;
   const int* qo = q_offsets + (size_t)h * (CQ + 1);
   const int* koff = k_offsets + (size_t)h * (CK + 1);
-  if (tid < nb) {
-    const int i = ib + tid;
-    const int u = min(max(order[(size_t)h * CQ + i], 0), CQ - 1);
-    const int s0 = spre[(size_t)h * (CQ + 1) + i];
-    const int a = max(gd.x, s0);
-    sg_u[tid] = u;
-    sg_row[tid] = min(max(qo[u], 0), N) + (a - s0);
-    sg_lr[tid] = a - gd.x;
-    sg_n[tid] = min(max(kv_count[(size_t)h * CQ + u], 0), CK);
-  }
-  if (tid == 0) sg_lr[nb] = gd.y - gd.x;
-  for (int v = tid; v < AT_MAXC / 2; v += NT) flg[v] = 0u;
-  __syncthreads();
-  // selection entries of the group's blocks, end-to-end (a prefix over the
-  // few blocks, then one parallel pass: the entries' loads go out together)
-  if (tid == 0) {
-    int c = 0;
-    for (int b = 0; b < nb; ++b) {
-      const int n = sg_n[b];
-      sg_n[b] = c;
-      c += n;
+  if (tid < ATTN_LB) {
+    int lr = 0x7fffffff;
+    if (tid < nb) {
+      const int i = ib + tid;
+      const int u = min(max(order[(size_t)h * CQ + i], 0), CQ - 1);
+      const int s0 = spre[(size_t)h * (CQ + 1) + i];
+      const int a = max(gd.x, s0);
+      sg_u[tid] = u;
+      sg_row[tid] = min(max(qo[u], 0), N) + (a - s0);
+      lr = a - gd.x;
     }
-    sg_n[nb] = c;
-  }
-  __syncthreads();
-  // bit b of key block v's flag: query block b of the group selected v
-  for (int e = tid; e < sg_n[nb]; e += NT) {
-    int b = 0;
-    while (b + 1 < nb && sg_n[b + 1] <= e) ++b;
-    const int v = kv_index[((size_t)h * CQ + sg_u[b]) * CK + (e - sg_n[b])];
-    if ((unsigned)v < (unsigned)CK) atomicOr(&flg[v >> 1], (1u << b) << (16 * (v & 1)));
+    sg_lr[tid] = lr;
   }
   __syncthreads();
   const bf16_t* Qh = Qp + (size_t)h * N * D;
@@ -819,11 +809,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
 
   // this lane's query row: group row 32 w + c32, query block bq of the group
   const int gr = 32 * w + c32;
-  const int grows = sg_lr[nb];
   int bq = 0;
-  while (bq + 1 < nb && sg_lr[bq + 1] <= gr) ++bq;
+#pragma unroll
+  for (int b = 1; b < ATTN_LB; ++b) bq += sg_lr[b] <= gr;  // (ascending; INT_MAX past the blocks)
   const int qr0 = sg_row[bq] + (gr - sg_lr[bq]);
-  const bool qvalid = gr < grows && (unsigned)qr0 < (unsigned)N;
+  const bool qvalid = gr < gd.y - gd.x && (unsigned)qr0 < (unsigned)N;
   const int qr = qvalid ? qr0 : 0;
   bf16x8_t qf[KS];
 #pragma unroll
@@ -832,38 +822,41 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
     if (qvalid) raw = *(const uint4*)(Qh + (size_t)qr * D + 16 * s2 + 8 * hf);
     qf[s2] = __builtin_bit_cast(bf16x8_t, raw);
   }
+  const int dst = qvalid ? q_perm[(size_t)h * N + qr] : -1;
+  // one-hot of the query block (the B operand of the bias product): lanes of
+  // half hf hold blocks 8 hf .. 8 hf + 7
+  const int oe = (qvalid ? bq : 0) - 8 * hf;
+  uint32_t ow[4];
 #pragma unroll
-  for (int s2 = 0; s2 < KS; ++s2) asm volatile("" ::"v"(qf[s2]));
-  // the bias row of this lane
-  const int bqq = qvalid ? bq : 0;
-  const int brow = bqq * KT, bcol = 4 * hf + bias_rot(bqq);
+  for (int k = 0; k < 4; ++k) ow[k] = (oe >> 1) == k ? 0x3f80u << (16 * (oe & 1)) : 0u;
+  const bf16x8_t hot = __builtin_bit_cast(bf16x8_t, make_uint4(ow[0], ow[1], ow[2], ow[3]));
 
-  // LDS read offsets (bf16 elements, relative to a slot)
-  // K (A operand of S^T): key row c32, chunk 2 s + hf
-  int kofs[KS];
-#pragma unroll
-  for (int s2 = 0; s2 < KS; ++s2) kofs[s2] = c32 * D + 8 * ((2 * s2 + hf) ^ swz_k<D>(c32));
+  // LDS read offsets (bytes, relative to a slot).  The swizzle only flips
+  // chunk bits, so the other k-steps and dimension blocks are XORs of one
+  // offset with a constant (slots are aligned to a row).
+  // K (A operand of S^T): key row c32, chunk 2 s + hf at kofs ^ 32 s
+  const uint32_t kofs = c32 * (2 * D) + 16 * (hf ^ swz_k<D>(c32));
   // V^T (A operand of O^T) by transpose reads: in 16-lane group G, lane j
   // gives row 4 hf + j/4 (+ 16 kappa, + 8 for the second read) and dims
-  // 32 db + 16 (G % 2) + 4 (j % 4); it receives dim 32 db + 16 (G % 2) + j
+  // 32 db + 16 (G % 2) + 4 (j % 4); it receives dim 32 db + 16 (G % 2) + j;
+  // block db at vofs ^ 64 db
   const int G = l >> 4, jg = l & 15;
   const int vr0 = 4 * hf + (jg >> 2);
-  int vofs[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) {
-    const int col = 32 * db + 16 * (G & 1) + 4 * (jg & 3);
-    vofs[db] = vr0 * D + 8 * ((col >> 3) ^ swz_v32<D>(vr0)) + (col & 7);
-  }
+  const int vcol = 16 * (G & 1) + 4 * (jg & 3);
+  const uint32_t vofs = vr0 * (2 * D) + 16 * ((vcol >> 3) ^ swz_v32<D>(vr0)) + 2 * (vcol & 7);
 
-  float m = -INFINITY, lpart = 0.0f;
+  // reference maximum: at the start a bound that any real score exceeds and
+  // the score of a key the row's block did not select (S - 3.4e38) does not,
+  // so such keys have probability 0 also before the first selected one
+  constexpr float NOKEY = -1.7014118e38f;  // -2^127
+  float m = NOKEY, lpart = 0.0f, tmax = NOKEY;
   f32x16_t acc[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b)
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[b][q] = 0.0f;
 
-  // DMA lanes: tile row rr[i], chunk position pch; a cursor into ut per row;
-  // kb[i]: selection bits of the row's key block (all lanes of a row agree)
+  // DMA lanes: tile row rr[i], chunk position pch
   const int pch = l % TS::CPR;
   const bool dma_w = w < TS::DW;
   int rr[TS::NI];
@@ -878,15 +871,30 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
     // stream table of this chunk: ut[j] = {stream position, first row of Kp}
     // of its j-th key block, ut[Uc] = {end position, -1}; selw[j] its bits
     {
-      uint32_t f[EPT];
-      int x[EPT], kst[EPT], c = 0, s = 0;
-      int2 kb2[EPT];  // block boundaries, loaded together (clamped ids)
+      // f[k], bit b: query block b of the group selected key block tid EPT + k
+      // (from the bit rows of the plan: one word per block and thread)
+      static_assert(32 % EPT == 0, "a thread's key blocks lie in one word of a bit row");
+      int2 kb2[EPT];  // block boundaries (clamped ids)
 #pragma unroll
       for (int k = 0; k < EPT; ++k) kb2[k] = *(const int2*)(koff + min(tid * EPT + k, CK - 1));
+      uint32_t f[EPT] = {};
+      for (int b0 = 0; b0 < nb; b0 += 4) {
+        uint32_t y[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          y[b] = bits[((size_t)h * CQ + sg_u[min(b0 + b, nb - 1)]) * 64 + tid * EPT / 32];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          y[b] = b0 + b < nb ? y[b] >> (tid * EPT % 32) : 0u;
+#pragma unroll
+          for (int k = 0; k < EPT; ++k) f[k] |= ((y[b] >> k) & 1u) << (b0 + b);
+        }
+      }
+      int x[EPT], kst[EPT], c = 0, s = 0;
 #pragma unroll
       for (int k = 0; k < EPT; ++k) {
         const int v = tid * EPT + k;
-        f[k] = v < CK ? (flg[v >> 1] >> (16 * (v & 1))) & 0xffffu : 0u;
+        if (v >= CK) f[k] = 0u;
         x[k] = 0;
         kst[k] = -1;
         if (f[k]) {
@@ -934,197 +942,209 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_grp(
     if (U == 0) break;
     const int Uc = min(ATTN_UCAP, U - ch * ATTN_UCAP);
     const int base = ut[0].x, nk = ut[Uc].x - base;
-    int jj[TS::NI], cj[TS::NI], kj[TS::NI], src[TS::NI];
-    uint32_t sw[TS::NI], kb[TS::NI];
-    int2 nx[TS::NI];
-#pragma unroll
-    for (int i = 0; i < TS::NI; ++i) {
-      jj[i] = 0;
-      cj[i] = base;
-      kj[i] = ut[0].y;
-      sw[i] = selw[0];
-      nx[i] = ut[1];
-      src[i] = 0;
-      kb[i] = 0u;
-    }
-    auto advance = [&](int t) {
-      if (!dma_w) return;
-#pragma unroll
-      for (int i = 0; i < TS::NI; ++i) {
-        const int pos = base + t * KT + rr[i];
-        while (pos >= nx[i].x && jj[i] + 1 < Uc) {
-          ++jj[i];
-          cj[i] = nx[i].x;
-          kj[i] = nx[i].y;
-          sw[i] = selw[jj[i]];
-          nx[i] = ut[jj[i] + 1];
+    // stream positions [ATTN_SEG sg, ATTN_SEG (sg + 1)) of this chunk as rows of
+    // Kp and selection bits (positions past the end: row 0, no bit), in the
+    // half of the table that segment sg - 2 held
+    auto expand = [&](int sg) {
+#pragma unroll 1
+      for (int k = 0; k < ATTN_SEG / NT; ++k) {
+        const int q = sg * ATTN_SEG + k * NT + tid, pos = base + q;
+        int lo = 0, hi = Uc - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (ut[mid].x <= pos) lo = mid;
+          else hi = mid - 1;
         }
-        const int r = kj[i] + (pos - cj[i]);
-        const bool ok = pos < base + nk && (unsigned)r < (unsigned)N;
-        src[i] = ok ? r : 0;
-        kb[i] = ok ? sw[i] : 0u;
+        const int2 e = ut[lo];
+        const int r = e.y + (pos - e.x);
+        const bool ok = q < nk && (unsigned)r < (unsigned)N;
+        srow[q & (2 * ATTN_SEG - 1)] = ok ? r : 0;
+        sbit[q & (2 * ATTN_SEG - 1)] = ok ? selw[lo] : (uint16_t)0;
       }
     };
-    // tile T: K into slot T % NSK, V into slot T % NSV, with the score bias
-    // of every (query block, tile row)
-    auto issue = [&](int T) {
+    // tile T: K into slot T % NSK with the score bias of every (tile row, query
+    // block), V into slot T % NSV (one step later: srcv are the rows of the
+    // tile whose keys went out in the step before)
+    int src[TS::NI], srcv[TS::NI];
+    uint32_t kb;  // selection bits of the tile row whose bias this thread writes
+    constexpr int BT = KT * ATTN_LB / 2 / NT;  // 32-bit words of the bias tile per thread
+    const int brow = tid * BT / 8, bword = tid * BT % 8;
+    auto rows_of = [&](int T) {
+#pragma unroll
+      for (int i = 0; i < TS::NI; ++i) {
+        srcv[i] = src[i];
+        src[i] = srow[((T * KT) & (2 * ATTN_SEG - 1)) + rr[i]];
+      }
+      kb = sbit[((T * KT) & (2 * ATTN_SEG - 1)) + brow];
+    };
+    auto issue_k = [&](int T) {
+      const int sk = T % NSK;
+      uint32_t* bs = (uint32_t*)(bias + sk * KT * ATTN_LB) + tid * BT;
+#pragma unroll
+      for (int k = 0; k < BT; ++k) {
+        const uint32_t y = kb >> (2 * (bword + k));
+        bs[k] = (y & 1u ? 0u : 0xff7fu) | (y & 2u ? 0u : 0xff7f0000u);
+      }
       if (!dma_w) return;
-      const int sk = T % NSK, sv = T % NSV;
-      bf16_t* ks = Ks + sk * TS::ELEMS;
-      bf16_t* vs = Vs + sv * TS::ELEMS;
+      const uint32_t ks = lds_addr(Ks) + sk * (2 * TS::ELEMS) + w * TS::NI * 1024;
 #pragma unroll
-      for (int i = 0; i < TS::NI; ++i) {
-        const int off = (w * TS::NI + i) * 512;  // 1 KB per wave-wide DMA
-        lds_dma16(Kh + (size_t)src[i] * D + 8 * (pch ^ swz_k<D>(rr[i])), lds_addr(ks + off));
-      }
-#pragma unroll
-      for (int i = 0; i < TS::NI; ++i) {
-        const int off = (w * TS::NI + i) * 512;
-        lds_dma16(Vh + (size_t)src[i] * D + 8 * (pch ^ swz_v32<D>(rr[i])), lds_addr(vs + off));
-      }
-      // row r of block b sits at b * KT + ((r + bias_rot(b)) % KT): groups of
-      // four rows stay contiguous and the 16 blocks of one row land in 16
-      // different banks
-      float* bs = bias + sk * ATTN_LB * KT;
+      for (int i = 0; i < TS::NI; ++i)  // 1 KB per wave-wide DMA
+        lds_dma16(Kh, (uint32_t)src[i] * (2 * D) + 16 * (pch ^ swz_k<D>(rr[i])), ks + 1024 * i);
+    };
+    auto issue_v = [&](int T) {
+      if (!dma_w) return;
+      const uint32_t vs = lds_addr(Vs) + (T % NSV) * (2 * TS::ELEMS) + w * TS::NI * 1024;
 #pragma unroll
       for (int i = 0; i < TS::NI; ++i)
-#pragma unroll
-        for (int b = pch; b < ATTN_LB; b += TS::CPR)
-          bs[b * KT + ((rr[i] + bias_rot(b)) & (KT - 1))] = ((kb[i] >> b) & 1u) ? 0.0f : -INFINITY;
+        lds_dma16(Vh, (uint32_t)srcv[i] * (2 * D) + 16 * (pch ^ swz_v32<D>(rr[i])), vs + 1024 * i);
     };
-    // S^T of tile T (32 keys x 32 queries; lane: keys 8 b + 4 hf + r of query
-    // c32), starting from the bias of those keys
-    auto scores = [&](int T, f32x16_t& st) {
+    // operands of tile T's scores: the K fragments, and the bias rows (key c32,
+    // blocks 8 hf ..): bias x one-hot adds 0 or -3.4e38 to a score exactly
+    bf16x8_t kf[KS], bf;
+    auto load_k = [&](int T) {
       const int sk = T % NSK;
-      const bf16_t* ks = Ks + sk * TS::ELEMS;
-      bf16x8_t kf[KS];
+      const uint32_t ko = lds_addr(Ks) + sk * (2 * TS::ELEMS) + kofs;
+      bf = *(lds_bf16x8_t*)(lds_addr(bias) + sk * (2 * KT * ATTN_LB) + 32 * c32 + 16 * hf);
 #pragma unroll
-      for (int s2 = 0; s2 < KS; ++s2) kf[s2] = *(const bf16x8_t*)(ks + kofs[s2]);
-      const float* br = bias + sk * ATTN_LB * KT + brow;
+      for (int s2 = 0; s2 < KS; ++s2) kf[s2] = *(lds_bf16x8_t*)(ko ^ (32 * s2));
+    };
+    auto bias_scores = [&]() {
+      const f32x16_t zero = {};
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf, hot, zero, 0, 0, 0);
+    };
+    auto row_max = [&](const f32x16_t& st) {
+      float x = fmaxf(st[0], st[1]);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const float4 y = *(const float4*)(br + ((bcol + 8 * b) & (KT - 1)));
-        st[4 * b + 0] = y.x;
-        st[4 * b + 1] = y.y;
-        st[4 * b + 2] = y.z;
-        st[4 * b + 3] = y.w;
-      }
-#pragma unroll
-      for (int s2 = 0; s2 < KS; ++s2)
-        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s2], qf[s2], st, 0, 0, 0);
+      for (int q = 2; q < 16; ++q) x = fmaxf(x, st[q]);
+      tmax = max_xor32(x);
     };
     const int ntiles = (nk + KT - 1) / KT;
-    // tiles 0 .. NSK - 1 in flight, then S^T of tile 0
-#pragma unroll
-    for (int p = 0; p < NSK; ++p)
-      if (p < ntiles) {
-        advance(p);
-        issue(p);
-      }
-    f32x16_t st_next;
-    if (ntiles > 0) {
-      wait_oldest<2 * TS::NI, NSK + 1>(ntiles - 1);
-      __syncthreads();
-      scores(0, st_next);
-    }
-    for (int t = 0; t < ntiles; ++t) {
-      // at the top: S^T(t) is in st_next; tiles t+1 .. t+NSK-1 are in flight
-      const f32x16_t st = st_next;
-      const int nxt = t + NSK;
-      if (nxt < ntiles) advance(nxt);
-      // K(t+1) (and with it everything issued before: V(t)) has landed; V(t+1)
-      // and the tiles after t+1 may stay in flight
-      if (t + 2 < ntiles) wait_oldest<TS::NI, 8>(2 * (min(ntiles - 2 - t, NSK - 2)) + 1);
-      else if (t + 1 < ntiles) wait_vmcnt<TS::NI>();
+    // One step of the pipeline.  At the top: sc holds the scores of tile t and
+    // tmax their row maxima, kf and bf the operands of tile t + 1's, tiles up
+    // to K(t+3), V(t+2) are in flight.  Every LDS read is issued half a step
+    // before its first use, and the vector work sits between the MFMAs:
+    //   first half   S(t+1) = K Q^T        beside the probabilities of tile t
+    //   second half  O += V(t)^T P(t)^T    beside the row maxima of tile t + 1
+    // (scores past the last tile come from a stale slot and are never used)
+    auto step = [&](int t, const f32x16_t& sc, f32x16_t& sn) {
+      // K(t+2) and everything issued before it (V(t)) has landed; V(t+1),
+      // K(t+3) and V(t+2) may stay in flight
+      if (t + NSK < ntiles) wait_vmcnt<3 * TS::NI>();
       else wait_vmcnt<0>();
-      __syncthreads();  // K(t+1), V(t) visible; K(t) and V(t-1) are free
-      // softmax of tile t and O^T += V^T P^T; the scores of tile t+1 are
-      // computed in the same block so that their MFMAs overlap this VALU work
-      // row maximum of tile t and the (lazy) rescale of the running state
-      auto rescale = [&]() {
-        float tmax = fmaxf(st[0], st[1]);
+      __syncthreads();  // K(t+2), V(t) visible; K(t+1) and V(t-1) are read
+      // every ATTN_SEG / KT tiles, the rows of the next segment (the prefetch
+      // has left the segment before this one)
+      if ((t & (ATTN_SEG / KT - 1)) == 0 && t * KT + ATTN_SEG < nk)
+        expand(t / (ATTN_SEG / KT) + 1);
+      // the reference maximum moves only when a row maximum exceeds it by more
+      // than 2^8 in probability (softmax is invariant to the shift; p <= 2^8)
+      if (__any((tmax - m) * scale_log2 > 8.0f)) {
+        const float mnew = fmaxf(m, tmax);
+        const float alpha = __builtin_amdgcn_exp2f((m - mnew) * scale_log2);
+        lpart *= alpha;
 #pragma unroll
-        for (int q = 2; q < 16; ++q) tmax = fmaxf(tmax, st[q]);
-        tmax = max_xor32(tmax);
-        // the reference maximum moves only when a row maximum exceeds it by
-        // more than 2^8 in probability (softmax is invariant to the shift; p <= 2^8)
-        if (__any((tmax - m) * scale_log2 > 8.0f)) {
-          // rows without a kept key so far keep m = -inf (and alpha = 1)
-          const float mnew = fmaxf(m, tmax);
-          const float alpha = mnew == m ? 1.0f : __builtin_amdgcn_exp2f((m - mnew) * scale_log2);
-          lpart *= alpha;
+        for (int b = 0; b < DB; ++b) acc[b] *= alpha;
+        m = mnew;
+      }
+      bf16x8_t vf[2][DB];
+      const uint32_t vo = lds_addr(Vs) + (t % NSV) * (2 * TS::ELEMS) + vofs;
 #pragma unroll
-          for (int b = 0; b < DB; ++b) acc[b] *= alpha;
-          m = mnew;
+      for (int kp = 0; kp < 2; ++kp)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const uint32_t v1 = (vo ^ (64 * db)) + 32 * kp * D;
+          const i16x4_t t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)v1);
+          const i16x4_t t2 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(v1 + 16 * D));
+          vf[kp][db] = __builtin_bit_cast(
+              bf16x8_t, (short __attribute__((ext_vector_type(8)))){t1[0], t1[1], t1[2], t1[3],
+                                                                    t2[0], t2[1], t2[2], t2[3]});
         }
-      };
-      // probabilities of tile t and O^T += V^T P^T in two 16-key steps; step
-      // kp takes scores 8 kp .. 8 kp + 7 (keys 16 kp + 4 hf + r and
-      // 16 kp + 8 + 4 hf + r)
-      auto pv = [&]() {
-        const float nms = m == -INFINITY ? 0.0f : -m * scale_log2;
-        const bf16_t* vs = Vs + (t % NSV) * TS::ELEMS;
+      // probabilities: step kp of the product takes scores 8 kp .. 8 kp + 7
+      // (keys 16 kp + 4 hf + r and 16 kp + 8 + 4 hf + r)
+      constexpr int EP = 16 / KS;  // scores per MFMA of the first half
+      const float nms = -m * scale_log2;
+      bf16x8_t pb[2];
+      float ls[2] = {0.0f, 0.0f};
+      sn = bias_scores();
 #pragma unroll
-        for (int kp = 0; kp < 2; ++kp) {
-          float p[8];
+      for (int s2 = 0; s2 < KS; ++s2) {
+        sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s2], qf[s2], sn, 0, 0, 0);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(fmaf(st[8 * kp + e], scale_log2, nms));
-            lpart += p[e];
-          }
-          bf16x8_t pb;
-#pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            const bf16x2_t two = __builtin_convertvector(f32x2_t{p[e], p[e + 1]}, bf16x2_t);
-            pb[e] = two[0];
-            pb[e + 1] = two[1];
-          }
-#pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            const bf16_t* v1 = vs + vofs[db] + 16 * kp * D;
-            const i16x4_t t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)v1);
-            const i16x4_t t2 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(v1 + 8 * D));
-            const bf16x8_t a = __builtin_bit_cast(
-                bf16x8_t, (short __attribute__((ext_vector_type(8)))){t1[0], t1[1], t1[2], t1[3],
-                                                                      t2[0], t2[1], t2[2], t2[3]});
-            acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb, acc[db], 0, 0, 0);
-          }
+        for (int e = EP * s2; e < EP * (s2 + 1); e += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], scale_log2, nms));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], scale_log2, nms));
+          ls[0] += p0;
+          ls[1] += p1;
+          const bf16x2_t two = __builtin_convertvector(f32x2_t{p0, p1}, bf16x2_t);
+          pb[e / 8][e % 8] = two[0];
+          pb[e / 8][e % 8 + 1] = two[1];
         }
-      };
-      // every tile is computed by every wavefront (keys that its query blocks
-      // did not select have score -inf, so they add nothing); the scores of
-      // tile t+1 (past the end: a stale slot, never used) are computed in the
-      // same block as the probabilities of tile t so that their MFMAs overlap
-      // that VALU work
-      rescale();
-      scores(t + 1, st_next);
-      pv();
-      // the DMAs of tile t+NSK go out after this step's compute: a DMA issue
-      // that stalls on a busy memory system then does not hold the MFMAs back
-      if (nxt < ntiles) issue(nxt);
+        // (the sums are taken here, so that the probabilities need not be kept)
+        asm volatile("" : "+v"(ls[0]), "+v"(ls[1]));
+      }
+      lpart += ls[0] + ls[1];
+      load_k(t + 2);
+      rows_of(t + NSK + 1);  // (past the end: row 0, or a stale row; not issued)
+#pragma unroll
+      for (int kp = 0; kp < 2; ++kp)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kp][db], pb[kp], acc[db], 0, 0, 0);
+      row_max(sn);
+      if (t + NSK + 1 < ntiles) issue_k(t + NSK + 1);
+      if (t + NSK < ntiles) issue_v(t + NSK);
+    };
+    expand(0);
+    __syncthreads();
+    static_assert(NSK == 3 && NSV == 4, "the pipeline's look-ahead");
+    // fill: K(0), K(1) V(0), K(2) V(1); S(0), the operands of S(1); K(3) V(2)
+    f32x16_t s0, s1;
+    if (ntiles > 0) {
+      // (Q has arrived: from here on the counted waits see only the DMAs)
+#pragma unroll
+      for (int s2 = 0; s2 < KS; ++s2) asm volatile("" ::"v"(qf[s2]));
+      asm volatile("" ::"v"(dst));
+#pragma unroll
+      for (int p = 0; p < NSK; ++p) {
+        rows_of(p);  // (past the end: row 0, no bit)
+        issue_k(p);
+        if (p > 0) issue_v(p - 1);
+      }
+      wait_vmcnt<3 * TS::NI>();  // K(0), K(1)
+      __syncthreads();
+      load_k(0);
+      s0 = bias_scores();
+#pragma unroll
+      for (int s2 = 0; s2 < KS; ++s2)
+        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s2], qf[s2], s0, 0, 0, 0);
+      load_k(1);
+      row_max(s0);
+      __syncthreads();  // K(0) is read
+      rows_of(NSK);
+      if (NSK < ntiles) issue_k(NSK);
+      if (NSK - 1 < ntiles) issue_v(NSK - 1);
+    }
+    for (int t = 0; t < ntiles; t += 2) {
+      step(t, s0, s1);
+      if (t + 1 < ntiles) step(t + 1, s1, s0);
     }
     __syncthreads();  // every wavefront is done with this chunk's tables and ring
   }
-  float lsum = lpart + __shfl_xor(lpart, 32, 64);
-  if (qvalid) {
-    const int dst = q_perm[(size_t)h * N + qr];
-    if ((unsigned)dst < (unsigned)N) {
-      const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
-      // natural-log normaliser: the probabilities are exp2((s - m) scale_log2)
-      // of raw scores s, so sum_j exp(s_j / sqrt(d)) = exp(m / sqrt(d)) lsum
-      if (lse && hf == 0)
-        lse[(size_t)h * N + dst] =
-            lsum > 0.0f ? m * (scale_log2 * 0.69314718055994531f) + logf(lsum) : -INFINITY;
-      OT* o = O + ((size_t)h * N + dst) * D + 4 * hf;
+  const float lsum = lpart + __shfl_xor(lpart, 32, 64);
+  if ((unsigned)dst >= (unsigned)N) return;
+  const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+  // natural-log normaliser: the probabilities are exp2((s - m) scale_log2) of
+  // raw scores s, so sum_j exp(s_j / sqrt(d)) = exp(m / sqrt(d)) lsum
+  if (lse && hf == 0)
+    lse[(size_t)h * N + dst] =
+        lsum > 0.0f ? m * (scale_log2 * 0.69314718055994531f) + logf(lsum) : -INFINITY;
+  OT* o = O + ((size_t)h * N + dst) * D + 4 * hf;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int bq4 = 0; bq4 < 4; ++bq4)
-          store_out4<OT>(o + 32 * db + 8 * bq4, acc[db][4 * bq4 + 0] * inv,
-                         acc[db][4 * bq4 + 1] * inv, acc[db][4 * bq4 + 2] * inv,
-                         acc[db][4 * bq4 + 3] * inv);
-    }
-  }
+    for (int b4 = 0; b4 < 4; ++b4)
+      store_out4<OT>(o + 32 * db + 8 * b4, acc[db][4 * b4 + 0] * inv, acc[db][4 * b4 + 1] * inv,
+                     acc[db][4 * b4 + 2] * inv, acc[db][4 * b4 + 3] * inv);
 }
 
 template <typename OT>
@@ -1151,7 +1171,7 @@ size_t attn_grp_offset(int H, int CQ);
 // the families [H][CQ], padded to 16 bytes (the bit rows follow)
 static size_t attn_fam_bytes(int H, int CQ) { return ((size_t)H * CQ * sizeof(int) + 15) & ~(size_t)15; }
 
-template <typename OT, int D, int NW>
+template <typename OT, int D>
 static park_status attn_grp_launch(const void* Qp, const void* Kp, const void* Vp, const int* qo,
                                    const int* ko, const int* kc, const int* ki, const int* qp,
                                    int H, int N, int CQ, int CK, void* plan, float sl2, void* O,
@@ -1170,19 +1190,20 @@ static park_status attn_grp_launch(const void* Qp, const void* Kp, const void* V
               kc, bits, CQ, CK, fam);
   PARK_LAUNCH("attn_plan", k_attn_gplan, dim3(H), dim3(1024), 0, st, qo, (const uint4*)rkey,
               (const int*)fam, N, CQ, CK, GPH, order, spre, grp);
-  // K ring, V ring, score biases, key-block flags, stream table, selection words
+  // K ring, V ring, score biases, stream table, selection words, stream rows
   constexpr size_t lds = (size_t)(2 * ATTN_KSLOTS + 1) * 32 * D * sizeof(bf16_t) +
-                         (size_t)ATTN_KSLOTS * ATTN_LB * 32 * 4 + (size_t)AT_MAXC / 2 * 4 +
-                         (size_t)(ATTN_UCAP + 1) * sizeof(int2) + (size_t)ATTN_UCAP * 2;
+                         (size_t)ATTN_KSLOTS * ATTN_LB * 32 * 2 +
+                         (size_t)(ATTN_UCAP + 1) * sizeof(int2) + (size_t)ATTN_UCAP * 2 +
+                         (size_t)2 * ATTN_SEG * 6;
   static const hipError_t attr = hipFuncSetAttribute(
-      (const void*)k_attn_grp<OT, D, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      (const void*)k_attn_grp<OT, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess)
     return fail(PARK_ERR_HIP, "attention: cannot reserve %zu bytes of LDS", lds);
   // 8 * ceil(items / 8) workgroups: every item owns one (see the remap in the kernel)
   const unsigned nwg = 8u * (((unsigned)H * (unsigned)GPH + 7u) / 8u);
-  PARK_LAUNCH("attn_mfma", (k_attn_grp<OT, D, NW>), dim3(nwg), dim3(64 * NW), lds, st,
-              (const bf16_t*)Qp, (const bf16_t*)Kp, (const bf16_t*)Vp, qo, ko, kc, ki, qp, order,
-              spre, grp, H, N, CQ, CK, GPH, sl2, (OT*)O, lse);
+  PARK_LAUNCH("attn_mfma", (k_attn_grp<OT, D>), dim3(nwg), dim3(2 * ATTN_R), lds, st,
+              (const bf16_t*)Qp, (const bf16_t*)Kp, (const bf16_t*)Vp, qo, ko, bits, qp, order, spre,
+              grp, H, N, CQ, CK, GPH, sl2, (OT*)O, lse);
   return PARK_OK;
 }
 
@@ -1193,9 +1214,9 @@ static park_status attn_mfma_d(const void* Qp, const void* Kp, const void* Vp, c
                                hipStream_t st) {
   const float sl2 = (float)(1.4426950408889634 / sqrt((double)D));
   if (D == 128)
-    return attn_grp_launch<OT, 128, ATTN_R / 32>(Qp, Kp, Vp, qo, ko, kc, ki, qp, H, N, CQ, CK,
+    return attn_grp_launch<OT, 128>(Qp, Kp, Vp, qo, ko, kc, ki, qp, H, N, CQ, CK,
                                                   plan, sl2, O, lse, st);
-  return attn_grp_launch<OT, 64, ATTN_R / 32>(Qp, Kp, Vp, qo, ko, kc, ki, qp, H, N, CQ, CK, plan,
+  return attn_grp_launch<OT, 64>(Qp, Kp, Vp, qo, ko, kc, ki, qp, H, N, CQ, CK, plan,
                                               sl2, O, lse, st);
 }
 

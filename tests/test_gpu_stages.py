@@ -373,6 +373,54 @@ def test_attention_f32_row_and_key_remainders(d, nsel):
         assert np.abs(Lg[h] - lref).max() <= 2.0 ** -24 * (d + N)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", ["tiles", "chunks"])
+def test_attention_pipeline_fill_and_stream_tables(d, shape):
+    # tiles: streams of 1 to 18 key tiles (the fill and drain of the tile
+    # pipeline, a partial last tile, the second and third table of 512 stream
+    # rows); chunks: a union of more key blocks than one stream table (1024),
+    # with rows that have no selected key in the first tables at all
+    rng = np.random.default_rng(23)
+    if shape == "tiles":
+        nks = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 192, 511, 512, 513, 545, 1025]
+        H, N, CQ, CK = len(nks), 1100, 2, 2
+        qoff = np.tile([0, 130, N], (H, 1))
+        koff = np.array([[0, nk, N] for nk in nks])
+        rows = [[np.array([0]), np.array([0])] for _ in range(H)]
+    else:
+        H, N, CQ, CK = 2, 3000, 40, 1500
+        qoff = np.tile(np.arange(0, N + 1, N // CQ), (H, 1))
+        koff = np.stack([np.concatenate([[0], np.sort(rng.choice(np.arange(1, N), CK - 1, False)),
+                                         [N]]) for _ in range(H)])
+        rows = [[np.arange(CK) if u % 4 == 0 else np.arange(CK - 1 - u, CK) if u % 4 == 1 else
+                 np.sort(rng.choice(CK, size=60, replace=False)) for u in range(CQ)]
+                for _ in range(H)]
+    q, k, v = (synth.bf16_round(2 * rng.standard_normal((H, N, d)).astype(np.float32))
+               for _ in range(3))
+    perm = np.stack([rng.permutation(N) for _ in range(H)])
+    kvc = np.array([[len(s) for s in r] for r in rows], np.int32)
+    kvi = np.zeros((H, CQ, CK), np.int32)
+    for h in range(H):
+        for u, s in enumerate(rows[h]):
+            kvi[h, u, :len(s)] = s
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).cuda()
+    Ot, Lt = P.park_block_sparse_attn(*(PT.to_dev(a, "bf16") for a in (q, k, v)), t(qoff), t(koff),
+                                      t(kvc), t(kvi), t(perm), CQ, CK, P.PARK_F32, want_lse=True)
+    Og, Lg = PT.np64(Ot), Lt.double().cpu().numpy()
+    for h in range(H):
+        args = (qoff[h], koff[h], rows[h], perm[h])
+        ref = O.block_sparse_attention(q[h], k[h], v[h], *args)
+        # a bf16 probability is off by at most 2^-8 of itself, so a row by 2^-8
+        # of its mean |v|; the float32 scores and sums add far less than 1e-3
+        bound = 2.0 ** -8 * O.block_sparse_attention(q[h], k[h], np.abs(v[h]), *args) + 1e-3
+        err = np.abs(Og[h] - ref)
+        assert np.all(err <= bound), (h, (err / bound).max())
+        largs = (q[h], k[h], qoff[h], koff[h], rows[h], perm[h])
+        lref = O.block_sparse_lse(*largs)
+        ok, worst = PT.lse_ok(Lg[h], lref, PT.lse_tol(*largs, lref))
+        assert ok, (h, worst)
+
+
 def test_attention_plan_selection_families():
     # query blocks drawn from a few families of nearly equal selections: the
     # plan's family of block u is the smallest v <= u with Jaccard(S_u, S_v)

@@ -2,22 +2,26 @@
 // row gathers X' = X[pi].  Two passes: per-tile histograms, then a stable
 // scatter in which each tile's workgroup first derives its own bases from the
 // histogram table (cluster totals scanned over clusters, plus the counts of
-// the earlier tiles) and then walks its tokens in order one wavefront (64
-// tokens) at a time.  All integer work; the result is unique, so it is
+// the earlier tiles) and then ranks its tokens, every wavefront its own run of
+// consecutive ones.  All integer work; the result is unique, so it is
 // bit-exact and deterministic.
 #include "common.h"
 #include "kernels.h"
 
 namespace park {
 
-// Tokens per sort tile: the smallest power of two >= 256 for which the
-// per-head histogram table (C x tiles) stays below 64K entries, so that each
-// scatter workgroup's pass over the table stays short while the scatter gets
-// as many workgroups as possible.
+constexpr int SORT_NW = 16, SORT_NT = 64 * SORT_NW;  // wavefronts, threads of a scatter workgroup
+constexpr int SORT_MAXC = 2048;
+
+// Tokens per sort tile: 4096 (four steps of 64 per wavefront), doubled until a
+// head has at most 32 tiles, so that a scatter workgroup reads its column of
+// the histogram table in one or two round trips of loads; at most 32768, since
+// the counts inside a tile are 16 bits wide.
 int sort_tile(int H, int N, int C) {
   (void)H;
-  int t = 256;
-  while ((long)C * ((N + t - 1) / t) > 65536 && t < (1 << 30)) t *= 2;
+  (void)C;
+  int t = 4096;
+  while ((N + t - 1) / t > 32 && t < 32768) t *= 2;
   return t;
 }
 
@@ -27,71 +31,126 @@ int sort_tiles(int H, int N, int C) {
 }
 
 // thist[h][tile][v] = #{ i in tile : z_i = v }
-__global__ __launch_bounds__(256) void k_sort_hist(const int* __restrict__ labels, int N, int C,
-                                                   int tile_sz, int* __restrict__ thist) {
+__global__ __launch_bounds__(SORT_NT) void k_sort_hist(const int* __restrict__ labels, int N, int C,
+                                                       int tile_sz, int* __restrict__ thist) {
   extern __shared__ int hist[];
   const int h = blockIdx.y, tile = blockIdx.x, nt = gridDim.x;
-  for (int v = threadIdx.x; v < C; v += 256) hist[v] = 0;
+  for (int v = threadIdx.x; v < C; v += SORT_NT) hist[v] = 0;
   __syncthreads();
   const int i0 = tile * tile_sz, i1 = min(N, i0 + tile_sz);
   const int* z = labels + (size_t)h * N;
-  // eight loads in flight per thread
-  for (int c0 = i0; c0 < i1; c0 += 8 * 256) {
-    int v[8];
+  // four loads in flight per thread
+  for (int c0 = i0; c0 < i1; c0 += 4 * SORT_NT) {
+    int v[4];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int i = c0 + 256 * k + threadIdx.x;
+    for (int k = 0; k < 4; ++k) {
+      const int i = c0 + SORT_NT * k + threadIdx.x;
       v[k] = i < i1 ? z[i] : -1;
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < 4; ++k)
       if ((unsigned)v[k] < (unsigned)C) atomicAdd(&hist[v[k]], 1);
   }
   __syncthreads();
   int* out = thist + ((size_t)h * nt + tile) * C;
-  for (int v = threadIdx.x; v < C; v += 256) out[v] = hist[v];
+  for (int v = threadIdx.x; v < C; v += SORT_NT) out[v] = hist[v];
 }
 
-// Stable scatter.  Bases first: thread v sums cluster v's counts over the
-// tiles before this one and over all tiles (table rows read coalesced, eight
-// in flight), the totals are scanned over clusters, and base_v = start_v +
-// earlier counts; tile 0 also writes the cluster offsets (o[C] = N).  Then
-// wavefront 0 walks the tile's tokens in increasing order; equal labels
-// inside the wavefront are matched with one ballot per label bit.
-__global__ __launch_bounds__(256) void k_sort_scatter(const int* __restrict__ labels, int N, int C,
-                                                      int nbits, int tile_sz,
-                                                      const int* __restrict__ thist,
-                                                      int* __restrict__ perm,
-                                                      int* __restrict__ offsets) {
-  extern __shared__ int run[];  // [C] bases, then [C] totals
-  __shared__ int wsum[4];
+// Stable scatter of one tile (grid: tiles x heads; thist may be null when a
+// head is one tile).
+//  1. Thread v sums cluster v's counts over the tiles before this one and over
+//     all tiles (16 table rows in flight); the totals are scanned over the
+//     clusters: base_v = start_v + earlier counts.  Tile 0 also writes the
+//     cluster offsets (o[C] = N).
+//  2. Every wavefront counts the clusters of its own tokens (LDS, 16-bit
+//     halves), and the counts become, per cluster, the tokens of the
+//     wavefronts before it.
+//  3. Every wavefront walks its tokens in order, 64 at a time; equal labels
+//     inside a step are matched with one ballot per label bit.
+// What bounds it: a chain of round trips, not the bytes.  One wavefront per
+// tile walking 64 steps alone, after 40 dependent batches of table loads per
+// thread, took 66 us at 3 x 119056 tokens, C = 1861 (14 us at 12 x 17019,
+// C = 266; 14.5 us at 1 x 4096; 51 us at 40 x 75600, C = 1182); sixteen
+// wavefronts with four steps each and 30-row tables take 14.6 us (8, 6.5, 35).
+__global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict__ labels, int N, int C,
+                                                          int nbits, int tile_sz,
+                                                          const int* __restrict__ thist,
+                                                          int* __restrict__ perm,
+                                                          int* __restrict__ offsets) {
+  extern __shared__ uint32_t sort_lds[];
+  const int C2 = (C + 1) / 2;       // 32-bit words of one wavefront's counts
+  uint32_t* cnt = sort_lds;         // [SORT_NW][C2]: two clusters per word
+  int* base = (int*)(cnt + SORT_NW * C2);  // [C]
+  __shared__ int wsum[SORT_NW];
   const int h = blockIdx.y, tile = blockIdx.x, nt = gridDim.x, tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
-  const int* b = thist + (size_t)h * nt * C;
-  int* tot = run + C;
-  for (int v = tid; v < C; v += 256) {
-    int before = 0, all = 0;
-    for (int t0 = 0; t0 < nt; t0 += 8) {
-      int c[8];
+  const int* z = labels + (size_t)h * N;
+  const int i0 = tile * tile_sz, i1 = min(N, i0 + tile_sz);
+  const int share = tile_sz / SORT_NW;  // tokens of a wavefront (a multiple of 256)
+  const int j0 = i0 + wid * share, j1 = min(i1, j0 + share);
+  for (int e = tid; e < SORT_NW * C2; e += SORT_NT) cnt[e] = 0u;
+  __syncthreads();
+  uint32_t* cw = cnt + wid * C2;
+  for (int c0 = j0; c0 < j1; c0 += 256) {
+    int v[4];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) c[k] = t0 + k < nt ? b[(size_t)(t0 + k) * C + v] : 0;
+    for (int k = 0; k < 4; ++k) {
+      const int i = c0 + 64 * k + lane;
+      v[k] = i < j1 ? z[i] : -1;
+    }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        all += c[k];
-        before += t0 + k < tile ? c[k] : 0;
+    for (int k = 0; k < 4; ++k)
+      if ((unsigned)v[k] < (unsigned)C) atomicAdd(&cw[v[k] >> 1], 1u << (16 * (v[k] & 1)));
+  }
+  // thread tid owns clusters tid and tid + SORT_NT in the table, and the
+  // consecutive ones tid * per + k in the scan
+  int before[SORT_MAXC / SORT_NT], all[SORT_MAXC / SORT_NT];
+#pragma unroll
+  for (int q = 0; q < SORT_MAXC / SORT_NT; ++q) {
+    const int v = tid + q * SORT_NT;
+    before[q] = all[q] = 0;
+    if (v < C && thist) {
+      const int* b = thist + (size_t)h * nt * C + v;
+      for (int t0 = 0; t0 < nt; t0 += 16) {
+        int c[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) c[k] = b[(size_t)min(t0 + k, nt - 1) * C];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          all[q] += t0 + k < nt ? c[k] : 0;
+          before[q] += t0 + k < tile ? c[k] : 0;
+        }
       }
     }
-    run[v] = before;
-    tot[v] = all;
   }
   __syncthreads();
-  // exclusive scan of tot over the clusters: thread tid owns clusters
-  // [tid * per, (tid + 1) * per)
-  const int per = (C + 255) / 256;
-  int s = 0;
-  for (int k = 0; k < per; ++k) {
+  // counts -> tokens of earlier wavefronts (two 16-bit clusters per word: a
+  // tile's 32768 tokens never carry from one into the other)
+  for (int e = tid; e < C2; e += SORT_NT) {
+    uint32_t run = 0u;
+#pragma unroll
+    for (int w = 0; w < SORT_NW; ++w) {
+      const uint32_t x = cnt[w * C2 + e];
+      cnt[w * C2 + e] = run;
+      run += x;
+    }
+    if (!thist) {  // one tile: these are the cluster totals
+      base[2 * e] = (int)(run & 0xffffu);
+      if (2 * e + 1 < C) base[2 * e + 1] = (int)(run >> 16);
+    }
+  }
+  if (thist)
+#pragma unroll
+    for (int q = 0; q < SORT_MAXC / SORT_NT; ++q)
+      if (tid + q * SORT_NT < C) base[tid + q * SORT_NT] = all[q];
+  __syncthreads();
+  const int per = (C + SORT_NT - 1) / SORT_NT;
+  int s = 0, tv[SORT_MAXC / SORT_NT];
+#pragma unroll
+  for (int k = 0; k < SORT_MAXC / SORT_NT; ++k) {
     const int v = tid * per + k;
-    s += v < C ? tot[v] : 0;
+    tv[k] = k < per && v < C ? base[v] : 0;
+    s += tv[k];
   }
   int inc = s;
 #pragma unroll
@@ -102,53 +161,54 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const int* __restrict__ la
   if (lane == 63) wsum[wid] = inc;
   __syncthreads();
   int pre = inc - s;
-  for (int q = 0; q < wid; ++q) pre += wsum[q];
+#pragma unroll
+  for (int q = 0; q < SORT_NW; ++q) pre += q < wid ? wsum[q] : 0;
   int* off = offsets + (size_t)h * (C + 1);
-  for (int k = 0; k < per; ++k) {
+#pragma unroll
+  for (int k = 0; k < SORT_MAXC / SORT_NT; ++k) {
     const int v = tid * per + k;
-    if (v < C) {
-      const int start = pre;
-      pre += tot[v];
-      run[v] += start;
-      if (tile == 0) off[v] = start;
+    if (k < per && v < C) {
+      base[v] = pre;
+      if (tile == 0) off[v] = pre;
+      pre += tv[k];
     }
   }
   if (tile == 0 && tid == 0) off[C] = N;
   __syncthreads();
-  if (wid != 0) return;
-  const int i0 = tile * tile_sz, i1 = min(N, i0 + tile_sz);
-  const int* z = labels + (size_t)h * N;
+#pragma unroll
+  for (int q = 0; q < SORT_MAXC / SORT_NT; ++q)
+    if (tid + q * SORT_NT < C) base[tid + q * SORT_NT] += before[q];
+  __syncthreads();
   int* p = perm + (size_t)h * N;
+  uint16_t* cw16 = (uint16_t*)cw;
   const uint64_t lt = (1ull << lane) - 1ull;
   const uint64_t gt = ~((2ull << lane) - 1ull);
-  // the labels of 16 wavefront steps are loaded together (latency once per
-  // 1024 tokens instead of once per step)
-  constexpr int UN = 16;
-  for (int c00 = i0; c00 < i1; c00 += 64 * UN) {
-    int vv[UN];
+  for (int c0 = j0; c0 < j1; c0 += 256) {
+    int vv[4];
 #pragma unroll
-    for (int k = 0; k < UN; ++k) {
-      const int i = c00 + 64 * k + lane;
-      vv[k] = i < i1 ? z[i] : -1;
+    for (int k = 0; k < 4; ++k) {
+      const int i = c0 + 64 * k + lane;
+      vv[k] = i < j1 ? z[i] : -1;
     }
 #pragma unroll
-    for (int k = 0; k < UN; ++k) {
-      if (c00 + 64 * k >= i1) break;
-      const int i = c00 + 64 * k + lane;
+    for (int k = 0; k < 4; ++k) {
+      const int i = c0 + 64 * k + lane;
       const int v = vv[k];
-      const bool ok = i < i1 && (unsigned)v < (unsigned)C;
+      const bool ok = (unsigned)v < (unsigned)C;
       uint64_t m = __ballot(ok);
+      if (m == 0ull) break;
       for (int bit = 0; bit < nbits; ++bit) {
         const bool set = (v >> bit) & 1;
         const uint64_t B = __ballot(ok && set);
         m &= set ? B : ~B;
       }
       const int rank = __popcll(m & lt);
-      if (ok) p[run[v] + rank] = i;
-      // one wavefront, whose LDS accesses complete in order; the fences keep
-      // the compiler from moving the base reads and updates across each other
+      const int own = ok ? (int)cw16[v] : 0;
+      if (ok) p[base[v] + own + rank] = i;
+      // the wavefront's own counts, whose LDS accesses complete in order; the
+      // fences keep the compiler from moving reads and updates across each other
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      if (ok && (m & gt) == 0) run[v] += rank + 1;
+      if (ok && (m & gt) == 0) cw16[v] = (uint16_t)(own + rank + 1);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
   }
@@ -160,10 +220,17 @@ park_status launch_count_sort(const int* labels, int H, int N, int C, int* thist
   const int nt = (N + tsz - 1) / tsz;
   int nbits = 1;
   while ((1 << nbits) < C) ++nbits;
-  PARK_LAUNCH("sort_hist", k_sort_hist, dim3(nt, H), dim3(256), (size_t)C * sizeof(int), st, labels,
-              N, C, tsz, thist);
-  PARK_LAUNCH("sort_scatter", k_sort_scatter, dim3(nt, H), dim3(256), (size_t)2 * C * sizeof(int),
-              st, labels, N, C, nbits, tsz, (const int*)thist, perm, offsets);
+  // one tile per head: the scatter counts for itself
+  if (nt > 1)
+    PARK_LAUNCH("sort_hist", k_sort_hist, dim3(nt, H), dim3(SORT_NT), (size_t)C * sizeof(int), st,
+                labels, N, C, tsz, thist);
+  const size_t lds = (size_t)SORT_NW * ((C + 1) / 2) * 4 + (size_t)C * 4;
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)k_sort_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          SORT_NW * SORT_MAXC / 2 * 4 + SORT_MAXC * 4);
+  if (attr != hipSuccess) return fail(PARK_ERR_HIP, "sort: cannot reserve %zu bytes of LDS", lds);
+  PARK_LAUNCH("sort_scatter", k_sort_scatter, dim3(nt, H), dim3(SORT_NT), lds, st, labels, N, C,
+              nbits, tsz, (const int*)(nt > 1 ? thist : nullptr), perm, offsets);
   return PARK_OK;
 }
 

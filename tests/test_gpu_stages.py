@@ -373,6 +373,29 @@ def test_attention_f32_row_and_key_remainders(d, nsel):
         assert np.abs(Lg[h] - lref).max() <= 2.0 ** -24 * (d + N)
 
 
+@pytest.mark.parametrize("N,C", [(1, 1), (65, 2), (4096, 63), (4097, 511), (9000, 2047),
+                                 (70001, 2048), (140000, 33)])
+def test_sort_tiles_and_listed_tokens(N, C):
+    # one round of k-means on small integers: many tokens are exactly as far
+    # from several centroids, so most of them are listed for the float64 pass
+    # (ties to the lowest id), and the permutation is the stable argsort of the
+    # labels over one sort tile, several, and tiles of twice the size
+    rng = np.random.default_rng(N + C)
+    x = rng.integers(-2, 3, size=(1, N, 64)).astype(np.float32)
+    r = P.park_cluster_keys(PT.to_dev(x, "bf16"), C, 1, seed=3, side=0,
+                            metric=P.PARK_METRIC_EUCLID)
+    z = r["labels"][0].cpu().numpy()
+    mu = x[0][O.init_indices(N, C, 3, 0, 0)].astype(np.float64)
+    ref = np.empty(N, np.int64)
+    for lo in range(0, N, 8192):  # integers: every product and sum is exact
+        xs = x[0, lo:lo + 8192].astype(np.float64)
+        ref[lo:lo + 8192] = np.argmin((mu * mu).sum(1) - 2.0 * xs @ mu.T, axis=1)
+    assert np.array_equal(z, ref)
+    assert np.array_equal(r["perm"][0].cpu().numpy(), np.argsort(z, kind="stable"))
+    off = r["offsets"][0].cpu().numpy()
+    assert np.array_equal(off, np.concatenate([[0], np.cumsum(np.bincount(z, minlength=C))]))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", ["tiles", "chunks"])
 def test_attention_pipeline_fill_and_stream_tables(d, shape):

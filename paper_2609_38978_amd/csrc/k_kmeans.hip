@@ -10,6 +10,8 @@
 // image under R^T of the transformed-space means (linearity).
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -134,8 +136,18 @@ __global__ void k_seed_centroids(const T* __restrict__ X, const int* __restrict_
 // magnitudes involved; r2[a] = (sqrt(dmax) + move)^2, rounded up, or -1 for
 // a cluster the sort left empty.  rmode >= 1 then clears dmax for the
 // coming assignment.
-template <int D, int NT>
-__global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
+//
+// What bounds it: latency (16 centroids read the metric's 128 KB once).  The
+// product W = M Gbar of a workgroup's 16 centroids runs on
+// v_mfma_f64_16x16x4_f64, wavefront w the columns 16 w .. 16 w + 15, with all
+// of its metric and centroid operands in flight at once; the dot products over
+// D columns that it replaces were chains of dependent batches of loads:
+// 39 -> 19 us at 3 x 119056 tokens, C = 1861; 12 -> 8 us at 8 x 16384, C = 256.
+// Large layers are near the memory's rate (71 -> 65 us at 40 x 75600: 200 MB).
+typedef double f64x4k_t __attribute__((ext_vector_type(4)));
+
+template <int D>
+__global__ __launch_bounds__(4 * D) void k_prep(const double* __restrict__ mu,
                                               const double* __restrict__ Gbar, int C,
                                               double* __restrict__ w, double* __restrict__ b,
                                               bf16_t* __restrict__ w3,
@@ -146,67 +158,80 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
                                               const int* __restrict__ offsets,
                                               double* __restrict__ r2,
                                               unsigned long long* __restrict__ dmax, int rmode) {
-  // NT threads: D lanes per centroid group, 16 / (NT / D) centroids per
-  // thread.  1024 threads shorten each thread's float64 chain over the D
-  // columns (small grids); 256 read the metric rows fewer times (large grids)
-  constexpr int CB = 16, NG = NT / D, PER = CB / NG;
-  static_assert(PER >= 1 && CB % NG == 0, "centroid groups");
+  constexpr int CB = 16, NT = 4 * D;
   __shared__ double ms[CB][D];
   __shared__ double ws[CB][D + 1];
   __shared__ float fnl[CB], fel[CB];
   const int h = blockIdx.y, v0 = blockIdx.x * CB, tid = threadIdx.x;
+  if (Gbar) {
+    // operand k-index: steps 2 j and 2 j + 1 take dimensions 8 j + 2 (l / 16)
+    // and the next one of both operands
+    const int w16 = 16 * (tid >> 6), c = tid & 15, kq = (tid >> 4) & 3;
+    const double* G = Gbar + (size_t)h * D * D;
+    const double* mr = mu + ((size_t)h * C + min(v0 + c, C - 1)) * D;
+    double2 am[D / 8];
+    double g0[D / 8], g1[D / 8];
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) am[j] = *(const double2*)(mr + 8 * j + 2 * kq);
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) {
+      g0[j] = G[(size_t)(8 * j + 2 * kq) * D + w16 + c];
+      g1[j] = G[(size_t)(8 * j + 2 * kq + 1) * D + w16 + c];
+    }
+    f64x4k_t acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) {
+      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(am[j].x, g0[j], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(am[j].y, g1[j], acc1, 0, 0, 0);
+    }
+    // register i: centroid kq + 4 i, column c
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ws[kq + 4 * i][w16 + c] = acc0[i] + acc1[i];
+  }
   for (int e = tid; e < CB * D; e += NT) {
     const int r = e / D, a = e % D;
-    ms[r][a] = (v0 + r < C) ? mu[((size_t)h * C + v0 + r) * D + a] : 0.0;
+    const double m = (v0 + r < C) ? mu[((size_t)h * C + v0 + r) * D + a] : 0.0;
+    ms[r][a] = m;
+    if (!Gbar) ws[r][a] = m;
   }
   __syncthreads();
-  const int a = tid % D, grp = tid / D;
-  double acc[PER];
-  if (Gbar) {
-    const double* G = Gbar + (size_t)h * D * D;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) acc[k] = 0.0;
-    // sixteen metric rows' loads issued together, then their products (the
-    // same fma order over the columns)
-    for (int c0 = 0; c0 < D; c0 += 16) {
-      double g[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) g[j] = G[(size_t)(c0 + j) * D + a];
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-#pragma unroll
-        for (int k = 0; k < PER; ++k) acc[k] = fma(g[j], ms[grp + NG * k][c0 + j], acc[k]);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) acc[k] = ms[grp + NG * k][a];
-  }
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int r = grp + NG * k;
-    ws[r][a] = acc[k];
-    if (v0 + r < C) {
+  // (w itself is written at the end: the radius bound reads the old w)
+  if (w3 || m2)
+    for (int e = 2 * tid; e < CB * D; e += 2 * NT) {
+      const int r = e / D, a = e % D;
+      if (v0 + r >= C) break;
       const size_t o = ((size_t)h * C + v0 + r) * D + a;
-      // (w itself is written at the end: the radius bound reads the old w)
       if (w3) {
         // w = w1 + w2 + w3 + r with bf16 parts and |r| <= 2^-24 |w| (1 + 2^-7)
-        const bf16_t p1 = f2bf((float)acc[k]);
-        const double r1 = acc[k] - (double)bf2f(p1);
-        const bf16_t p2 = f2bf((float)r1);
-        const double r2 = r1 - (double)bf2f(p2);
-        w3[o] = p1;
-        w3[o + plane] = p2;
-        w3[o + 2 * plane] = f2bf((float)r2);
+        uint32_t p1 = 0u, p2 = 0u, p3 = 0u;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const double x = ws[r][a + k];
+          const bf16_t q1 = f2bf((float)x);
+          const double r1 = x - (double)bf2f(q1);
+          const bf16_t q2 = f2bf((float)r1);
+          const double r2 = r1 - (double)bf2f(q2);
+          p1 |= (uint32_t)q1 << (16 * k);
+          p2 |= (uint32_t)q2 << (16 * k);
+          p3 |= (uint32_t)f2bf((float)r2) << (16 * k);
+        }
+        *(uint32_t*)(w3 + o) = p1;
+        *(uint32_t*)(w3 + o + plane) = p2;
+        *(uint32_t*)(w3 + o + 2 * plane) = p3;
       }
       if (m2) {  // the centroid itself in two bf16 parts (candidate filter)
-        const double mv = ms[r][a];
-        const bf16_t q1 = f2bf((float)mv);
-        m2[o] = q1;
-        m2[o + plane] = f2bf((float)(mv - (double)bf2f(q1)));
+        uint32_t p1 = 0u, p2 = 0u;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const double mv = ms[r][a + k];
+          const bf16_t q1 = f2bf((float)mv);
+          p1 |= (uint32_t)q1 << (16 * k);
+          p2 |= (uint32_t)f2bf((float)(mv - (double)bf2f(q1))) << (16 * k);
+        }
+        *(uint32_t*)(m2 + o) = p1;
+        *(uint32_t*)(m2 + o + plane) = p2;
       }
     }
-  }
-  __syncthreads();
   // b_v and |w_v|^2: 16 lanes per centroid (the first four wavefronts),
   // partial sums added in a fixed tree
   if (tid < 256) {
@@ -1018,6 +1043,131 @@ __global__ __launch_bounds__(256) void k_refine_cand(const bf16_t* __restrict__ 
   }
 }
 
+// Float64 assignment of the listed tokens against every centroid, on
+// v_mfma_f64_16x16x4_f64: the tokens the fast pass could not certify when the
+// head has few centroids of 64 dimensions.  A workgroup takes 16 listed
+// tokens, wavefront w the 16-centroid tiles w, w + 8, ...; lane l holds the
+// scores of token l % 16, so each keeps a running minimum (ties to the lowest
+// id) and the lanes and wavefronts are merged at the end.
+//
+// What bounds it: latency, then the float64 matrix rate.  k_refine_cand sweeps
+// the centroids once more in bf16 to find each token's candidates, then scores
+// those: 17.0 us a round at 12 x 17019 tokens, d = 64, C = 266, most of it the
+// chain list, tokens, ring of tiles, candidates; this 13.5 us.  At d = 128 the
+// float64 tiles cost twice as much and the sweep is the better one (8 x 16384,
+// C = 256: 20.1 us against 26.1).
+template <int D>
+__global__ __launch_bounds__(512) void k_refine_all(const bf16_t* __restrict__ X,
+                                                    const double* __restrict__ w64,
+                                                    const double* __restrict__ b64, int N, int C,
+                                                    const int* __restrict__ flags,
+                                                    const int* __restrict__ nflag,
+                                                    int* __restrict__ labels, int* status) {
+  constexpr int TC = 16, KD = D / 8, NW = 8;
+  __shared__ int wsc[NW], spos[TC];
+  __shared__ double rb[NW][TC];
+  __shared__ int ri[NW][TC];
+  const int h = blockIdx.y, tid = threadIdx.x, l = tid & 63, c = l & 15, kq = l >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // thread tid: list lengths of tiles tid * per .. ; pre: listed tokens before them
+  const int NT = (N + kmeans_tile - 1) / kmeans_tile, per = (NT + 64 * NW - 1) / (64 * NW);
+  const int* nf = nflag + (size_t)h * NT;
+  const int tb0 = min(tid * per, NT), tb1 = min(tb0 + per, NT);
+  int own = 0;
+  for (int t = tb0; t < tb1; ++t) own += min(max(nf[t], 0), kmeans_tile);
+  int inc = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(inc, o, 64);
+    if (l >= o) inc += y;
+  }
+  if (l == 63) wsc[w] = inc;
+  __syncthreads();
+  int pre = inc - own, cnt = 0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    pre += q < w ? wsc[q] : 0;
+    cnt += wsc[q];
+  }
+  const bf16_t* Xh = X + (size_t)h * N * D;
+  const double* wh = w64 + (size_t)h * C * D;
+  const double* bh = b64 + (size_t)h * C;
+  const int ntile = (C + 15) / 16;
+  for (int lo = blockIdx.x * TC; lo < cnt; lo += gridDim.x * TC) {
+    __syncthreads();  // the previous chunk's slots and minima are read
+    if (tid < TC) spos[tid] = -1;
+    __syncthreads();
+    for (int t = tb0, at = pre; t < tb1 && at < lo + TC; ++t) {
+      const int n = min(max(nf[t], 0), kmeans_tile);
+      for (int i = max(at, lo); i < min(at + n, lo + TC); ++i) spos[i - lo] = t * kmeans_tile + (i - at);
+      at += n;
+    }
+    __syncthreads();
+    const int sp = spos[c];
+    int tok = sp >= 0 ? flags[(size_t)h * N + sp] : -1;
+    tok = (unsigned)tok < (unsigned)N ? tok : -1;
+    // operand k-index: steps 2 j and 2 j + 1 take dimensions 8 j + 2 kq and the next
+    uint32_t xr[KD];
+#pragma unroll
+    for (int j = 0; j < KD; ++j) xr[j] = *(const uint32_t*)(Xh + (size_t)max(tok, 0) * D + 8 * j + 2 * kq);
+    double best = INFINITY;
+    int bi = 0x7fffffff;
+    for (int t = w; t < ntile; t += NW) {
+      const double* wr = wh + (size_t)min(16 * t + c, C - 1) * D + 2 * kq;
+      double2 a[KD];
+      double bv[4];
+#pragma unroll
+      for (int j = 0; j < KD; ++j) a[j] = *(const double2*)(wr + 8 * j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bv[i] = bh[min(16 * t + kq + 4 * i, C - 1)];
+      f64x4k_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+#pragma unroll
+      for (int j = 0; j < KD; ++j) {
+        s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].x, (double)__uint_as_float(xr[j] << 16), s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[j].y, (double)__uint_as_float(xr[j] & 0xffff0000u), s1,
+                                                  0, 0, 0);
+      }
+      // register i: centroid 16 t + kq + 4 i of token c
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int v = 16 * t + kq + 4 * i;
+        const double sc = fma(-2.0, s0[i] + s1[i], bv[i]);
+        if (v < C && sc < best) {
+          best = sc;
+          bi = v;
+        }
+      }
+    }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+      const double ob = __shfl_xor(best, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ob < best || (ob == best && oi < bi)) {
+        best = ob;
+        bi = oi;
+      }
+    }
+    if (l < TC) {
+      rb[w][l] = best;
+      ri[w][l] = bi;
+    }
+    __syncthreads();
+    if (tid < TC && tok >= 0) {
+#pragma unroll
+      for (int q = 0; q < NW; ++q)
+        if (rb[q][tid] < best || (rb[q][tid] == best && ri[q][tid] < bi)) {
+          best = rb[q][tid];
+          bi = ri[q][tid];
+        }
+      if (!isfinite(best) || (unsigned)bi >= (unsigned)C) {
+        raise_status(status, ST_NONFINITE);
+        bi = 0;
+      }
+      labels[(size_t)h * N + tok] = bi;
+    }
+  }
+}
+
 // Exact float64 assignment: labels[j] = argmin_v (b_v - 2 x_j . w_v), ties to
 // the lowest v.  TM tokens x 64 centroids per step (centroids staged in LDS
 // in 32-dim slices), 4 tokens x (64 / (256 / (TM / 4))) centroids per
@@ -1294,18 +1444,10 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     const int rmode = !filt || t == 0 ? 0 : (t == 1 || exact_radius ? 1 : 2);
     double* r2 = filt ? kb.kf->r2 : nullptr;
     unsigned long long* dmax = filt ? kb.kf->dmax : nullptr;
-    if ((long)nbm * H < 512)
-      PARK_LAUNCH("kmeans_prep", (k_prep<D, 1024>), dim3(nbm, H), dim3(1024), 0, st,
-                  (const double*)kb.mu, Gbar, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
-                  fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
-                  fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax,
-                  rmode);
-    else
-      PARK_LAUNCH("kmeans_prep", (k_prep<D, 256>), dim3(nbm, H), dim3(256), 0, st,
-                  (const double*)kb.mu, Gbar, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
-                  fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
-                  fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax,
-                  rmode);
+    PARK_LAUNCH("kmeans_prep", k_prep<D>, dim3(nbm, H), dim3(4 * D), 0, st,
+                (const double*)kb.mu, Gbar, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
+                fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
+                fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax, rmode);
     if constexpr (fast) {
       if (filt && t > 0)
         PARK_TRY(launch_kfilter_round((const bf16_t*)X, H, N, D, C, kb, *kb.kf, rmode == 1, st));
@@ -1319,13 +1461,18 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
                     dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
                     (const float*)kb.b32, kmeans_cpad(C), (const float*)kb.wn, (const float*)kb.eb,
                     (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, kb.flagu, kb.nflag);
-      PARK_LAUNCH("kmeans_refine64", k_refine_cand<D>, dim3(8 * ((rg * H + 7) / 8)),
-                  dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
-                  (const float*)kb.b32, (const float*)kb.wn, (const float*)kb.eb, kmeans_cpad(C),
-                  (const double*)kb.w, (const double*)kb.b, H, N, C, rg, (const int*)kb.flags,
-                  (const float*)kb.flagu, (const int*)kb.nflag, kb.labels, status,
-                  filt && t > 0 ? (const double*)kb.kf->xn : nullptr,
-                  filt && t > 0 ? kb.kf->dmax : nullptr);
+      if (D == 64 && C < 512)  // few, short centroids: every one in float64 (see k_refine_all)
+        PARK_LAUNCH("kmeans_refine64", k_refine_all<D>, dim3(std::min((N + 255) / 256, 1024), H),
+                    dim3(512), 0, st, (const bf16_t*)X, (const double*)kb.w, (const double*)kb.b, N,
+                    C, (const int*)kb.flags, (const int*)kb.nflag, kb.labels, status);
+      else
+        PARK_LAUNCH("kmeans_refine64", k_refine_cand<D>, dim3(8 * ((rg * H + 7) / 8)),
+                    dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
+                    (const float*)kb.b32, (const float*)kb.wn, (const float*)kb.eb, kmeans_cpad(C),
+                    (const double*)kb.w, (const double*)kb.b, H, N, C, rg, (const int*)kb.flags,
+                    (const float*)kb.flagu, (const int*)kb.nflag, kb.labels, status,
+                    filt && t > 0 ? (const double*)kb.kf->xn : nullptr,
+                    filt && t > 0 ? kb.kf->dmax : nullptr);
     } else {
       PARK_LAUNCH("kmeans_assign64", (k_assign64<T, D, 64>), dim3((N + 63) / 64, H), dim3(256), 0, st,
                   X, (const double*)kb.w, (const double*)kb.b, N, C, (const int*)nullptr,

@@ -887,95 +887,267 @@ __global__ __launch_bounds__(256) void k_select_band(const double* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Fast PAMA on bf16 MFMA (bf16 queries), with a per-row error bound.
+// Fast PAMA on f16 MFMA (bf16 queries), with a per-row error bound.
 //
-// Centroids (float) are split into three bf16 parts, c = c1 + c2 + c3 + r with
-// |r| <= 2^-24 |c|.  t = q.c is accumulated as q.(c2 + c3) in one chain over
+// Centroids (float) are split into two f16 parts, c = c1 + c2 + r with
+// |r| <= 2^-22 |c|: eleven significand bits each, so two parts hold what took
+// three bf16 parts (the sweep was bound by its MFMAs and vector operations
+// together: 24 MFMAs per 32 x 32 tile, 8.78 ms at 24 x 119056 tokens,
+// C = 1861; 16 take 7.3 ms, and 4.44 -> 3.3 ms at 24 x 115200, C = 1024).  The range of f16 is met by powers of two:
+// every tile of 32 centroids is scaled so that its largest element lies in
+// [2^14, 2^15), every chunk of 32 queries likewise (a bf16 value has eight
+// bits, exact in f16), and the logit's factor takes both back.  Elements below
+// 2^-28 of the largest may lose bits or flush to zero: an error of at most
+// 2^-28 of the largest element each, 2^-28 sqrt(D) of the norm together.
+//   t = q.c is accumulated as q.c2 in one chain over
 // all dimensions plus q.c1 in 32-dimension segments, each a fresh
-// accumulator except the last, which starts from the finished c2 + c3 chain;
-// the D/32 segment results are added on the VALU.  With 2^-23 per MFMA
-// addition and 2^-24 per VALU rounding,
-//   |t^ - t| <= et |q| |c|,  et = 2^-24 1.01 + (32 2^-23 + (D/32-1) 2^-24) 1.01
-//                                + 2^-8 1.01 (2D) 2^-23 + 2^-24 1.01
-// (residual r; the c1 segments and their sum; the c2 + c3 chain; the last
-// segment's 32 additions onto the seed, 32 2^-23 |q.(c2 + c3)| < 2^-24 |q||c|).
-// The logit adds log2(e) log n_v, precomputed in float (k_cen_prep).
-// The logit S = t/sqrt(d) + log n is formed with one FMA; its error
-//   e_i = isd (et + 1.01 2^-24) |q_i| cmax + 1.01 2^-24 (2 lgmax + 1.01 isd |q_i| cmax)
-// bounds every centroid of query i (cmax = max |c_v|, lgmax = max log n_v).
-// Pass 1 keeps, per lane and query, an online (max, sum of exp2); lanes are
-// merged at the end.  Pass 2 recomputes the logits and accumulates
-// P = exp2((S - m) log2 e) / Z over the queries into per-wavefront LDS
-// columns, which are added in wavefront order (deterministic).
-// Relative error of each W^_uv:
-//   delta_u = max_i (2.02 e_i + dZ_i + 2^-23 (3 + 1.5 argmax_i)) + 17 2^-24
-// where argmax_i = 2 (isd |q_i| cmax + lgmax) log2 e bounds the exp2
-// arguments (an argument x carries a relative exp2 error <= 2^-23 (2 + 1.5|x|))
-// and dZ_i bounds the float normaliser (see the kernel); values below float's
-// normal range carry an extra absolute error, handled by the selection.  Rows whose selection this bound cannot certify are recomputed
-// in float64.
+// accumulator except the last, which starts from the finished c2 chain;
+// the D/32 segment results are added on the VALU.  Products of f16 values are
+// exact in float.  With 2^-23 per MFMA addition and 2^-24 per VALU rounding,
+//   |t^ - t| <= et |q| |c| + 2^-28 sqrt(D) qmax |c|,
+//   et = 2^-22 1.01 + (32 2^-23 + (D/32-1) 2^-24) 1.01
+//        + 2^-11 1.01 (D + 32) 2^-23 + 2^-28 sqrt(D) 1.01
+// (residual r; the c1 segments and their sum; the c2 chain and the last
+// segment's 32 additions onto it; flushed centroid elements; qmax the largest
+// norm of the query's chunk: flushed query elements).  Tiles or chunks whose
+// largest element is below 2^-100 or not finite get an infinite bound.
+//
+// Softmax in base 2 with the sizes as weights: P_iv = n_v 2^(x_iv) / z_i,
+//   x_iv = t_iv f - R_i + B,  f = log2(e)/sqrt(d) and the scales' inverse,
+//   z_i = sum_v n_v 2^(x_iv),
+// R_i an integer within 8 of the query's largest logit over the nonempty
+// blocks and B the exponent of the head's largest n_v.  x is one FMA whose
+// result is small where P is not, so its rounding is too (adding log n_v to a
+// logit of 65 and taking the maximum from it later lost 2^-18 twice); R moves
+// by whole powers of two, exactly; and no term pays an addition for n_v or a
+// subtraction of the maximum: the weights enter the first level of the sums.
+// Errors: x by ln 2 times
+//   e_i = isd (et |q_i| + 2^-28 sqrt(D) qmax) cmax + 2^-24 1.01 2.02 isd |q_i| cmax
+//         + 2^-24 0.71 xm,  xm = 2 isd |q_i| cmax log2(e) + 36 >= |x|
+// (cmax = max |c_v|), 2^x by 2^-23 (2 + 1.5 xm) relative: E = 1.01 e_i + that;
+// z by E and at most C/32 + 12 roundings, the weighted sums over the queries
+// and blocks by 12 more:
+//   delta_u = max_i (2.02 E + 2^-24 (C/32 + 30)) + 2^-24 (17 + 2 chunks).
+// A term below 2^-126 before the weight may flush to zero: at most
+// 1.5 2^-126 of P, since z >= 2^(B - 1/2).  Values below float's normal range
+// carry such an absolute error, handled by the selection.  Rows whose
+// selection this bound cannot certify are recomputed in float64.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// Splits the centroids into three bf16 planes and records log2(e) log n_v
-// (-inf for empty blocks; the logits are in base 2), |c_v| rounded up, and
-// per-block maxima of |c_v| and |log n_v|.
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+
+// power of two that brings a largest element mx (> 0, finite) into [2^14, 2^15)
+__device__ __forceinline__ float f16_scale(float mx) {
+  const int e = (int)((__float_as_uint(mx) >> 23) & 255u) - 127;  // mx >= 2^-100: normal
+  return __uint_as_float((uint32_t)(127 + min(14 - e, 120)) << 23);
+}
+// whether a tile or chunk with largest element mx can be scaled
+__device__ __forceinline__ bool f16_scalable(float mx) {
+  return mx >= 7.8886091e-31f && mx <= 3.4028235e38f;  // 2^-100 .. FLT_MAX
+}
+
+// Splits the centroids into two f16 planes (scaled by their 32-centroid tile's
+// power of two, whose inverse goes to tsc) and records the weights n_v (0 for
+// empty blocks and the padding) and per-tile maxima of |c_v| (rounded up;
+// infinite for a tile that cannot be scaled) and n_v.  An empty block takes
+// the row of the head's first nonempty one: with weight 0 it adds nothing, and
+// the largest logit is that of a block that counts.
 template <int D>
 __global__ __launch_bounds__(256) void k_cen_prep(const float* __restrict__ cen,
                                                   const int* __restrict__ k_sizes, int CK,
-                                                  bf16_t* __restrict__ c3, size_t plane,
-                                                  float* __restrict__ lg, int CKpad,
-                                                  float* __restrict__ cn,
+                                                  uint16_t* __restrict__ c2, size_t plane,
+                                                  float* __restrict__ nv, int CKpad,
+                                                  float* __restrict__ tsc,
                                                   float* __restrict__ bmax) {
-  constexpr int CB = 16, TPC = 256 / CB, EPT = D / TPC;
+  constexpr int CB = 32, TPC = 256 / CB, EPT = D / TPC;
   __shared__ float part[CB][TPC];
+  __shared__ float wmax[4];
+  __shared__ int first;  // the head's first nonempty block
   const int h = blockIdx.y, v0 = blockIdx.x * CB, tid = threadIdx.x;
   const int r = tid / TPC, j = tid % TPC, v = v0 + r;
-  float ss = 0.0f;
-  if (v < CK) {
-    const size_t o = ((size_t)h * CK + v) * D + j * EPT;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const float x = cen[o + e];
-      const bf16_t p1 = f2bf(x);
-      const float r1 = x - bf2f(p1);
-      const bf16_t p2 = f2bf(r1);
-      const float r2 = r1 - bf2f(p2);
-      c3[o + e] = p1;
-      c3[o + e + plane] = p2;
-      c3[o + e + 2 * plane] = f2bf(r2);
-      ss = fmaf(x, x, ss);
+  const size_t o = ((size_t)h * CK + min(v, CK - 1)) * D + j * EPT;
+  const int* ks = k_sizes + (size_t)h * CK;
+  if (tid == 0) first = CK;
+  __syncthreads();
+  const bool empty = ks[min(v, CK - 1)] <= 0;
+  if (__any(empty)) {  // (uniform per wavefront; the barrier below is reached by all)
+    for (int q = tid & 63; q < CK; q += 64) {
+      const uint64_t m = __ballot(ks[q] > 0);
+      if (m) {
+        if ((tid & 63) == 0) atomicMin(&first, q + __ffsll((unsigned long long)m) - 1);
+        break;
+      }
     }
   }
+  __syncthreads();
+  const size_t oi = empty && first < CK ? ((size_t)h * CK + first) * D + j * EPT : o;
+  float x[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; e += 4) {
+    const float4 q = *(const float4*)(cen + oi + e);
+    x[e] = q.x;
+    x[e + 1] = q.y;
+    x[e + 2] = q.z;
+    x[e + 3] = q.w;
+  }
+  float mx = 0.0f, ss = 0.0f;
+  bool fin = true;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    mx = fmaxf(mx, fabsf(x[e]));
+    fin &= isfinite(x[e]);
+  }
+  if (!fin) mx = INFINITY;
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w, 64));
+  if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+  const float sc = f16_scalable(mx) ? f16_scale(mx) : 1.0f;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) ss = fmaf(x[e] * sc, x[e] * sc, ss);  // (squares in range)
   part[r][j] = ss;
   __syncthreads();
+  if (v < CK) {
+    uint32_t p1[EPT / 2], p2[EPT / 2];
+#pragma unroll
+    for (int e = 0; e < EPT; e += 2) {
+      p1[e / 2] = p2[e / 2] = 0u;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float y = x[e + k] * sc;
+        const _Float16 a = (_Float16)y, b = (_Float16)(y - (float)a);
+        p1[e / 2] |= (uint32_t)__builtin_bit_cast(uint16_t, a) << (16 * k);
+        p2[e / 2] |= (uint32_t)__builtin_bit_cast(uint16_t, b) << (16 * k);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < EPT / 2; e += 4) {
+      *(uint4*)(c2 + o + 2 * e) = make_uint4(p1[e], p1[e + 1], p1[e + 2], p1[e + 3]);
+      *(uint4*)(c2 + plane + o + 2 * e) = make_uint4(p2[e], p2[e + 1], p2[e + 2], p2[e + 3]);
+    }
+  }
   float fn = 0.0f, fl = 0.0f;
   if (tid < CB) {
     const int vv = v0 + tid;
     if (vv < CK) {
       float s2 = 0.0f;
       for (int q = 0; q < TPC; ++q) s2 += part[tid][q];
-      fn = sqrtf(s2) * 1.0001f;
+      fn = sqrtf(s2) * 1.0001f / sc;
       const int n = k_sizes[(size_t)h * CK + vv];
-      const float l = n > 0 ? (float)log((double)n) : -INFINITY;
-      cn[(size_t)h * CK + vv] = fn;
-      lg[(size_t)h * CKpad + vv] = l * 1.4426950408889634f;  // log2(e) log n, one rounding
-      fl = n > 0 ? fabsf(l) : 0.0f;
+      fl = (float)max(n, 0);
+      nv[(size_t)h * CKpad + vv] = fl;
     }
   }
   if (blockIdx.x == gridDim.x - 1)  // padding blocks: never scored
-    for (int vv = CK + tid; vv < CKpad; vv += 256) lg[(size_t)h * CKpad + vv] = -INFINITY;
+    for (int vv = CK + tid; vv < CKpad; vv += 256) nv[(size_t)h * CKpad + vv] = 0.0f;
   if (tid < 64) {
-    for (int o = 8; o > 0; o >>= 1) {
-      fn = fmaxf(fn, __shfl_xor(fn, o, 64));
-      fl = fmaxf(fl, __shfl_xor(fl, o, 64));
+    for (int w = 16; w > 0; w >>= 1) {
+      fn = fmaxf(fn, __shfl_xor(fn, w, 64));
+      fl = fmaxf(fl, __shfl_xor(fl, w, 64));
     }
     if (tid == 0) {
+      if (mx > 0.0f && !f16_scalable(mx)) fn = INFINITY;
       bmax[((size_t)h * gridDim.x + blockIdx.x) * 2] = fn;
       bmax[((size_t)h * gridDim.x + blockIdx.x) * 2 + 1] = fl;
+      tsc[(size_t)h * gridDim.x + blockIdx.x] = 1.0f / sc;
     }
   }
+}
+
+// A chunk of queries as f16 operands: the lane's bf16 fragments (query c32,
+// dims 16 s + 8 hf ..) scaled by one power of two for the 64 lanes' 32 queries.
+// inv: its inverse; qn: the query's norm rounded up; qmax: the chunk's largest
+// (infinite when the chunk cannot be scaled).
+template <int KS>
+__device__ __forceinline__ void f16_queries(const uint4 (&raw)[KS], f16x8_t (&qf)[KS], float& inv,
+                                            float& qn, float& qmax) {
+  float mx = 0.0f, qsq = 0.0f;
+  bool fin = true;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const uint32_t q[4] = {raw[s].x, raw[s].y, raw[s].z, raw[s].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __uint_as_float(q[e] << 16), hi = __uint_as_float(q[e] & 0xffff0000u);
+      mx = fmaxf(mx, fmaxf(fabsf(lo), fabsf(hi)));
+      fin &= isfinite(lo) && isfinite(hi);
+    }
+  }
+  if (!fin) mx = INFINITY;
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w, 64));
+  const float sc = f16_scalable(mx) ? f16_scale(mx) : 1.0f;
+  inv = 1.0f / sc;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const uint32_t q[4] = {raw[s].x, raw[s].y, raw[s].z, raw[s].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __uint_as_float(q[e] << 16) * sc, hi = __uint_as_float(q[e] & 0xffff0000u) * sc;
+      qf[s][2 * e] = (_Float16)lo;
+      qf[s][2 * e + 1] = (_Float16)hi;
+      qsq = fmaf(lo, lo, fmaf(hi, hi, qsq));  // (of the scaled values: squares in range)
+    }
+  }
+  qsq += __shfl_xor(qsq, 32, 64);
+  qn = sqrtf(qsq) * 1.0001f * inv;
+  qmax = qn;
+#pragma unroll
+  for (int w = 16; w > 0; w >>= 1) qmax = fmaxf(qmax, __shfl_xor(qmax, w, 64));
+  if (mx > 0.0f && !f16_scalable(mx)) qmax = INFINITY;
+}
+
+// The relative error bound of one query's probabilities (see above).
+template <int D>
+__device__ __forceinline__ float pama_bound(float isd, float qn, float qmax, float cmax, int CK) {
+  constexpr float U24 = 5.9604645e-08f, DEL = 1.1920929e-07f, L2E = 1.4426950408889634f;
+  constexpr float FL = 3.7252903e-09f * (D == 128 ? 11.3138f : 8.0001f);  // 2^-28 sqrt(D)
+  constexpr float ET = 4.0f * U24 * 1.01f + (32.0f * DEL + (D / 32 - 1) * U24) * 1.01f +
+                       0.00048828125f * 1.01f * (D + 32) * DEL + FL * 1.01f;
+  const float xm = 2.01f * isd * qn * cmax * L2E + 36.0f;
+  const float ei = isd * ((ET + 2.1f * U24) * qn + FL * 1.01f * qmax) * cmax + 0.71f * U24 * xm;
+  const float b = 2.02f * (1.01f * ei + DEL * (2.0f + 1.5f * xm)) + U24 * ((float)(CK / 32) + 31.0f);
+  return b == b ? b : INFINITY;  // (0 x inf: nothing is known)
+}
+
+// B and the two scalings of the sums (see above): 2^B >= n_max
+__device__ __forceinline__ float pama_bias(float nmax) {
+  return (float)((int)((__float_as_uint(fmaxf(nmax, 1.0f)) >> 23) & 255u) - 126);
+}
+
+// scores of one tile against one query (pass 1): x[q] = hi[q] f + nR, the
+// reference moved when a score exceeds it by more than 2^8; then the weighted
+// sum of 2^x, its first level with the weights nw
+__device__ __forceinline__ void pama_tile_sum(const f32x16_t& hi, float f, float Bf, const float (&nw)[16],
+                                              float& R, float& z) {
+  float x[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = fmaf(hi[q], f, Bf - R);
+  float tmax = fmaxf(x[0], x[1]);
+#pragma unroll
+  for (int q = 2; q < 16; ++q) tmax = fmaxf(tmax, x[q]);
+  if (__any(tmax > Bf + 8.0f)) {
+    float mh = fmaxf(hi[0], hi[1]);
+#pragma unroll
+    for (int q = 2; q < 16; ++q) mh = fmaxf(mh, hi[q]);
+    const float Rn = tmax > Bf + 8.0f ? rintf(mh * f) : R;
+    z *= __builtin_amdgcn_exp2f(R - Rn);  // (z = 0 before the first tile: R = -inf)
+    R = Rn;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) x[q] = fmaf(hi[q], f, Bf - R);
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = __builtin_amdgcn_exp2f(x[q]);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) x[q] = fmaf(x[q + 8], nw[q + 8], x[q] * nw[q]);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < o; ++q) x[q] += x[q + o];
+  z += x[0];
 }
 
 // One wave-wide LDS DMA (lane l's 16 bytes at g land at LDS byte lds + 16 l),
@@ -1079,7 +1251,7 @@ __global__ __launch_bounds__(1024) void k_pama_plan(const int* __restrict__ q_of
 // Fast retrieval.  A workgroup takes four items of one head (one round of 64
 // queries of a query block per wavefront, from the plan) and streams the
 // head's key-block centroids through an NS-slot LDS ring (32 rows of the
-// three bf16 parts per tile, LDS DMA, rows swizzled in 16-byte chunks),
+// two f16 parts per tile, LDS DMA, rows swizzled in 16-byte chunks),
 // twice: pass 1 builds each query's normaliser, pass 2 sums the
 // probabilities over the round's queries.  Every tile serves 256 queries.
 //
@@ -1090,34 +1262,34 @@ __global__ __launch_bounds__(1024) void k_pama_plan(const int* __restrict__ q_of
 // centroid, queries 8b + 4(l/32) + r); each pass then reduces within lanes.
 // Accuracy as in the float error bound below: the c1 part is accumulated in
 // 32-dimension segments (two MFMAs from zero) added in float, the two small
-// parts in one chain over all dimensions.
+// part in one chain over all dimensions.
 //
-// Scores are kept in log2 units, s' = (q.c / sqrt(d) + log n_v) log2 e.
-// Pass 1 keeps per query a reference maximum m and z = sum 2^(s' - m) (one
-// rescale per tile, tile terms added in a tree); pass 2 uses
-// c_q = m + log2 z, so p = 2^(s' - c_q).
+// Scores are kept in log2 units; pass 1 keeps per query the reference R and
+// z (tile terms added in a tree), pass 2 recomputes 2^x and weights it with
+// 1 / z per query and n_v per centroid (both sides of the sums scaled by
+// 2^40 and back, against underflow of a small term before its weight).
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__ Qp,
                                                       const int* __restrict__ q_offsets,
                                                       const int4* __restrict__ items,
                                                       const int* __restrict__ nitem, int icap,
                                                       float* __restrict__ part, int pcap,
-                                                      const bf16_t* __restrict__ c3, size_t plane,
-                                                      const float* __restrict__ lg, int CKpad,
-                                                      const float* __restrict__ bmax, int nbm, int H,
+                                                      const uint16_t* __restrict__ c2, size_t plane,
+                                                      const float* __restrict__ nv, int CKpad,
+                                                      const float* __restrict__ tsc,
+                                                      const float* __restrict__ bmax, int H,
                                                       int N, int CQ, int CK, float* __restrict__ W32,
                                                       float* __restrict__ delta) {
   constexpr int CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
-  constexpr int NI = 3 * CT / (4 * RPI);  // DMAs per wavefront and tile
-  static_assert(NI * 4 * RPI == 3 * CT && KS % 2 == 0, "tile shape");
+  constexpr int NI = 2 * CT / (4 * RPI);  // DMAs per wavefront and tile
+  static_assert(NI * 4 * RPI == 2 * CT && KS % 2 == 0, "tile shape");
   constexpr int NS = 3;
-  constexpr float U24 = 5.9604645e-08f, DEL = 1.1920929e-07f, L2E = 1.4426950408889634f;
-  constexpr float ET = U24 * 1.01f + (32.0f * DEL + (KS / 2 - 1) * U24) * 1.01f +
-                       0.00390625f * 1.01f * (2 * D) * DEL + U24 * 1.01f;
-  __shared__ __attribute__((aligned(16))) bf16_t Ct[NS][3 * CT * D];  // [slot][part][row][D]
+  constexpr float L2E = 1.4426950408889634f;
+  __shared__ __attribute__((aligned(16))) uint16_t Ct[NS][2 * CT * D];  // [slot][part][row][D]
   __shared__ __attribute__((aligned(16))) float Lt[NS][CT];
-  __shared__ __attribute__((aligned(16))) float cbuf[4][64];  // c_q of each wavefront's chunk
+  __shared__ __attribute__((aligned(16))) float cbuf[2][4][64];  // B - R_q and 2^40 / z_q per wavefront
   __shared__ float mx_s[2];
+  __shared__ float ts_s[MAXC / CT];  // inverse scale of each centroid tile
   // workgroups of a head on one XCD (its L2 holds the head's centroids)
   const int G = (icap + 7) / 8, nwgs = G * H, per = (nwgs + 7) >> 3;
   const int wgi = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -1146,11 +1318,13 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
       orow[g] = part + ((size_t)h * pcap + itm.z) * CK;
     else orow[g] = nullptr;
   }
+  const int nt = (CK + CT - 1) / CT;
   if (tid < 64) {
     float a = 0.0f, c = 0.0f;
-    for (int i = tid; i < nbm; i += 64) {
-      a = fmaxf(a, bmax[((size_t)h * nbm + i) * 2]);
-      c = fmaxf(c, bmax[((size_t)h * nbm + i) * 2 + 1]);
+    for (int i = tid; i < nt; i += 64) {
+      a = fmaxf(a, bmax[((size_t)h * nt + i) * 2]);
+      c = fmaxf(c, bmax[((size_t)h * nt + i) * 2 + 1]);
+      ts_s[i] = tsc[(size_t)h * nt + i];
     }
     for (int o = 32; o > 0; o >>= 1) {
       a = fmaxf(a, __shfl_xor(a, o, 64));
@@ -1162,12 +1336,11 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
     }
   }
   __syncthreads();
-  const float cmax = mx_s[0], lgmax = mx_s[1];
+  const float cmax = mx_s[0], Bf = pama_bias(mx_s[1]);
   const float isd = 1.0f / sqrtf((float)D), isdL = isd * L2E;
-  const bf16_t* P1 = c3 + (size_t)h * CK * D;
-  const float* lgh = lg + (size_t)h * CKpad;
+  const uint16_t* P1 = c2 + (size_t)h * CK * D;
+  const float* nvh = nv + (size_t)h * CKpad;
   const int pch = l % CPR;
-  const int nt = (CK + CT - 1) / CT;
   auto issue = [&](int tile, int slot) {
     const int c0 = tile * CT;
 #pragma unroll
@@ -1175,10 +1348,10 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
       const int row = (w * NI + i) * RPI + l / CPR;
       const int part = row / CT, r = row % CT;
       const int v = min(c0 + r, CK - 1);
-      const bf16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ pm_swz<D>(r));
+      const uint16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ pm_swz<D>(r));
       pm_dma16(src, pm_lds_addr(&Ct[slot][0] + (w * NI + i) * 512));
     }
-    if (w == 0 && l < CT / 4) pm_dma16(lgh + c0 + 4 * l, pm_lds_addr(&Lt[slot][0]));
+    if (w == 0 && l < CT / 4) pm_dma16(nvh + c0 + 4 * l, pm_lds_addr(&Lt[slot][0]));
   };
   // the centroid fragment of this lane: row c32 of a tile, dims 16 s + 8 hf ..
   const int crow = c32 * D, cswz = pm_swz<D>(c32);
@@ -1202,23 +1375,22 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
     return it % NS;
   };
   // products of both query groups with one tile: S^T (pass 1: lane = query,
-  // 16 centroids) or S (pass 2: lane = centroid, 16 queries); c2 + c3 in one
+  // 16 centroids) or S (pass 2: lane = centroid, 16 queries); c2 in one
   // chain over all dimensions, c1 in 32-dimension segments (two MFMAs from
-  // zero, the last from the finished c2 + c3 chain) added in float
-  auto products = [&](const bf16x8_t (*q2)[KS], const bf16_t* B1, bool qa_left, f32x16_t* hi) {
-    const bf16_t* B2 = B1 + CT * D;
-    const bf16_t* B3 = B2 + CT * D;
+  // zero, the last from the finished c2 chain) added in float
+  auto products = [&](const f16x8_t (*q2)[KS], const uint16_t* B1, bool qa_left, f32x16_t* hi) {
+    const uint16_t* B2 = B1 + CT * D;
     constexpr int LS = KS / 2 - 1;  // the last segment
-    auto mm = [&](const bf16x8_t& b, const bf16x8_t& q, const f32x16_t& c) {
-      return qa_left ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, b, c, 0, 0, 0)
-                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, q, c, 0, 0, 0);
+    auto mm = [&](const f16x8_t& b, const f16x8_t& q, const f32x16_t& c) {
+      return qa_left ? __builtin_amdgcn_mfma_f32_32x32x16_f16(q, b, c, 0, 0, 0)
+                     : __builtin_amdgcn_mfma_f32_32x32x16_f16(b, q, c, 0, 0, 0);
     };
     f32x16_t rest[2];
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
       for (int q = 0; q < 16; ++q) rest[g][q] = 0.0f;
-    bf16x8_t bl[2];  // c1 fragments of the last segment
+    f16x8_t bl[2];  // c1 fragments of the last segment
 #pragma unroll
     for (int sp = 0; sp < KS / 2; ++sp) {
       f32x16_t seg[2];
@@ -1229,15 +1401,13 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
 #pragma unroll
       for (int s = 2 * sp; s < 2 * sp + 2; ++s) {
         const int co = crow + 8 * ((2 * s + hf) ^ cswz);
-        const bf16x8_t b1 = *(const bf16x8_t*)(B1 + co);
-        const bf16x8_t b2 = *(const bf16x8_t*)(B2 + co);
-        const bf16x8_t b3 = *(const bf16x8_t*)(B3 + co);
+        const f16x8_t b1 = *(const f16x8_t*)(B1 + co);
+        const f16x8_t b2 = *(const f16x8_t*)(B2 + co);
         if (sp == LS) bl[s - 2 * sp] = b1;
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
           if (sp < LS) seg[g] = mm(b1, q2[g][s], seg[g]);
           rest[g] = mm(b2, q2[g][s], rest[g]);
-          rest[g] = mm(b3, q2[g][s], rest[g]);
         }
       }
       if (sp < LS) {
@@ -1253,46 +1423,32 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
       hi[g] = LS == 0 ? seg : hi[g] + seg;
     }
   };
-  bf16x8_t qf[2][KS];
+  f16x8_t qf[2][KS];
+  float fq[2];  // log2(e) / sqrt(d) and the chunk's inverse scale
   {
     bool ong[2];
 #pragma unroll
     for (int g = 0; g < 2; ++g) ong[g] = orow[g] != nullptr;
     const bool on = ong[0] || ong[1];
-    float m[2], z[2];
+    float R[2], z[2];
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
       const int qa = q0[g] + 32 * rc[g] + c32;
       const bool qv = ong[g] && qa < q1[g];
-      float qsq = 0.0f;
+      uint4 raw[KS];
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-        if (qv) raw = *(const uint4*)(Qp + ((size_t)h * N + qa) * D + 16 * s + 8 * hf);
-        qf[g][s] = __builtin_bit_cast(bf16x8_t, raw);
-        asm volatile("" ::"v"(qf[g][s]));  // loads complete here, not inside the ring waits
-        const uint32_t q[4] = {raw.x, raw.y, raw.z, raw.w};
+        raw[s] = make_uint4(0u, 0u, 0u, 0u);
+        if (qv) raw[s] = *(const uint4*)(Qp + ((size_t)h * N + qa) * D + 16 * s + 8 * hf);
+      }
+      float inv, qn, qmax;
+      f16_queries<KS>(raw, qf[g], inv, qn, qmax);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = __uint_as_float(q[e] << 16), hi = __uint_as_float(q[e] & 0xffff0000u);
-          qsq = fmaf(lo, lo, fmaf(hi, hi, qsq));
-        }
-      }
-      qsq += __shfl_xor(qsq, 32, 64);
-      if (qv) {
-        // row error bound of this query (|q| rounded up)
-        const float qn = sqrtf(qsq) * 1.0001f;
-        const float ei = isd * (ET + 1.01f * U24) * qn * cmax +
-                         1.01f * U24 * (3.0f * lgmax + 2.02f * isd * qn * cmax);
-        const float argmax = 2.0f * (isd * qn * cmax + lgmax) * L2E;
-        const float nadd = fmaxf((float)(CK / 16 + 1), (float)(CK / 32 + 5));
-        const float dZ = DEL * (10.0f + 3.0f * log2f((float)CK + 1.0f) + 2.0f * nadd +
-                                3.0f * argmax) +
-                         2.0f * U24 * (nadd + 24.0f);
-        dmax[g] = fmaxf(dmax[g], 2.02f * ei + dZ +
-                                     DEL * (3.0f + 2.5f * argmax + 2.0f * log2f((float)CK + 1.0f)));
-      }
-      m[g] = -INFINITY;
+      for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qf[g][s]));  // (not inside the ring waits)
+      fq[g] = isdL * inv;
+      // row error bound of this query
+      if (qv) dmax[g] = fmaxf(dmax[g], pama_bound<D>(isd, qn, qmax, cmax, CK));
+      R[g] = -INFINITY;
       z[g] = 0.0f;
     }
     // pass 1: lane holds query c32 of each group, centroids c0 + 8b + 4hf + r
@@ -1301,67 +1457,60 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
       if (!on) continue;
       f32x16_t hi[2];
       products(qf, &Ct[slot][0], false, hi);
+      const float ft = ts_s[tile];
+      float nw[16];
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        float sv[16];
-#pragma unroll
-        for (int bq = 0; bq < 4; ++bq) {
-          const float4 l4 = *(const float4*)(&Lt[slot][8 * bq + 4 * hf]);
-          const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            sv[4 * bq + r] = fmaf(hi[g][4 * bq + r], isdL, lv[r]);
-        }
-        float tmax = fmaxf(sv[0], sv[1]);
-#pragma unroll
-        for (int q = 2; q < 16; ++q) tmax = fmaxf(tmax, sv[q]);
-        const float mn = fmaxf(m[g], tmax);
-        if (mn != -INFINITY) {
-#pragma unroll
-          for (int q = 0; q < 16; ++q) sv[q] = __builtin_amdgcn_exp2f(sv[q] - mn);
-#pragma unroll
-          for (int o = 8; o > 0; o >>= 1)
-#pragma unroll
-            for (int q = 0; q < o; ++q) sv[q] += sv[q + o];
-          z[g] = (m[g] == mn ? z[g] : z[g] * __builtin_amdgcn_exp2f(m[g] - mn)) + sv[0];
-          m[g] = mn;
-        }
+      for (int bq = 0; bq < 4; ++bq) {
+        const float4 n4 = *(const float4*)(&Lt[slot][8 * bq + 4 * hf]);
+        nw[4 * bq] = n4.x;
+        nw[4 * bq + 1] = n4.y;
+        nw[4 * bq + 2] = n4.z;
+        nw[4 * bq + 3] = n4.w;
       }
+#pragma unroll
+      for (int g = 0; g < 2; ++g) pama_tile_sum(hi[g], fq[g] * ft, Bf, nw, R[g], z[g]);
     }
-    // c_q = m + log2 z per query (halves merged); invalid queries +inf
+    // the halves of a query merged; invalid queries have weight 0
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      const float om = __shfl_xor(m[g], 32, 64), oz = __shfl_xor(z[g], 32, 64);
-      const float M = fmaxf(m[g], om);
-      float zz = 0.0f;
-      if (M != -INFINITY)
-        zz = z[g] * __builtin_amdgcn_exp2f(m[g] - M) + oz * __builtin_amdgcn_exp2f(om - M);
+      const float oR = __shfl_xor(R[g], 32, 64), oz = __shfl_xor(z[g], 32, 64);
+      const float Rm = fmaxf(R[g], oR);
+      const float zz = z[g] * __builtin_amdgcn_exp2f(R[g] - Rm) + oz * __builtin_amdgcn_exp2f(oR - Rm);
       const int qa = q0[g] + 32 * rc[g] + c32;
-      const float c = (ong[g] && qa < q1[g] && zz > 0.0f) ? M + __builtin_amdgcn_logf(zz) : INFINITY;
-      if (hf == 0) cbuf[w][32 * g + c32] = c;
+      const bool qv = ong[g] && qa < q1[g] && zz > 0.0f;
+      if (hf == 0) {
+        cbuf[0][w][32 * g + c32] = qv ? Bf - Rm : 0.0f;
+        cbuf[1][w][32 * g + c32] = qv ? 1.0995116e12f / zz : 0.0f;  // 2^40
+      }
     }
     // pass 2: lane holds centroid c0 + c32, queries 8b + 4hf + r of each group
     for (int tile = 0; tile < nt; ++tile, ++it) {
       const int slot = ring_step();
       if (!on) continue;
-      const float lgj = Lt[slot][c32];
+      const float wv = Lt[slot][c32] * 9.0949470e-13f;  // 2^-40
       float ws[2];
       f32x16_t hi[2];
       products(qf, &Ct[slot][0], true, hi);
+      const float ft = ts_s[tile];
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        float e[16];
+        const float f = fq[g] * ft;
+        float e[16], gq[16];
 #pragma unroll
         for (int bq = 0; bq < 4; ++bq) {
-          const float4 c4 = *(const float4*)(&cbuf[w][32 * g + 8 * bq + 4 * hf]);
-          const float cv[4] = {c4.x, c4.y, c4.z, c4.w};
+          const float4 r4 = *(const float4*)(&cbuf[0][w][32 * g + 8 * bq + 4 * hf]);
+          const float4 g4 = *(const float4*)(&cbuf[1][w][32 * g + 8 * bq + 4 * hf]);
+          const float rv[4] = {r4.x, r4.y, r4.z, r4.w}, gv[4] = {g4.x, g4.y, g4.z, g4.w};
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            e[4 * bq + r] = __builtin_amdgcn_exp2f(
-                fmaf(hi[g][4 * bq + r], isdL, lgj) - cv[r]);
+          for (int r = 0; r < 4; ++r) {
+            e[4 * bq + r] = __builtin_amdgcn_exp2f(fmaf(hi[g][4 * bq + r], f, rv[r]));
+            gq[4 * bq + r] = gv[r];
+          }
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1)
+        for (int q = 0; q < 8; ++q) e[q] = fmaf(e[q + 8], gq[q + 8], e[q] * gq[q]);
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1)
 #pragma unroll
           for (int q = 0; q < o; ++q) e[q] += e[q + o];
         ws[g] = e[0] + __shfl_xor(e[0], 32, 64);
@@ -1369,7 +1518,7 @@ __global__ __launch_bounds__(256, 2) void k_pama_fast(const bf16_t* __restrict__
       // lanes of half g write chunk g's sums
       const int v = tile * CT + c32;
       float* dst = hf ? orow[1] : orow[0];
-      if (dst && v < CK) dst[v] = (hf ? ws[1] : ws[0]) / (float)(hf ? nu[1] : nu[0]);
+      if (dst && v < CK) dst[v] = (hf ? ws[1] : ws[0]) * wv / (float)(hf ? nu[1] : nu[0]);
     }
   }
 #pragma unroll
@@ -1391,34 +1540,33 @@ constexpr int FULLK_NT = 8;
 // sweep over the centroids instead of two.  A wavefront takes one 32-query
 // chunk (items as in the fast retrieval, four per workgroup) and computes S^T
 // (lane: one query, 16 of each tile's 32 centroids) exactly as the fast
-// path's first pass, keeping every final logit of its query row in
-// registers; the online normaliser (m, z) is the fast path's, so the row
-// bound delta_u is the same.  The probabilities then come from the kept
-// logits, and each centroid's sum over the chunk's 32 queries is a fixed
-// five-level butterfly over the lanes (the fast path's pass 2 sums the same
-// values in a five-level tree), written to the chunk's row as before.
+// path's first pass, keeping every score of its query row in registers; the
+// exponentials, taken once from the final reference R, the weighted sum z and
+// the row bound delta_u are the fast path's.  Each centroid's sum over the
+// chunk's 32 queries is a fixed five-level butterfly over the lanes (the fast
+// path's pass 2 sums the same values in a five-level tree), written to the
+// chunk's row as before.
 template <int D, int FK_NT>
 __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict__ Qp,
                                                        const int* __restrict__ q_offsets,
                                                        const int4* __restrict__ items,
                                                        const int* __restrict__ nitem, int icap,
                                                        float* __restrict__ part, int pcap,
-                                                       const bf16_t* __restrict__ c3,
-                                                       size_t plane, const float* __restrict__ lg,
-                                                       int CKpad, const float* __restrict__ bmax,
-                                                       int nbm, int H, int N, int CQ, int CK,
+                                                       const uint16_t* __restrict__ c2,
+                                                       size_t plane, const float* __restrict__ nv,
+                                                       int CKpad, const float* __restrict__ tsc,
+                                                       const float* __restrict__ bmax, int H, int N, int CQ, int CK,
                                                        float* __restrict__ W32,
                                                        float* __restrict__ delta) {
   constexpr int CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
-  constexpr int NI = 3 * CT / (4 * RPI);  // DMAs per wavefront and tile
-  static_assert(NI * 4 * RPI == 3 * CT && KS % 2 == 0, "tile shape");
+  constexpr int NI = 2 * CT / (4 * RPI);  // DMAs per wavefront and tile
+  static_assert(NI * 4 * RPI == 2 * CT && KS % 2 == 0, "tile shape");
   constexpr int NS = 3;
-  constexpr float U24 = 5.9604645e-08f, DEL = 1.1920929e-07f, L2E = 1.4426950408889634f;
-  constexpr float ET = U24 * 1.01f + (32.0f * DEL + (KS / 2 - 1) * U24) * 1.01f +
-                       0.00390625f * 1.01f * (2 * D) * DEL + U24 * 1.01f;
-  __shared__ __attribute__((aligned(16))) bf16_t Ct[NS][3 * CT * D];  // [slot][part][row][D]
-  __shared__ __attribute__((aligned(16))) float Lt[NS][CT];
+  constexpr float L2E = 1.4426950408889634f;
+  __shared__ __attribute__((aligned(16))) uint16_t Ct[NS][2 * CT * D];  // [slot][part][row][D]
   __shared__ float mx_s[2];
+  __shared__ __attribute__((aligned(16))) float nv_s[32 * FK_NT];
+  __shared__ float ts_s[FK_NT];  // inverse scale of each centroid tile
   // workgroups of a head on one XCD (its L2 holds the head's centroids)
   const int G = (icap + 3) / 4, nwgs = G * H, per = (nwgs + 7) >> 3;
   const int wgi = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -1442,11 +1590,13 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
     if (rc == 0) orow = W32 + ((size_t)h * CQ + u) * CK;
     else if (itm.z >= 0 && itm.z < pcap) orow = part + ((size_t)h * pcap + itm.z) * CK;
   }
+  const int nt = (CK + CT - 1) / CT;
   if (tid < 64) {
     float a = 0.0f, c = 0.0f;
-    for (int i = tid; i < nbm; i += 64) {
-      a = fmaxf(a, bmax[((size_t)h * nbm + i) * 2]);
-      c = fmaxf(c, bmax[((size_t)h * nbm + i) * 2 + 1]);
+    for (int i = tid; i < nt; i += 64) {
+      a = fmaxf(a, bmax[((size_t)h * nt + i) * 2]);
+      c = fmaxf(c, bmax[((size_t)h * nt + i) * 2 + 1]);
+      ts_s[i] = tsc[(size_t)h * nt + i];
     }
     for (int o = 32; o > 0; o >>= 1) {
       a = fmaxf(a, __shfl_xor(a, o, 64));
@@ -1457,13 +1607,13 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
       mx_s[1] = c;
     }
   }
+  // (padded to a multiple of 64; 0 past the last block)
+  for (int v = tid; v < 32 * FK_NT; v += 256) nv_s[v] = v < CKpad ? nv[(size_t)h * CKpad + v] : 0.0f;
   __syncthreads();
-  const float cmax = mx_s[0], lgmax = mx_s[1];
+  const float cmax = mx_s[0], Bf = pama_bias(mx_s[1]);
   const float isd = 1.0f / sqrtf((float)D), isdL = isd * L2E;
-  const bf16_t* P1 = c3 + (size_t)h * CK * D;
-  const float* lgh = lg + (size_t)h * CKpad;
+  const uint16_t* P1 = c2 + (size_t)h * CK * D;
   const int pch = l % CPR;
-  const int nt = (CK + CT - 1) / CT;  // <= FK_NT (the launcher checks)
   auto issue = [&](int tile, int slot) {
     const int c0 = tile * CT;
 #pragma unroll
@@ -1471,60 +1621,44 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
       const int row = (w * NI + i) * RPI + l / CPR;
       const int part = row / CT, r = row % CT;
       const int v = min(c0 + r, CK - 1);
-      const bf16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ pm_swz<D>(r));
+      const uint16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ pm_swz<D>(r));
       pm_dma16(src, pm_lds_addr(&Ct[slot][0] + (w * NI + i) * 512));
     }
-    if (w == 0 && l < CT / 4) pm_dma16(lgh + c0 + 4 * l, pm_lds_addr(&Lt[slot][0]));
   };
   const int crow = c32 * D, cswz = pm_swz<D>(c32);
   const bool on = orow != nullptr;
   // the query fragment and the row bound of this lane's query
   const int qa = q0 + 32 * rc + c32;
   const bool qv = on && qa < q1;
-  bf16x8_t qf[KS];
-  float dmax = 0.0f;
+  f16x8_t qf[KS];
+  float dmax = 0.0f, fq;
   {
-    float qsq = 0.0f;
+    uint4 raw[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-      if (qv) raw = *(const uint4*)(Qp + ((size_t)h * N + qa) * D + 16 * s + 8 * hf);
-      qf[s] = __builtin_bit_cast(bf16x8_t, raw);
-      asm volatile("" ::"v"(qf[s]));  // loads complete here, not inside the ring waits
-      const uint32_t q[4] = {raw.x, raw.y, raw.z, raw.w};
+      raw[s] = make_uint4(0u, 0u, 0u, 0u);
+      if (qv) raw[s] = *(const uint4*)(Qp + ((size_t)h * N + qa) * D + 16 * s + 8 * hf);
+    }
+    float inv, qn, qmax;
+    f16_queries<KS>(raw, qf, inv, qn, qmax);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float lo = __uint_as_float(q[e] << 16), hi = __uint_as_float(q[e] & 0xffff0000u);
-        qsq = fmaf(lo, lo, fmaf(hi, hi, qsq));
-      }
-    }
-    qsq += __shfl_xor(qsq, 32, 64);
-    if (qv) {
-      // the row error bound of this query, as in the fast path
-      const float qn = sqrtf(qsq) * 1.0001f;
-      const float ei = isd * (ET + 1.01f * U24) * qn * cmax +
-                       1.01f * U24 * (3.0f * lgmax + 2.02f * isd * qn * cmax);
-      const float argmax = 2.0f * (isd * qn * cmax + lgmax) * L2E;
-      const float nadd = fmaxf((float)(CK / 16 + 1), (float)(CK / 32 + 5));
-      const float dZ = DEL * (10.0f + 3.0f * log2f((float)CK + 1.0f) + 2.0f * nadd +
-                              3.0f * argmax) +
-                       2.0f * U24 * (nadd + 24.0f);
-      dmax = 2.02f * ei + dZ + DEL * (3.0f + 2.5f * argmax + 2.0f * log2f((float)CK + 1.0f));
-    }
+    for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qf[s]));  // (not inside the ring waits)
+    fq = isdL * inv;
+    // the row error bound of this query, as in the fast path
+    if (qv) dmax = pama_bound<D>(isd, qn, qmax, cmax, CK);
   }
 #pragma unroll
   for (int p = 0; p < NS - 1; ++p)
     if (p < nt) issue(p, p);
   // the sweep: S^T of each tile (lane: query c32, centroids 8b + 4hf + r),
-  // kept in registers, and the online normaliser
+  // kept in registers, and the largest logit
   float L[FK_NT][16];
-  float m = -INFINITY, z = 0.0f;
+  float m = -INFINITY;
 #pragma unroll
   for (int tile = 0; tile < FK_NT; ++tile) {
     if (tile < nt) {
       if (tile + 1 < nt) {
-        if (w == 0) pm_wait_vmcnt<NI + 1>();
-        else pm_wait_vmcnt<NI>();
+        pm_wait_vmcnt<NI>();
       } else {
         pm_wait_vmcnt<0>();
       }
@@ -1532,16 +1666,16 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
       if (tile + NS - 1 < nt) issue(tile + NS - 1, (tile + NS - 1) % NS);
       const int slot = tile % NS;
       if (!on) continue;  // no chunk: the ring steps only
-      const bf16_t* B1 = &Ct[slot][0];
-      const bf16_t* B2 = B1 + CT * D;
-      const bf16_t* B3 = B2 + CT * D;
-      // c2 + c3 in one chain, c1 in 32-dimension segments (the last one
-      // from the finished c2 + c3 chain) added in float, as the fast path
+      const uint16_t* B1 = &Ct[slot][0];
+      const uint16_t* B2 = B1 + CT * D;
+      const float f = fq * ts_s[tile];
+      // c2 in one chain, c1 in 32-dimension segments (the last one
+      // from the finished c2 chain) added in float, as the fast path
       constexpr int LS = KS / 2 - 1;
       f32x16_t hi, rest;
 #pragma unroll
       for (int q = 0; q < 16; ++q) rest[q] = 0.0f;
-      bf16x8_t bl[2];
+      f16x8_t bl[2];
 #pragma unroll
       for (int sp = 0; sp < KS / 2; ++sp) {
         f32x16_t seg;
@@ -1550,13 +1684,11 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
 #pragma unroll
         for (int s = 2 * sp; s < 2 * sp + 2; ++s) {
           const int co = crow + 8 * ((2 * s + hf) ^ cswz);
-          const bf16x8_t b1 = *(const bf16x8_t*)(B1 + co);
-          const bf16x8_t b2 = *(const bf16x8_t*)(B2 + co);
-          const bf16x8_t b3 = *(const bf16x8_t*)(B3 + co);
+          const f16x8_t b1 = *(const f16x8_t*)(B1 + co);
+          const f16x8_t b2 = *(const f16x8_t*)(B2 + co);
           if (sp == LS) bl[s - 2 * sp] = b1;
-          else seg = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, qf[s], seg, 0, 0, 0);
-          rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b2, qf[s], rest, 0, 0, 0);
-          rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b3, qf[s], rest, 0, 0, 0);
+          else seg = __builtin_amdgcn_mfma_f32_32x32x16_f16(b1, qf[s], seg, 0, 0, 0);
+          rest = __builtin_amdgcn_mfma_f32_32x32x16_f16(b2, qf[s], rest, 0, 0, 0);
         }
         if (sp < LS) hi = sp == 0 ? seg : hi + seg;
       }
@@ -1564,45 +1696,47 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
         f32x16_t seg = rest;
 #pragma unroll
         for (int s = 2 * LS; s < 2 * LS + 2; ++s)
-          seg = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl[s - 2 * LS], qf[s], seg, 0, 0, 0);
+          seg = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl[s - 2 * LS], qf[s], seg, 0, 0, 0);
         hi = LS == 0 ? seg : hi + seg;
       }
+      float tmax = fmaxf(hi[0], hi[1]);
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq) {
-        const float4 l4 = *(const float4*)(&Lt[slot][8 * bq + 4 * hf]);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+      for (int q = 2; q < 16; ++q) tmax = fmaxf(tmax, hi[q]);
+      m = fmaxf(m, tmax * f);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          L[tile][4 * bq + r] = fmaf(hi[4 * bq + r], isdL, lv[r]);
-      }
-      {
-        float tmax = fmaxf(L[tile][0], L[tile][1]);
-#pragma unroll
-        for (int q = 2; q < 16; ++q) tmax = fmaxf(tmax, L[tile][q]);
-        const float mn = fmaxf(m, tmax);
-        if (mn != -INFINITY) {
-          float sv[16];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) sv[q] = __builtin_amdgcn_exp2f(L[tile][q] - mn);
-#pragma unroll
-          for (int o = 8; o > 0; o >>= 1)
-#pragma unroll
-            for (int q = 0; q < o; ++q) sv[q] += sv[q + o];
-          z = (m == mn ? z : z * __builtin_amdgcn_exp2f(m - mn)) + sv[0];
-          m = mn;
-        }
-      }
+      for (int q = 0; q < 16; ++q) L[tile][q] = hi[q];
     }
   }
-  // c_q = m + log2 z per query (the two halves of a query merged); invalid
-  // queries +inf, so their probabilities are zero
-  float cq;
-  {
-    const float om = __shfl_xor(m, 32, 64), oz = __shfl_xor(z, 32, 64);
-    const float M = fmaxf(m, om);
-    float zz = 0.0f;
-    if (M != -INFINITY) zz = z * __builtin_amdgcn_exp2f(m - M) + oz * __builtin_amdgcn_exp2f(om - M);
-    cq = (qv && zz > 0.0f) ? M + __builtin_amdgcn_logf(zz) : INFINITY;
+  // 2^x of every kept score (one exponential each) and their weighted sum;
+  // invalid queries have weight 0
+  float gq = 0.0f;
+  if (on) {
+    const float R = rintf(fmaxf(m, __shfl_xor(m, 32, 64))), nR = Bf - R;
+    float z = 0.0f;
+#pragma unroll
+    for (int tile = 0; tile < FK_NT; ++tile) {
+      if (tile < nt) {
+        const float f = fq * ts_s[tile];
+        float y[16];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const float4 n4 = *(const float4*)&nv_s[32 * tile + 8 * b + 4 * hf];
+          const float nw[4] = {n4.x, n4.y, n4.z, n4.w};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            L[tile][4 * b + r] = __builtin_amdgcn_exp2f(fmaf(L[tile][4 * b + r], f, nR));
+            y[4 * b + r] = L[tile][4 * b + r] * nw[r];
+          }
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+          for (int q = 0; q < o; ++q) y[q] += y[q + o];
+        z += y[0];
+      }
+    }
+    z += __shfl_xor(z, 32, 64);
+    gq = qv && z > 0.0f ? 1.0995116e12f / z : 0.0f;  // 2^40 / z
   }
   // probabilities from the kept logits, summed over the chunk's 32 queries
   // per centroid: each tile's 32 x 32 probabilities go through LDS (this
@@ -1620,7 +1754,7 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
       if (tile < nt) {
         float e[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) e[q] = __builtin_amdgcn_exp2f(L[tile][q] - cq);
+        for (int q = 0; q < 16; ++q) e[q] = L[tile][q] * gq;
         // lane (query c32, hf) holds centroids 8b + 4hf + r
 #pragma unroll
         for (int b = 0; b < 4; ++b)
@@ -1636,7 +1770,7 @@ __global__ __launch_bounds__(256, 2) void k_pama_fullk(const bf16_t* __restrict_
         const float other = __shfl_xor(x[0], 32, 64);
         const float sum = hf ? other + x[0] : x[0] + other;
         const int v = tile * CT + c32;
-        if (hf == 0 && v < CK) orow[v] = sum / fnu;
+        if (hf == 0 && v < CK) orow[v] = sum * (nv_s[v] * 9.0949470e-13f) / fnu;  // 2^-40
       }
     }
     // the row's bound: the largest over its chunks, finished by k_pama_combine
@@ -2121,7 +2255,7 @@ park_status launch_retrieve(const void* Qp, const int* q_offsets, const float* c
     return PARK_OK;
   }
   const size_t plane = (size_t)H * CK * D;
-  const int nbm = (CK + 15) / 16;
+  const int nbm = (CK + 31) / 32;
   float* W32 = W_out ? W_out : rb.W32;
   const int CKpad = pama_ckpad(CK);
   // chunks of 32 queries, eight per workgroup (work list per head)
@@ -2137,33 +2271,33 @@ park_status launch_retrieve(const void* Qp, const int* q_offsets, const float* c
   if (fullk) {
     if (D == 128) {
       PARK_LAUNCH("pama_cen_prep", k_cen_prep<128>, dim3(nbm, H), dim3(256), 0, st, cen, k_sizes,
-                  CK, rb.c3, plane, rb.lg, CKpad, rb.cn, rb.bmax);
+                  CK, rb.c2, plane, rb.nv, CKpad, rb.tsc, rb.bmax);
       PARK_LAUNCH("pama_fullk", (k_pama_fullk<128, FULLK_NT>), dim3(nwg4), dim3(256), 0, st,
                   (const bf16_t*)Qp, q_offsets, (const int4*)rb.qitems, (const int*)rb.nitem,
-                  icap, part, pcap, (const bf16_t*)rb.c3, plane, (const float*)rb.lg, CKpad,
-                  (const float*)rb.bmax, nbm, H, N, CQ, CK, W32, rb.delta);
+                  icap, part, pcap, (const uint16_t*)rb.c2, plane, (const float*)rb.nv, CKpad,
+                  (const float*)rb.tsc, (const float*)rb.bmax, H, N, CQ, CK, W32, rb.delta);
     } else {
       PARK_LAUNCH("pama_cen_prep", k_cen_prep<64>, dim3(nbm, H), dim3(256), 0, st, cen, k_sizes,
-                  CK, rb.c3, plane, rb.lg, CKpad, rb.cn, rb.bmax);
+                  CK, rb.c2, plane, rb.nv, CKpad, rb.tsc, rb.bmax);
       PARK_LAUNCH("pama_fullk", (k_pama_fullk<64, FULLK_NT>), dim3(nwg4), dim3(256), 0, st,
                   (const bf16_t*)Qp, q_offsets, (const int4*)rb.qitems, (const int*)rb.nitem,
-                  icap, part, pcap, (const bf16_t*)rb.c3, plane, (const float*)rb.lg, CKpad,
-                  (const float*)rb.bmax, nbm, H, N, CQ, CK, W32, rb.delta);
+                  icap, part, pcap, (const uint16_t*)rb.c2, plane, (const float*)rb.nv, CKpad,
+                  (const float*)rb.tsc, (const float*)rb.bmax, H, N, CQ, CK, W32, rb.delta);
     }
   } else if (D == 128) {
     PARK_LAUNCH("pama_cen_prep", k_cen_prep<128>, dim3(nbm, H), dim3(256), 0, st, cen, k_sizes, CK,
-                rb.c3, plane, rb.lg, CKpad, rb.cn, rb.bmax);
+                rb.c2, plane, rb.nv, CKpad, rb.tsc, rb.bmax);
     PARK_LAUNCH("pama_fast", k_pama_fast<128>, dim3(nwg), dim3(256), 0, st, (const bf16_t*)Qp,
                 q_offsets, (const int4*)rb.qitems, (const int*)rb.nitem, icap, part, pcap,
-                (const bf16_t*)rb.c3, plane,
-                (const float*)rb.lg, CKpad, (const float*)rb.bmax, nbm, H, N, CQ, CK, W32, rb.delta);
+                (const uint16_t*)rb.c2, plane,
+                (const float*)rb.nv, CKpad, (const float*)rb.tsc, (const float*)rb.bmax, H, N, CQ, CK, W32, rb.delta);
   } else {
     PARK_LAUNCH("pama_cen_prep", k_cen_prep<64>, dim3(nbm, H), dim3(256), 0, st, cen, k_sizes, CK,
-                rb.c3, plane, rb.lg, CKpad, rb.cn, rb.bmax);
+                rb.c2, plane, rb.nv, CKpad, rb.tsc, rb.bmax);
     PARK_LAUNCH("pama_fast", k_pama_fast<64>, dim3(nwg), dim3(256), 0, st, (const bf16_t*)Qp,
                 q_offsets, (const int4*)rb.qitems, (const int*)rb.nitem, icap, part, pcap,
-                (const bf16_t*)rb.c3, plane,
-                (const float*)rb.lg, CKpad, (const float*)rb.bmax, nbm, H, N, CQ, CK, W32, rb.delta);
+                (const uint16_t*)rb.c2, plane,
+                (const float*)rb.nv, CKpad, (const float*)rb.tsc, (const float*)rb.bmax, H, N, CQ, CK, W32, rb.delta);
   }
   PARK_LAUNCH("pama_combine", k_pama_combine, dim3(CQ, H), dim3(256), 0, st, q_offsets,
               (const int*)rb.qstart, H, N, CQ, CK, (const float*)part, pcap, W32, rb.delta);

@@ -102,9 +102,9 @@ struct RetrieveBufs {
   float* delta;   // [H][CQ]     relative error bound of each fast row
   int* rows;      // [H][CQ]     rows left for the float64 path
   int* nrows;     // [H]
-  bf16_t* c3;     // [3][H][CK][D] centroids as three bf16 parts
-  float* lg;      // [H][pama_ckpad(CK)] log2(e) log n_v (-inf: empty and padding blocks)
-  float* cn;      // [H][CK]     |c_v|
+  uint16_t* c2;   // [2][H][CK][D] centroids as two f16 parts
+  float* nv;      // [H][CKpad]  n_v as floats, 0 past the last block
+  float* tsc;     // [H][ceil(CK / 32)] inverse scale of each centroid tile
   float* bmax;    // [H][ceil(CK/16)][2] per-block max |c_v|, |log n_v|
   int4* qitems;   // [H][pama_icap] fast-retrieval work list (chunks of 32 queries)
   int* nitem;     // [H] items per head

@@ -167,6 +167,38 @@ def test_retrieval_matches_oracle(case, mode):
             assert np.array_equal(kvi[h][u, :kvc[h][u]], kvi2[h][u, :kvc2[h][u]]), (h, u)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("CK", [33, 256, 300])
+@pytest.mark.parametrize("qexp,kexp", [(0, 0), (70, -70), (-60, 60), (-120, 90)])
+def test_retrieval_operand_ranges(d, CK, qexp, kexp):
+    # the f16 operands of the fast retrieval follow the range of the inputs by
+    # powers of two: queries and centroids far outside f16's range, norms that
+    # differ by 2^14 inside a 32-query chunk and by 2^9 inside a centroid tile,
+    # a zero query and a zero centroid, one sweep (CK <= 256) and two
+    rng = np.random.default_rng(1000 + d + CK + qexp)
+    N, CQ = 1500, 20
+    off = np.concatenate([[0], np.sort(rng.choice(np.arange(1, N), CQ - 1, False)), [N]])
+    Qp = 2.0 * rng.standard_normal((N, d)) * 2.0 ** rng.choice([0.0, -3.0, -14.0], size=(N, 1))
+    c = 2.0 * rng.standard_normal((CK, d)) * 2.0 ** rng.choice([0.0, -2.0, -9.0], size=(CK, 1))
+    Qp[5], c[7] = 0.0, 0.0
+    Qp = synth.bf16_round((Qp * 2.0 ** qexp).astype(np.float32))
+    c = (c * 2.0 ** kexp).astype(np.float32)
+    n = rng.integers(0, 40, CK)
+    W = O.pama(Qp, off, c, n)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)[None]).cuda()
+    for mode, param in (("topk", 0.2), ("topp", 0.9)):
+        sel = P.PARK_SELECT_TOPK if mode == "topk" else P.PARK_SELECT_TOPP
+        args = (PT.to_dev(Qp[None], "bf16"), t(off.astype(np.int32)), t(c), t(n.astype(np.int32)),
+                CQ, CK, sel, param)
+        kc, ki, Wg = P.park_retrieve_blocks(*args, want_W=True)
+        ok, err = PT.w_error_ok("bf16", Wg[0].cpu().numpy(), W)
+        assert ok, (mode, err)
+        kc2, ki2, _ = P.park_retrieve_blocks(*args)
+        for a, b in ((kc, ki), (kc2, ki2)):
+            assert PT.compare_masks(W, n, np.diff(off), mode, param, a[0].cpu().numpy(),
+                                    b[0].cpu().numpy())[1] == 0
+
+
 @pytest.mark.parametrize("mode", ["topk", "topp"])
 def test_retrieval_small_query_blocks(mode):
     # query blocks of 0-40 rows and a few of 100-300 (bf16): a wavefront's

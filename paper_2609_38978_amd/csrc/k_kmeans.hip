@@ -1408,21 +1408,15 @@ static bool kfilter_exact_radius() {
   return e && e[0] == '1';
 }
 
+// One part of the k-means: -1 the starting centroids, t in [0, T) the t-th
+// round, T the permutation of the last labels.
 template <typename T, int D>
 static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int C, int T_,
-                               uint64_t seed, int side, const KmeansBufs& kb, int* status,
+                               uint64_t seed, int side, const KmeansBufs& kb, int part, int* status,
                                hipStream_t st) {
   constexpr bool fast = sizeof(T) == 2;  // bf16 points: MFMA fast path + float64 refine
   const size_t plane = (size_t)H * C * D;
   const long ncen = (long)H * C * D;
-  if (kb.mu_init) {  // warm start: the caller's centroids (the previous recompute's means)
-    PARK_LAUNCH("kmeans_warm", k_copy64, dim3((unsigned)((ncen + 255) / 256)), dim3(256), 0, st,
-                kb.mu_init, kb.mu, ncen);
-  } else {
-    PARK_LAUNCH("kmeans_init", k_init_idx, dim3(H), dim3(1024), 0, st, N, C, seed, side, kb.init);
-    PARK_LAUNCH("kmeans_seed", k_seed_centroids<T>, dim3(C, H), dim3(D), 0, st, X,
-                (const int*)kb.init, N, D, C, kb.mu);
-  }
   // refine grid: persistent workgroups per head looping over 64-token chunks
   int rg = (2048 + H - 1) / H;
   const int max_tiles = (N + 63) / 64;
@@ -1433,11 +1427,23 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
   // round is a few tens of microseconds and the filter's passes cost more
   const bool filt = fast && kb.kf != nullptr && C >= 512 && kmeans_filter_enabled();
   const bool exact_radius = kfilter_exact_radius();
-  if constexpr (fast)
-    if (filt) PARK_TRY(launch_kfilter_setup((const bf16_t*)X, Gbar, H, N, D, *kb.kf, st));
+  if (part < 0) {
+    if (kb.mu_init) {  // warm start: the caller's centroids (the previous recompute's means)
+      PARK_LAUNCH("kmeans_warm", k_copy64, dim3((unsigned)((ncen + 255) / 256)), dim3(256), 0, st,
+                  kb.mu_init, kb.mu, ncen);
+    } else {
+      PARK_LAUNCH("kmeans_init", k_init_idx, dim3(H), dim3(1024), 0, st, N, C, seed, side, kb.init);
+      PARK_LAUNCH("kmeans_seed", k_seed_centroids<T>, dim3(C, H), dim3(D), 0, st, X,
+                  (const int*)kb.init, N, D, C, kb.mu);
+    }
+    if constexpr (fast)
+      if (filt) PARK_TRY(launch_kfilter_setup((const bf16_t*)X, Gbar, H, N, D, *kb.kf, st));
+    return PARK_OK;
+  }
   bf16_t* m2 = filt ? kb.kf->m2 : nullptr;
   float* mn = filt ? kb.kf->mn : nullptr;
-  for (int t = 0; t < T_; ++t) {
+  if (part < T_) {
+    const int t = part;
     const int nbm = (C + 15) / 16;
     // radii: round 1 measures them (k_radius); later rounds bound them from
     // the previous assignment's distances and the centroids' moves
@@ -1484,6 +1490,7 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
                   (const int*)kb.perm, (const int*)kb.offsets, N, C, kb.mu, (float*)nullptr,
                   (int*)nullptr);
     }
+    return PARK_OK;
   }
   PARK_TRY(launch_count_sort(kb.labels, H, N, C, kb.thist, kb.perm, kb.offsets, st));
   if (kb.mu_out) {
@@ -1499,16 +1506,20 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
 }
 
 park_status launch_kmeans(const void* X, const double* Gbar, int H, int N, int D, int dtype, int C,
-                          int T, uint64_t seed, int side, const KmeansBufs& kb, hipStream_t st) {
+                          int T, uint64_t seed, int side, const KmeansBufs& kb, int part,
+                          hipStream_t st) {
   int* status = kb.status;
   if (D == 128) {
     if (dtype == PARK_BF16)
-      return kmeans_impl<bf16_t, 128>((const bf16_t*)X, Gbar, H, N, C, T, seed, side, kb, status, st);
-    return kmeans_impl<float, 128>((const float*)X, Gbar, H, N, C, T, seed, side, kb, status, st);
+      return kmeans_impl<bf16_t, 128>((const bf16_t*)X, Gbar, H, N, C, T, seed, side, kb, part,
+                                      status, st);
+    return kmeans_impl<float, 128>((const float*)X, Gbar, H, N, C, T, seed, side, kb, part, status,
+                                   st);
   }
   if (dtype == PARK_BF16)
-    return kmeans_impl<bf16_t, 64>((const bf16_t*)X, Gbar, H, N, C, T, seed, side, kb, status, st);
-  return kmeans_impl<float, 64>((const float*)X, Gbar, H, N, C, T, seed, side, kb, status, st);
+    return kmeans_impl<bf16_t, 64>((const bf16_t*)X, Gbar, H, N, C, T, seed, side, kb, part, status,
+                                   st);
+  return kmeans_impl<float, 64>((const float*)X, Gbar, H, N, C, T, seed, side, kb, part, status, st);
 }
 
 }  // namespace park

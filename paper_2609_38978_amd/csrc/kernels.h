@@ -88,9 +88,11 @@ struct KmeansBufs {
   const double* mu_init = nullptr;  // [H][C][D] starting centroids (null: seeded init)
   double* mu_out = nullptr;         // [H][C][D] receives the means of the final clusters
 };
+// One part: -1 the starting centroids, t in [0, T) round t, T the permutation
+// (parts -1 .. T in order are the whole k-means).
 park_status launch_kmeans(const void* X, const double* Gbar /* null = Euclidean */, int H, int N,
                           int D, int dtype, int C, int T, uint64_t seed, int side,
-                          const KmeansBufs& kb, hipStream_t st);
+                          const KmeansBufs& kb, int part, hipStream_t st);
 park_status launch_segment_mean(const void* X, const int* perm, const int* offsets, int H, int N,
                                 int D, int dtype, int C, double* mu64, float* c32, int* sizes,
                                 hipStream_t st);

@@ -107,34 +107,44 @@ __global__ __launch_bounds__(256) void k_gram_mfma(const T* __restrict__ X, int 
     }
 }
 
-// G[h] = (sum over chunks, in chunk order) / N
-__global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, int nch, int DD,
-                                                     double invN, double* __restrict__ G) {
-  const int h = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= DD) return;
-  const double* p = part + (size_t)h * nch * DD + e;
-  double s = 0.0;
-  for (int c = 0; c < nch; ++c) s += p[(size_t)c * DD];
-  G[(size_t)h * DD + e] = s * invN;
-}
-
-// Symmetrise, scale and stabilise (Eq. (11)):
+// G = (sum over the chunks, in chunk order) / N, symmetrised, scaled and
+// stabilised (Eq. (11)):
 //   Gbar = (1 - alpha) (G + G^T) / 2 + (alpha s + eps s) I,
-//   s = max(tr G / d, s_min) (trace summed in index order);
-// one workgroup per head.  A non-finite entry (non-finite queries) raises
-// ST_NONFINITE.
+//   s = max(tr G / d, s_min) (trace summed in index order).
+// Workgroup = 256 entries of a head.  Bounded by the latency of the chunks'
+// loads: 32 are in flight per thread, and each workgroup sums the d diagonal
+// entries for the trace itself, so that one launch does what took two, the
+// second with one workgroup per head (d = 128: 20 + 23 -> 28 us at 8 x 16384,
+// 20 + 24 -> 15 us at 3 x 119056).  A non-finite entry (non-finite queries)
+// raises ST_NONFINITE.
 template <int D>
-__global__ __launch_bounds__(256) void k_metric_gbar(const double* __restrict__ G, double alpha,
-                                                     double eps, double s_min,
-                                                     double* __restrict__ Gbar_out, int* status) {
+__global__ __launch_bounds__(256) void k_metric_gbar(const double* __restrict__ part, int nch,
+                                                     double invN, double alpha, double eps,
+                                                     double s_min, double* __restrict__ Gbar_out,
+                                                     int* status) {
   __shared__ double pv[D];
   __shared__ double sc;
-  __shared__ int bad;
-  const int h = blockIdx.x, tid = threadIdx.x;
-  const double* Gh = G + (size_t)h * D * D;
-  if (tid == 0) bad = 0;
-  if (tid < D) pv[tid] = Gh[tid * D + tid];
+  const int h = blockIdx.y, tid = threadIdx.x;
+  const double* p = part + (size_t)h * nch * D * D;
+  const int e = blockIdx.x * 256 + tid, di = min(tid, D - 1) * (D + 1);
+  // this thread's entry and a diagonal one, 32 loads in flight
+  double g = 0.0, dg = 0.0;
+  for (int c0 = 0; c0 < nch; c0 += 16) {
+    double x[16], y[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double* pc = p + (size_t)min(c0 + k, nch - 1) * (D * D);
+      x[k] = pc[e];
+      y[k] = pc[di];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (c0 + k < nch) {
+        g += x[k];
+        dg += y[k];
+      }
+  }
+  if (tid < D) pv[tid] = dg * invN;
   __syncthreads();
   if (tid == 0) {
     double t = 0.0;
@@ -145,18 +155,11 @@ __global__ __launch_bounds__(256) void k_metric_gbar(const double* __restrict__ 
   const double s = sc;
   const double as = alpha * s, es = eps * s;
   double* Gb = Gbar_out + (size_t)h * D * D;
-  bool nf = false;
-  for (int e = tid; e < D * D; e += 256) {
-    const int i = e / D, j = e - i * D;
-    double v = (i == j) ? Gh[i * D + j] : (Gh[i * D + j] + Gh[j * D + i]) / 2.0;
-    v = (1.0 - alpha) * v;
-    if (i == j) v = (v + as) + es;
-    nf |= !isfinite(v);
-    Gb[e] = v;
-  }
-  if (nf) bad = 1;
-  __syncthreads();
-  if (tid == 0 && bad) raise_status(status, ST_NONFINITE);
+  // (the partial matrices are symmetric bit for bit: both triangles are one sum)
+  double v = (1.0 - alpha) * (g * invN);
+  if (e % (D + 1) == 0) v = (v + as) + es;
+  Gb[e] = v;
+  if (__any(!isfinite(v)) && (tid & 63) == 0) raise_status(status, ST_NONFINITE);
 }
 
 // Cholesky factor of Gbar = L L^T (R = L; x~ = R^T x); one workgroup per
@@ -268,7 +271,7 @@ size_t gram_chunks(int H, int N) {
 }
 
 park_status launch_metric(const void* Q, int H, int N, int D, int dtype, double alpha, double eps,
-                          double s_min, double* part, double* G, double* Gbar, int* status,
+                          double s_min, double* part, double* Gbar, int* status,
                           hipStream_t st) {
   const int nch = (int)gram_chunks(H, N);
   const int rows_per = (N + nch - 1) / nch;
@@ -288,15 +291,13 @@ park_status launch_metric(const void* Q, int H, int N, int D, int dtype, double 
       PARK_LAUNCH("gram_partial", (k_gram_mfma<float, 64>), g1, dim3(256), 0, st,
                   (const float*)Q, N, rows_per, part);
   }
-  const int DD = D * D;
-  PARK_LAUNCH("gram_reduce", k_gram_reduce, dim3((DD + 255) / 256, H), dim3(256), 0, st, part, nch,
-              DD, 1.0 / (double)N, G);
+  const double invN = 1.0 / (double)N;
   if (D == 128)
-    PARK_LAUNCH("metric_gbar", k_metric_gbar<128>, dim3(H), dim3(256), 0, st, G, alpha, eps,
-                s_min, Gbar, status);
+    PARK_LAUNCH("metric_gbar", k_metric_gbar<128>, dim3(64, H), dim3(256), 0, st, part, nch, invN,
+                alpha, eps, s_min, Gbar, status);
   else
-    PARK_LAUNCH("metric_gbar", k_metric_gbar<64>, dim3(H), dim3(256), 0, st, G, alpha, eps,
-                s_min, Gbar, status);
+    PARK_LAUNCH("metric_gbar", k_metric_gbar<64>, dim3(16, H), dim3(256), 0, st, part, nch, invN,
+                alpha, eps, s_min, Gbar, status);
   return PARK_OK;
 }
 

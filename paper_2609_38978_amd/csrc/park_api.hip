@@ -118,7 +118,6 @@ static park_status check_select(int mode, double param) {
 struct ClusterWs {
   int* init;
   double* part;
-  double* G;
   double* Gbar;
   double* R;
   double* mu;
@@ -141,7 +140,6 @@ static ClusterWs carve_cluster(Carver& cv, int H, int N, int D, int C) {
   ClusterWs c;
   c.init = cv.take<int>((size_t)H * C);
   c.part = cv.take<double>((size_t)H * gram_chunks(H, N) * D * D);
-  c.G = cv.take<double>((size_t)H * D * D);
   c.Gbar = cv.take<double>((size_t)H * D * D);
   c.R = cv.take<double>((size_t)H * D * D);
   c.mu = cv.take<double>((size_t)H * C * D);
@@ -401,7 +399,7 @@ static park_status cluster_body(const void* X, const void* Qm, const park_dims& 
   ClusterWs cw = carve_cluster(cv, H, N, D, C);
   const bool qrkc = metric == PARK_METRIC_QRKC;
   if (qrkc) {
-    PARK_TRY(launch_metric(Qm, H, N, D, dm.dtype, alpha, eps, s_min, cw.part, cw.G, cw.Gbar, status,
+    PARK_TRY(launch_metric(Qm, H, N, D, dm.dtype, alpha, eps, s_min, cw.part, cw.Gbar, status,
                            st));
     if (R_out || Xt_out) {
       double* R = R_out ? R_out : cw.R;
@@ -721,7 +719,7 @@ park_status park_forward(const void* Q, const void* K, const void* V, const park
     // longer than a small layer's rounds take the GPU (a single pass of 1 x 4096
     // float32 tokens 710 -> 608 us, of 8 x 16384 2073 -> 2021 us).
     park_status r = qrkc ? launch_metric(Q, H, N, D, dims->dtype, p->alpha, p->eps, p->s_min, ck.part,
-                                         ck.G, ck.Gbar, status, st)
+                                         ck.Gbar, status, st)
                          : PARK_OK;
     for (int part = -1; part <= p->T && r == PARK_OK; ++part) {
       r = launch_kmeans(Q, nullptr, H, N, D, dims->dtype, p->CQ, p->T, p->seed, 0, kq, part, sq);

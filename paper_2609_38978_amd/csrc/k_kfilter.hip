@@ -303,103 +303,113 @@ __global__ __launch_bounds__(256) void k_radius(const bf16_t* __restrict__ X,
 // rows of A (test with r2[a]) and, for V > A, word A of the rows of V (test
 // with r2[v], bits gathered across lanes by ballots).  Every word of every
 // row has exactly one writer.
-// Workgroup: one 32-cluster tile A (the B operand: mu parts, in LDS for the
-// four wavefronts) and a group of 16 centroid tiles (the A operand: w parts,
-// four per wavefront).
+// With S = V1[v] - |mu_a| V2[v] - 2 t^ + A, where V1, V2 and A gather lo's and
+// the gap's terms of v and of a, v is dropped from S_a when S > 4 r2[a]
+// (1 + 1e-9) (the 1e-12 covers this order's float64 rounding as well): six
+// float64 operations a pair for both tests.
+// Workgroup: four 32-cluster tiles A, one per wavefront (the B operand: both mu
+// parts in registers), against vc <= kCandTiles centroid tiles (the A operand: w
+// parts), which stream through an LDS ring that the four wavefronts share.  It
+// is bounded by the reads of w and their latency: wavefronts that each read
+// their own w rows straight into the operand layout, a quarter of a line at a
+// time, took 94 us at 40 heads, C = 1182 and 126 us at 24 heads, C = 1861,
+// now 49 and 63 us (d = 128).
+constexpr int kCandTiles = 8;
 template <int D>
-__global__ __launch_bounds__(256, 2) void k_cand(const bf16_t* __restrict__ m2, size_t mplane,
+__global__ __launch_bounds__(256, 3) void k_cand(const bf16_t* __restrict__ m2, size_t mplane,
                                                  const bf16_t* __restrict__ w3, size_t wplane,
                                                  const float* __restrict__ mn,
                                                  const float* __restrict__ wn, int Cpad,
                                                  const double* __restrict__ b,
-                                                 const double* __restrict__ r2, int C,
+                                                 const double* __restrict__ r2, int C, int vc,
                                                  uint32_t* __restrict__ cand) {
-  constexpr int KS = D / 16, CPR = D / 8;
+  constexpr int KS = D / 16, CPR = D / 8, RPI = 64 / CPR, NI = 64 / (4 * RPI);
   constexpr double EC = 3.2 * 1.52587890625e-05 + (3 * D + 1) * 1.1920928955078125e-07 * 1.02;
   const int h = blockIdx.y, tid = threadIdx.x, l = tid & 63, hf = l >> 5, c32 = l & 31;
-  const int w = tid >> 6;
-  const int at = blockIdx.x, a0 = at * 32, a = a0 + c32;
-  const int nvt = (C + 31) / 32;
-  const int vt_beg = max(at, (int)blockIdx.z * 16), vt_end = min(nvt, (int)(blockIdx.z + 1) * 16);
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int at = 4 * (int)blockIdx.x + w, a0 = at * 32, a = a0 + c32;
+  const int nvt = (C + 31) / 32, z0 = (int)blockIdx.z * vc;
+  const int vt_beg = max(4 * (int)blockIdx.x, z0), vt_end = min(nvt, z0 + vc);
   if (vt_beg >= vt_end) return;  // the transposed writes of other tile pairs cover these
+  __shared__ __attribute__((aligned(16))) bf16_t Wt[2][2 * 32 * D];
+  __shared__ double v1_s[32 * kCandTiles], v2_s[32 * kCandTiles], vr_s[32 * kCandTiles];
+  // a tile of w in two bf16 parts, 16-byte chunks swizzled by the row
+  auto issue = [&](int vt, int slot) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = (w * NI + i) * RPI + l / CPR, part = row / 32, r = row % 32;
+      const int v = min(vt * 32 + r, C - 1);
+      const bf16_t* src =
+          w3 + part * wplane + ((size_t)h * C + v) * D + 8 * ((l % CPR) ^ kf_swz<D>(r));
+      kf_dma16(src, kf_lds_addr(&Wt[slot][0] + (w * NI + i) * 512));
+    }
+  };
+  issue(vt_beg, 0);
   const bool aval = a < C;
   const int ar = aval ? a : C - 1;
-  // the tile's centroids in two bf16 parts, 16-byte chunks swizzled by the row
-  __shared__ __attribute__((aligned(16))) bf16_t Ms[2 * 32 * D];
-  for (int e = tid; e < 2 * 32 * CPR; e += 256) {
-    const int part = e / (32 * CPR), rem = e % (32 * CPR), row = rem / CPR, c = rem % CPR;
-    const int rr = min(a0 + row, C - 1);
-    const uint4 v = *(const uint4*)(m2 + part * mplane + ((size_t)h * C + rr) * D + 8 * c);
-    *(uint4*)(Ms + part * 32 * D + row * D + 8 * (c ^ kf_swz<D>(row))) = v;
+  kf_bf16x8_t m1f[KS], m2f[KS];
+  {
+    const bf16_t* M1 = m2 + ((size_t)h * C + ar) * D + 8 * hf;
+#pragma unroll
+    for (int s2 = 0; s2 < KS; ++s2) {
+      m1f[s2] = *(const kf_bf16x8_t*)(M1 + 16 * s2);
+      m2f[s2] = *(const kf_bf16x8_t*)(M1 + mplane + 16 * s2);
+    }
   }
-  const double ra = aval ? r2[(size_t)h * C + a] : -1.0;
+  const double ra = aval ? 4.0 * r2[(size_t)h * C + a] * (1.0 + 1e-9) : -1.0;
   const double ba = b[(size_t)h * C + ar];
   const double man = (double)mn[(size_t)h * C + ar];
-  const double ana = man * (double)wn[(size_t)h * Cpad + ar];
+  const double A =
+      ba - (1e-9 + 1e-12) * fabs(ba) - 1e-12 * (man * (double)wn[(size_t)h * Cpad + ar]);
+  const uint32_t amask = C - a0 >= 32 ? ~0u : (1u << max(C - a0, 0)) - 1u;
   uint32_t* crow = cand + ((size_t)h * C + ar) * 64;
-  // b_v, |w_v|, |mu_v| |w_v| and r2[v] of this workgroup's 16 centroid tiles
-  __shared__ double vb_s[512], vw_s[512], vm_s[512], vr_s[512];
-  for (int e = tid; e < 512; e += 256) {
-    const int v = (int)blockIdx.z * 512 + e, vr = min(v, C - 1);
-    const double wv = (double)wn[(size_t)h * Cpad + vr];
-    vb_s[e] = b[(size_t)h * C + vr];
-    vw_s[e] = wv;
-    vm_s[e] = (double)mn[(size_t)h * C + vr] * wv;
-    vr_s[e] = v < C ? r2[(size_t)h * C + v] : -1.0;
+  // V1, V2 and 4 r2[v] (1 + 1e-9) of this workgroup's centroid tiles
+  for (int e = tid; e < 32 * vc; e += 256) {
+    const int v = z0 * 32 + e, vr = min(v, C - 1);
+    const double wv = (double)wn[(size_t)h * Cpad + vr], bv = b[(size_t)h * C + vr];
+    v1_s[e] = bv - (1e-9 + 1e-12) * fabs(bv) - 1e-12 * ((double)mn[(size_t)h * C + vr] * wv);
+    v2_s[e] = 2.0 * EC * wv;
+    vr_s[e] = v < C ? 4.0 * r2[(size_t)h * C + v] * (1.0 + 1e-9) : -1.0;
   }
-  __syncthreads();
   const int rowo = c32 * D, swk = kf_swz<D>(c32);
-  const bf16_t* M1 = Ms;
-  const bf16_t* M2 = Ms + 32 * D;
-  for (int vt = vt_beg + w; vt < vt_end; vt += 4) {
+  for (int vt = vt_beg; vt < vt_end; ++vt) {
+    kf_wait_vmcnt<0>();
+    __syncthreads();  // tile vt landed; tile vt - 1 consumed by every wavefront
+    const int slot = (vt - vt_beg) & 1;
+    if (vt + 1 < vt_end) issue(vt + 1, slot ^ 1);
+    if (vt < at || at >= nvt) continue;
     const int v0 = vt * 32;
-    kf_bf16x8_t w1f[KS], w2f[KS];
-    {
-      const int vr = min(v0 + c32, C - 1);
-      const bf16_t* W1 = w3 + ((size_t)h * C + vr) * D + 8 * hf;
-#pragma unroll
-      for (int s2 = 0; s2 < KS; ++s2) {
-        w1f[s2] = __builtin_bit_cast(kf_bf16x8_t, *(const uint4*)(W1 + 16 * s2));
-        w2f[s2] = __builtin_bit_cast(kf_bf16x8_t, *(const uint4*)(W1 + wplane + 16 * s2));
-      }
-    }
-
+    const bf16_t* W1 = &Wt[slot][0];
+    const bf16_t* W2 = W1 + 32 * D;
     kf_f32x16_t acc;
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.0f;
 #pragma unroll
     for (int s2 = 0; s2 < KS; ++s2) {
-      const kf_bf16x8_t m1 = *(const kf_bf16x8_t*)(M1 + rowo + 8 * ((2 * s2 + hf) ^ swk));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2f[s2], m1, acc, 0, 0, 0);
+      const kf_bf16x8_t w2 = *(const kf_bf16x8_t*)(W2 + rowo + 8 * ((2 * s2 + hf) ^ swk));
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2, m1f[s2], acc, 0, 0, 0);
     }
 #pragma unroll
     for (int s2 = 0; s2 < KS; ++s2) {
-      const int co = rowo + 8 * ((2 * s2 + hf) ^ swk);
-      const kf_bf16x8_t m1 = *(const kf_bf16x8_t*)(M1 + co);
-      const kf_bf16x8_t mm2 = *(const kf_bf16x8_t*)(M2 + co);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1f[s2], mm2, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1f[s2], m1, acc, 0, 0, 0);
+      const kf_bf16x8_t w1 = *(const kf_bf16x8_t*)(W1 + rowo + 8 * ((2 * s2 + hf) ^ swk));
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, m2f[s2], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, m1f[s2], acc, 0, 0, 0);
     }
     // lane: pairs (a, v0 + 8 bq + 4 hf + r) for q = 4 bq + r
     uint32_t bits = 0u;
     uint32_t tw[16];  // transposed: bit (a, v) of row v, by q
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int vi = 8 * (q >> 2) + 4 * hf + (q & 3), v = v0 + vi;
-      const int li = v0 - (int)blockIdx.z * 512 + vi;
-      const double bv = vb_s[li];
-      const double t = (double)acc[q];
-      const double lo = ba + bv - 2.0 * t - 2.0 * EC * man * vw_s[li] -
-                        1e-12 * (fabs(ba) + fabs(bv) + ana + vm_s[li]);
-      const double gap = 1e-9 * (fabs(ba) + fabs(bv));
-      const bool inr = v < C && aval;
-      const bool keep = inr && ra >= 0.0 && (v == a || !(lo > 4.0 * ra * (1.0 + 1e-9) + gap));
+      const int vi = 8 * (q >> 2) + 4 * hf + (q & 3), li = v0 - z0 * 32 + vi;
+      const double S = fma(-2.0, (double)acc[q], fma(-man, v2_s[li], v1_s[li] + A));
       const double rv = vr_s[li];
-      const bool keept = inr && rv >= 0.0 && !(lo > 4.0 * rv * (1.0 + 1e-9) + gap);
-      bits |= keep ? (1u << vi) : 0u;
-      const unsigned long long bal = __ballot(keept);
-      tw[q] = (uint32_t)(hf == 0 ? bal : (bal >> 32));
+      bits |= S > ra ? 0u : (1u << vi);
+      const unsigned long long bal = __ballot(rv >= 0.0 && !(S > rv));
+      tw[q] = (uint32_t)(hf == 0 ? bal : (bal >> 32)) & amask;
     }
+    if (vt == at) bits |= 1u << c32;
+    if (!(ra >= 0.0)) bits = 0u;
+    if (C - v0 < 32) bits &= (1u << (C - v0)) - 1u;
     bits |= (uint32_t)__shfl_xor((int)bits, 32, 64);
     if (hf == 0 && aval) crow[vt] = bits;
     if (vt > at) {
@@ -462,20 +472,25 @@ __global__ __launch_bounds__(256) void k_tile_union(const int* __restrict__ perm
 // exact argmin over all centroids; the certification uses the maxima of the
 // error terms over all centroids.  Uncertified tokens are listed for the
 // float64 refinement as before.
+// Bounded by the latency of its chain of loads (the tile's union, its rows of
+// X and w; 2.4 steps of 32 rows a tile at 40 x 75600, C = 1182): the rows of X
+// are asked for before the row list is built, the first rows of w and the
+// scores' constants together after it, and neighbouring tiles, which share
+// candidates, run on one XCD (311 -> 259 us there, 55 -> 42 us at 3 x 119056).
 // workgroups per CU of the two-part filtered assignment (its LDS allows 3;
-// 3 caps it at 168 registers, which spills, and measured no faster than 2)
+// at 2 the early loads cost the third: 292 us)
 // bf16 parts of w in the filtered assignment at C >= 512 (3 below)
 #ifndef PARK_KM_CAND_NP
 #define PARK_KM_CAND_NP 2
 #endif
 #ifndef PARK_KM_CAND_OCC
-#define PARK_KM_CAND_OCC 2
+#define PARK_KM_CAND_OCC 3
 #endif
 template <int D, int NP>
 __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_cand(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ w3, size_t plane,
     const float* __restrict__ b32, int Cpad, const float* __restrict__ wn,
-    const float* __restrict__ eb, const float* __restrict__ bmax, int nbm, int N, int C,
+    const float* __restrict__ eb, const float* __restrict__ bmax, int nbm, int H, int N, int C, int NT,
     const int* __restrict__ perm, const uint32_t* __restrict__ tun,
     const int* __restrict__ talo, int* __restrict__ labels, int* __restrict__ flags,
     float* __restrict__ flagu, int* __restrict__ nflag, const double* __restrict__ xn,
@@ -499,25 +514,45 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
   __shared__ float mx_s[2];
   __shared__ int wcnt[4];
   __shared__ unsigned long long dm_s[64];  // radius bounds of clusters alo .. alo + 63
-  const int h = blockIdx.y, tid = threadIdx.x, l = tid & 63, hf = l >> 5, c32 = l & 31;
+  const int tid = threadIdx.x, l = tid & 63, hf = l >> 5, c32 = l & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int p0 = blockIdx.x * kmeans_tile;
+  const int per = (H * NT + 7) >> 3, ti = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (ti >= H * NT) return;
+  const int h = ti / NT, tile = ti - h * NT, nw = (C + 31) / 32;
+  const int p0 = tile * kmeans_tile;
   const int pend = min(N, p0 + kmeans_tile);
   const int* ph = perm + (size_t)h * N;
-  const int* zh = labels + (size_t)h * N;
+  // tokens of this wavefront: sorted positions p0 + w 32 TB + 32 tb + c32.
+  // Their rows are loaded before the row list is built, which takes several
+  // dependent loads itself
+  const bf16_t* Xh = X + (size_t)h * N * D;
+  kf_bf16x8_t xf[TB][KS];
+  float xsq[TB];
+  int toks[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    const int p = p0 + w * 32 * TB + 32 * tb + c32;
+    toks[tb] = p < pend ? ph[p] : -1;
+  }
   // the union of the candidate sets of the clusters this tile spans, and its
   // first cluster (k_tile_union, from the previous labels)
-  const size_t ti = (size_t)h * gridDim.x + blockIdx.x;
   if (tid < 64) {
-    uw[tid] = tun[ti * 64 + tid];
+    uw[tid] = tid < nw ? tun[(size_t)ti * 64 + tid] : 0u;
     dm_s[tid] = 0ull;
   }
   if (tid == 0) seg[0] = talo[ti];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) {
+    toks[tb] = (unsigned)toks[tb] < (unsigned)N ? toks[tb] : -1;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      xf[tb][s] = *(const kf_bf16x8_t*)(Xh + (size_t)max(toks[tb], 0) * D + 16 * s + 8 * hf);
+    }
+  }
   __syncthreads();
   const int alo = min(max(seg[0], 0), C - 1);
   if (tid < 64) {
-    const uint32_t x = tid * 32 < C ? uw[tid] : 0u;
-    int inc = __popc(x);
+    int inc = __popc(uw[tid]);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const int y = __shfl_up(inc, o, 64);
@@ -527,25 +562,33 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
     if (tid == 0) wpre[0] = 0;
   }
   __syncthreads();
-  const int U = wpre[64];
-  for (int e = tid; e < 64 * 32; e += 256) {
+  const int U = wpre[64], ntiles = (U + CT - 1) / CT;
+  for (int e = tid; e < nw * 32; e += 256) {
     const int word = e >> 5, bit = e & 31;
-    const uint32_t x = word * 32 < C ? uw[word] : 0u;
-    if ((x >> bit) & 1u) {
-      const int pos = wpre[word] + __popc(x & ((1u << bit) - 1u));
-      const int v = word * 32 + bit;
-      ulist[pos] = (uint16_t)v;
-      ub[pos] = b32[(size_t)h * Cpad + v];
+    const uint32_t x = uw[word];
+    if ((x >> bit) & 1u)
+      ulist[wpre[word] + __popc(x & ((1u << bit) - 1u))] = (uint16_t)(word * 32 + bit);
+  }
+  if (tid < ntiles * CT - U) ulist[U + tid] = 0;  // any valid row; its score is +inf
+  __syncthreads();  // ulist ready
+  const bf16_t* P1 = w3 + (size_t)h * C * D;
+  const int pch = l % CPR;
+  auto issue = [&](int t, int slot) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = (w * NI + i) * RPI + l / CPR;
+      const int part = row / CT, r = row % CT;
+      const int v = min((int)ulist[t * CT + r], C - 1);
+      const bf16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ kf_swz<D>(r));
+      kf_dma16(src, kf_lds_addr(&Wt[slot][0] + (w * NI + i) * 512));
     }
-  }
-  const int ntiles = (U + CT - 1) / CT;
-  for (int pos = U + tid; pos < ntiles * CT; pos += 256) {
-    ulist[pos] = 0;  // any valid row; its score is +inf
-    ub[pos] = INFINITY;
-  }
-  if (tid < 64) {
+  };
+  if (ntiles > 0) issue(0, 0);
+  for (int pos = tid; pos < ntiles * CT; pos += 256)
+    ub[pos] = pos < U ? b32[(size_t)h * Cpad + ulist[pos]] : INFINITY;
+  if (w == 3) {
     float a = 0.0f, c = 0.0f;
-    for (int i = tid; i < nbm; i += 64) {
+    for (int i = l; i < nbm; i += 64) {
       a = fmaxf(a, bmax[((size_t)h * nbm + i) * 2]);
       c = fmaxf(c, bmax[((size_t)h * nbm + i) * 2 + 1]);
     }
@@ -553,42 +596,17 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
       a = fmaxf(a, __shfl_xor(a, o, 64));
       c = fmaxf(c, __shfl_xor(c, o, 64));
     }
-    if (tid == 0) {
+    if (l == 0) {
       mx_s[0] = a;
       mx_s[1] = c;
     }
   }
-  __syncthreads();  // ulist, ub, mx_s ready
-  const bf16_t* P1 = w3 + (size_t)h * C * D;
-  const int pch = l % CPR;
-  auto issue = [&](int tile, int slot) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int row = (w * NI + i) * RPI + l / CPR;
-      const int part = row / CT, r = row % CT;
-      const int v = min((int)ulist[tile * CT + r], C - 1);
-      const bf16_t* src = P1 + part * plane + (size_t)v * D + 8 * (pch ^ kf_swz<D>(r));
-      kf_dma16(src, kf_lds_addr(&Wt[slot][0] + (w * NI + i) * 512));
-    }
-  };
-  if (ntiles > 0) issue(0, 0);
-  // tokens of this wavefront: sorted positions p0 + w 32 TB + 32 tb + c32
-  const bf16_t* Xh = X + (size_t)h * N * D;
-  kf_bf16x8_t xf[TB][KS];
-  float xsq[TB];
-  int toks[TB];
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb) {
     xsq[tb] = 0.0f;
-    const int p = p0 + w * 32 * TB + 32 * tb + c32;
-    int tok = p < pend ? ph[p] : -1;
-    tok = (unsigned)tok < (unsigned)N ? tok : -1;
-    toks[tb] = tok;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-      if (tok >= 0) raw = *(const uint4*)(Xh + (size_t)tok * D + 16 * s + 8 * hf);
-      xf[tb][s] = __builtin_bit_cast(kf_bf16x8_t, raw);
+      const uint4 raw = __builtin_bit_cast(uint4, xf[tb][s]);
       const uint32_t q[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -700,6 +718,7 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
     if (hf == 0 && tok >= 0) {
       bool ok = false;
       float e1 = 0.0f;
+      const double xnt = xn[(size_t)h * N + tok];
       if (bidx[tb] >= 0 && isfinite(best[tb])) {
         const int v = bidx[tb];
         e1 = fmaf(kx[tb], wn[(size_t)h * Cpad + v], eb[(size_t)h * Cpad + v]);
@@ -712,7 +731,7 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
         labels[(size_t)h * N + tok] = v;
         // D(x, mu_v)^2 <= x^T Gbar x + (the exact score's upper bound); the
         // 1e-6 e1 term covers the float64 score against the exact one
-        const double d2 = fmax(xn[(size_t)h * N + tok] + (double)ubv[tb] + 1e-6 * (double)e1, 0.0);
+        const double d2 = fmax(xnt + (double)ubv[tb] + 1e-6 * (double)e1, 0.0);
         const unsigned long long bits = (unsigned long long)__double_as_longlong(d2);
         if ((unsigned)(v - alo) < 64u) atomicMax(&dm_s[v - alo], bits);
         else atomicMax(&dmax[(size_t)h * C + v], bits);
@@ -731,9 +750,9 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
   __syncthreads();
   if (tid < 64 && alo + tid < C && dm_s[tid] != 0ull)
     atomicMax(&dmax[(size_t)h * C + alo + tid], dm_s[tid]);
-  int base = blockIdx.x * kmeans_tile;
+  int base = p0;
   for (int q = 0; q < w; ++q) base += wcnt[q];
-  if (tid == 0) nflag[(size_t)h * gridDim.x + blockIdx.x] = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+  if (tid == 0) nflag[ti] = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
   if (tot > 0) {
     const uint64_t below = (1ull << l) - 1ull;
 #pragma unroll
@@ -1121,11 +1140,17 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
   const int Cpad = kmeans_cpad(C);
   const size_t plane = (size_t)H * C * D;
   const int nbm = (C + 15) / 16;
-  const dim3 gr((C + 3) / 4, H), gc((C + 31) / 32, H, ((C + 31) / 32 + 15) / 16),
-      ga((N + kmeans_tile - 1) / kmeans_tile, H);
-  // refine on the union: one wavefront per tile, a head's tiles on one XCD
   const int NT = (N + kmeans_tile - 1) / kmeans_tile;
-  const dim3 gu(8 * ((H * NT + 7) / 8));
+  // k_cand: half as many tiles a workgroup where that leaves most of the 768
+  // workgroups the chip holds idle (3 heads, C = 1861: 23 us with 8, 19 with 4;
+  // 40 heads, C = 1182: 49 and 55)
+  const int nvt = (C + 31) / 32, ngrp = (nvt + 3) / 4;
+  const int vc = H * ngrp * ((nvt + kCandTiles - 1) / kCandTiles) >= 768 ? kCandTiles
+                                                                           : kCandTiles / 2;
+  const dim3 gr((C + 3) / 4, H), gc(ngrp, H, (nvt + vc - 1) / vc);
+  // assignment and refine: a head's neighbouring tiles, which share candidates,
+  // on one XCD
+  const dim3 gt(8 * ((H * NT + 7) / 8));
   if (D == 128) {
     if (measure_radius)
       PARK_LAUNCH("kfilter_radius", k_radius<128>, gr, dim3(256), 0, st, X, (const int*)kb.perm,
@@ -1133,23 +1158,23 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
                   (const double*)kb.b, N, C, kf.r2);
     PARK_LAUNCH("kfilter_cand", k_cand<128>, gc, dim3(256), 0, st, (const bf16_t*)kf.m2, plane,
                 (const bf16_t*)kb.w3, plane, (const float*)kf.mn, (const float*)kb.wn, Cpad,
-                (const double*)kb.b, (const double*)kf.r2, C, kf.cand);
+                (const double*)kb.b, (const double*)kf.r2, C, vc, kf.cand);
     PARK_LAUNCH("kfilter_union", k_tile_union, dim3((H * NT + 3) / 4), dim3(256), 0, st,
                 (const int*)kb.perm, (const int*)kb.labels, (const uint32_t*)kf.cand, H, N, C, NT,
                 kf.tun, kf.talo);
     if (C >= 512 && PARK_KM_CAND_NP == 2)
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 2>), ga, dim3(256), 0, st, X,
+      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 2>), gt, dim3(256), 0, st, X,
                   (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, N, C, (const int*)kb.perm,
+                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
                   (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
                   kb.nflag, (const double*)kf.xn, kf.dmax);
     else
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 3>), ga, dim3(256), 0, st, X,
+      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 3>), gt, dim3(256), 0, st, X,
                   (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, N, C, (const int*)kb.perm,
+                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
                   (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
                   kb.nflag, (const double*)kf.xn, kf.dmax);
-    PARK_LAUNCH("kmeans_refine_union", k_refine_union<128>, gu, dim3(64), 0, st, X,
+    PARK_LAUNCH("kmeans_refine_union", k_refine_union<128>, gt, dim3(64), 0, st, X,
                 (const bf16_t*)kb.w3, plane, (const float*)kb.b32, (const float*)kb.wn,
                 (const float*)kb.eb, Cpad, (const double*)kb.w, (const double*)kb.b,
                 (const uint32_t*)kf.cand, H, N, C, NT, (const int*)kb.flags,
@@ -1162,23 +1187,23 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
                   (const double*)kb.b, N, C, kf.r2);
     PARK_LAUNCH("kfilter_cand", k_cand<64>, gc, dim3(256), 0, st, (const bf16_t*)kf.m2, plane,
                 (const bf16_t*)kb.w3, plane, (const float*)kf.mn, (const float*)kb.wn, Cpad,
-                (const double*)kb.b, (const double*)kf.r2, C, kf.cand);
+                (const double*)kb.b, (const double*)kf.r2, C, vc, kf.cand);
     PARK_LAUNCH("kfilter_union", k_tile_union, dim3((H * NT + 3) / 4), dim3(256), 0, st,
                 (const int*)kb.perm, (const int*)kb.labels, (const uint32_t*)kf.cand, H, N, C, NT,
                 kf.tun, kf.talo);
     if (C >= 512 && PARK_KM_CAND_NP == 2)
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 2>), ga, dim3(256), 0, st, X,
+      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 2>), gt, dim3(256), 0, st, X,
                   (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, N, C, (const int*)kb.perm,
+                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
                   (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
                   kb.nflag, (const double*)kf.xn, kf.dmax);
     else
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 3>), ga, dim3(256), 0, st, X,
+      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 3>), gt, dim3(256), 0, st, X,
                   (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, N, C, (const int*)kb.perm,
+                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
                   (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
                   kb.nflag, (const double*)kf.xn, kf.dmax);
-    PARK_LAUNCH("kmeans_refine_union", k_refine_union<64>, gu, dim3(64), 0, st, X,
+    PARK_LAUNCH("kmeans_refine_union", k_refine_union<64>, gt, dim3(64), 0, st, X,
                 (const bf16_t*)kb.w3, plane, (const float*)kb.b32, (const float*)kb.wn,
                 (const float*)kb.eb, Cpad, (const double*)kb.w, (const double*)kb.b,
                 (const uint32_t*)kf.cand, H, N, C, NT, (const int*)kb.flags,

@@ -863,3 +863,32 @@ def test_kmeans_candidate_filter_matches_oracle_and_dense(name, grid, C, side):
         assert n_bad == 0
         p2, o2 = O.stable_argsort(lab[h], C)
         assert np.array_equal(perm[h], p2) and np.array_equal(off[h], o2)
+
+
+# Both group sizes of the candidate kernel (many heads or few), centroid tiles
+# and tile groups cut short, the most centroids: whichever centroids the filter
+# leaves, the labels, order and offsets are those of scoring every centroid.
+@pytest.mark.parametrize("H,N,C,d", [(64, 1111, 520, 128), (64, 1111, 545, 64),
+                                     (3, 4097, 2048, 128), (2, 2049, 673, 64)])
+def test_kmeans_candidate_tiles(H, N, C, d):
+    import os
+    g = torch.Generator().manual_seed(11)
+    cen = 2.0 * torch.randn(H, 96, d, generator=g)
+    pick = torch.randint(96, (H, N, 1), generator=g).expand(-1, -1, d)
+    K = (cen.gather(1, pick) + torch.randn(H, N, d, generator=g)).to(torch.bfloat16).cuda()
+    Q = torch.randn(H, N, d, generator=g).to(torch.bfloat16).cuda()
+    print(f"[candidate tiles {H} {N} {C} {d}]", flush=True)
+
+    def run():
+        o = P.park_cluster_keys(K, C, 4, seed=5, side=1, metric=P.PARK_METRIC_QRKC, Qmetric=Q)
+        P.park_check(o["ws"])
+        return [o[k].cpu().numpy() for k in ("labels", "perm", "offsets")]
+
+    got = run()
+    os.environ["PARK_KMEANS_FILTER"] = "0"
+    try:
+        ref = run()
+    finally:
+        del os.environ["PARK_KMEANS_FILTER"]
+    for x, y in zip(got, ref):
+        assert np.array_equal(x, y)

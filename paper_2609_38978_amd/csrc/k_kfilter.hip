@@ -477,17 +477,10 @@ __global__ __launch_bounds__(256) void k_tile_union(const int* __restrict__ perm
 // are asked for before the row list is built, the first rows of w and the
 // scores' constants together after it, and neighbouring tiles, which share
 // candidates, run on one XCD (311 -> 259 us there, 55 -> 42 us at 3 x 119056).
-// workgroups per CU of the two-part filtered assignment (its LDS allows 3;
-// at 2 the early loads cost the third: 292 us)
-// bf16 parts of w in the filtered assignment at C >= 512 (3 below)
-#ifndef PARK_KM_CAND_NP
-#define PARK_KM_CAND_NP 2
-#endif
-#ifndef PARK_KM_CAND_OCC
-#define PARK_KM_CAND_OCC 3
-#endif
-template <int D, int NP>
-__global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_cand(
+// Three workgroups per CU at d = 128 (as the LDS allows): at two, for which the
+// compiler's own register choice leaves room, 292 us.
+template <int D>
+__global__ __launch_bounds__(256, 3) void k_assign_cand(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ w3, size_t plane,
     const float* __restrict__ b32, int Cpad, const float* __restrict__ wn,
     const float* __restrict__ eb, const float* __restrict__ bmax, int nbm, int H, int N, int C, int NT,
@@ -495,12 +488,12 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
     const int* __restrict__ talo, int* __restrict__ labels, int* __restrict__ flags,
     float* __restrict__ flagu, int* __restrict__ nflag, const double* __restrict__ xn,
     unsigned long long* __restrict__ dmax) {
-  constexpr int TB = PARK_KM_TB, CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
+  constexpr int NP = 2, TB = PARK_KM_TB, CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
   constexpr int NI = NP * CT / (4 * RPI);
-  static_assert(NI * 4 * RPI == NP * CT && (NP == 2 || NP == 3), "tile shape");
+  static_assert(NI * 4 * RPI == NP * CT, "tile shape");
   static_assert(kmeans_tile == 128 * TB, "tile tokens");
   constexpr float U24 = 5.9604645e-08f, DEL = 1.1920929e-07f;
-  constexpr float ER = NP == 2 ? 1.52587891e-05f : U24;
+  constexpr float ER = 1.52587891e-05f;
   constexpr float ET = ER * 1.01f + (D + 1) * DEL * 1.0079f +
                        0.00390625f * 1.01f * ((NP - 1) * D + 1) * DEL + U24 * 1.01f;
   constexpr float KXC = 1.1f * (2.0f * ET + 2.01f * U24) * 1.0001f;
@@ -640,7 +633,6 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
     const int slot = t % NS;
     const bf16_t* W1 = &Wt[slot][0];
     const bf16_t* W2 = W1 + CT * D;
-    const bf16_t* W3 = W2 + CT * D;
     kf_f32x16_t acc[TB];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
@@ -650,14 +642,9 @@ __global__ __launch_bounds__(256, NP == 2 ? PARK_KM_CAND_OCC : 2) void k_assign_
     for (int s = 0; s < KS; ++s) {
       const int co = rowo + 8 * ((2 * s + hf) ^ swk);
       const kf_bf16x8_t a2 = *(const kf_bf16x8_t*)(W2 + co);
-      kf_bf16x8_t a3;
-      if constexpr (NP == 3) a3 = *(const kf_bf16x8_t*)(W3 + co);
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
+      for (int tb = 0; tb < TB; ++tb)
         acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, xf[tb][s], acc[tb], 0, 0, 0);
-        if constexpr (NP == 3)
-          acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, xf[tb][s], acc[tb], 0, 0, 0);
-      }
     }
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -1162,18 +1149,11 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
     PARK_LAUNCH("kfilter_union", k_tile_union, dim3((H * NT + 3) / 4), dim3(256), 0, st,
                 (const int*)kb.perm, (const int*)kb.labels, (const uint32_t*)kf.cand, H, N, C, NT,
                 kf.tun, kf.talo);
-    if (C >= 512 && PARK_KM_CAND_NP == 2)
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 2>), gt, dim3(256), 0, st, X,
-                  (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
-                  (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
-                  kb.nflag, (const double*)kf.xn, kf.dmax);
-    else
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<128, 3>), gt, dim3(256), 0, st, X,
-                  (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
-                  (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
-                  kb.nflag, (const double*)kf.xn, kf.dmax);
+    PARK_LAUNCH("kmeans_assign_cand", k_assign_cand<128>, gt, dim3(256), 0, st, X,
+                (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
+                (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
+                (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
+                kb.nflag, (const double*)kf.xn, kf.dmax);
     PARK_LAUNCH("kmeans_refine_union", k_refine_union<128>, gt, dim3(64), 0, st, X,
                 (const bf16_t*)kb.w3, plane, (const float*)kb.b32, (const float*)kb.wn,
                 (const float*)kb.eb, Cpad, (const double*)kb.w, (const double*)kb.b,
@@ -1191,18 +1171,11 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
     PARK_LAUNCH("kfilter_union", k_tile_union, dim3((H * NT + 3) / 4), dim3(256), 0, st,
                 (const int*)kb.perm, (const int*)kb.labels, (const uint32_t*)kf.cand, H, N, C, NT,
                 kf.tun, kf.talo);
-    if (C >= 512 && PARK_KM_CAND_NP == 2)
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 2>), gt, dim3(256), 0, st, X,
-                  (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
-                  (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
-                  kb.nflag, (const double*)kf.xn, kf.dmax);
-    else
-      PARK_LAUNCH("kmeans_assign_cand", (k_assign_cand<64, 3>), gt, dim3(256), 0, st, X,
-                  (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
-                  (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
-                  (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
-                  kb.nflag, (const double*)kf.xn, kf.dmax);
+    PARK_LAUNCH("kmeans_assign_cand", k_assign_cand<64>, gt, dim3(256), 0, st, X,
+                (const bf16_t*)kb.w3, plane, (const float*)kb.b32, Cpad, (const float*)kb.wn,
+                (const float*)kb.eb, (const float*)kb.hmax, nbm, H, N, C, NT, (const int*)kb.perm,
+                (const uint32_t*)kf.tun, (const int*)kf.talo, kb.labels, kb.flags, kb.flagu,
+                kb.nflag, (const double*)kf.xn, kf.dmax);
     PARK_LAUNCH("kmeans_refine_union", k_refine_union<64>, gt, dim3(64), 0, st, X,
                 (const bf16_t*)kb.w3, plane, (const float*)kb.b32, (const float*)kb.wn,
                 (const float*)kb.eb, Cpad, (const double*)kb.w, (const double*)kb.b,

@@ -329,8 +329,8 @@ __global__ __launch_bounds__(4 * D) void k_prep(const double* __restrict__ mu,
 //
 // For a bf16 point x the score s_v = b_v - 2 x.w_v is evaluated with w_v
 // split into NP bf16 parts, w = w1 + w2 (+ w3) + r, with |r| <= 2^-16 (1.01)
-// |w| for two parts and 2^-24 (1 + 2^-7)|w| for three.  All products are
-// bf16 x bf16, exact in float.  With delta = 2^-23 per addition inside an
+// |w| for two parts (here) and 2^-24 (1 + 2^-7)|w| for three (the refinement).
+// All products are bf16 x bf16, exact in float.  With delta = 2^-23 per addition inside an
 // MFMA (any faithful rounding) and 2^-24 for a VALU rounding, the forward
 // error of t^ = x.w is at most
 //   et sum_a |x_a w_a|,  et = er 1.01 + (D+1) delta (1 + 2^-7)
@@ -340,9 +340,12 @@ __global__ __launch_bounds__(4 * D) void k_prep(const double* __restrict__ mu,
 // v_mfma_f32_32x32x16_bf16 added once, and (the fast path) the smaller parts'
 // chain continued by the D products of x.w1, whose partial sums are then at
 // most (1 + 2^-8 1.01)(1 + 2^-7) sum_a |x_a w_a|, i.e. D delta (1.012) in
-// place of (D+1) delta (1 + 2^-7) + 2^-24 1.01.  Two parts take 2/3 of the MFMA work and
-// double the bound; they pay off when the centroid count makes the pass
-// MFMA-bound (C >= 512), three parts otherwise.
+// place of (D+1) delta (1 + 2^-7) + 2^-24 1.01.  Two parts take 2/3 of the MFMA
+// work of three and double the bound, half of which is the additions' share
+// either way; the tokens that leaves uncertified cost the refinement less than
+// the third part did at any size (8 x 16384, d = 128, C = 256: 28.5 -> 21.5 us
+// and the refinement 20 us as before; 12 x 17019, d = 64, C = 266: 32.6 -> 28.8
+// and 13.3 -> 14.1 us),
 // and with sum_a |x_a w_a| <= |x| |w_v|, the float roundings of b_v and of
 // the score, and |s^_v| <= |b_v| + 2.01 |x| |w_v|:
 //   |s^_v - s_v| <= E_v = Kx |w_v| + eb_v,
@@ -393,7 +396,7 @@ __device__ __forceinline__ void km_wait_vmcnt() {
 #define PARK_KM_NS 3
 #endif
 
-template <int D, int NP>
+template <int D>
 __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict__ X,
                                                      const bf16_t* __restrict__ w3, size_t plane,
                                                      const float* __restrict__ b32, int Cpad,
@@ -405,13 +408,12 @@ __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict
                                                      int* __restrict__ flags,
                                                      float* __restrict__ flagu,
                                                      int* __restrict__ nflag) {
-  constexpr int TB = PARK_KM_TB, CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
+  constexpr int NP = 2, TB = PARK_KM_TB, CT = 32, KS = D / 16, CPR = D / 8, RPI = 64 / CPR;
   constexpr int NI = NP * CT / (4 * RPI);  // DMAs per wavefront and tile
-  static_assert(NI * 4 * RPI == NP * CT && (NP == 2 || NP == 3), "tile shape");
+  static_assert(NI * 4 * RPI == NP * CT, "tile shape");
   static_assert(kmeans_tile == 128 * TB, "tile tokens");
   constexpr float U24 = 5.9604645e-08f, DEL = 1.1920929e-07f;
-  // residual of the split: 2^-16 (two parts) or 2^-24 (three parts), relative
-  constexpr float ER = NP == 2 ? 1.52587891e-05f : U24;
+  constexpr float ER = 1.52587891e-05f;  // residual of the split: 2^-16, relative
   constexpr float ET = ER * 1.01f + (D + 1) * DEL * 1.0079f +
                        0.00390625f * 1.01f * ((NP - 1) * D + 1) * DEL + U24 * 1.01f;
   constexpr float KXC = 1.1f * (2.0f * ET + 2.01f * U24) * 1.0001f;
@@ -520,7 +522,6 @@ __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict
     const int slot = t % NS;
     const bf16_t* W1 = &Wt[slot][0];
     const bf16_t* W2 = W1 + CT * D;
-    const bf16_t* W3 = W2 + CT * D;  // third part (NP == 3)
     // the small parts first, then the leading part on top of them (one
     // accumulator, no separate addition of the two sums)
 #pragma unroll
@@ -531,14 +532,9 @@ __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict
     for (int s = 0; s < KS; ++s) {
       const int co = rowo + 8 * ((2 * s + hf) ^ swk);
       const bf16x8_t a2 = *(const bf16x8_t*)(W2 + co);
-      bf16x8_t a3;
-      if constexpr (NP == 3) a3 = *(const bf16x8_t*)(W3 + co);
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
+      for (int tb = 0; tb < TB; ++tb)
         a[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, xf[tb][s], a[tb], 0, 0, 0);
-        if constexpr (NP == 3)
-          a[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, xf[tb][s], a[tb], 0, 0, 0);
-      }
     }
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -1457,13 +1453,8 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     if constexpr (fast) {
       if (filt && t > 0)
         PARK_TRY(launch_kfilter_round((const bf16_t*)X, H, N, D, C, kb, *kb.kf, rmode == 1, st));
-      else if (C >= 512)
-        PARK_LAUNCH("kmeans_assign_fast", (k_assign_fast<D, 2>), dim3((N + kmeans_tile - 1) / kmeans_tile, H),
-                    dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
-                    (const float*)kb.b32, kmeans_cpad(C), (const float*)kb.wn, (const float*)kb.eb,
-                    (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, kb.flagu, kb.nflag);
       else
-        PARK_LAUNCH("kmeans_assign_fast", (k_assign_fast<D, 3>), dim3((N + kmeans_tile - 1) / kmeans_tile, H),
+        PARK_LAUNCH("kmeans_assign_fast", k_assign_fast<D>, dim3((N + kmeans_tile - 1) / kmeans_tile, H),
                     dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
                     (const float*)kb.b32, kmeans_cpad(C), (const float*)kb.wn, (const float*)kb.eb,
                     (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, kb.flagu, kb.nflag);

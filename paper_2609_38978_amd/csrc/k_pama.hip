@@ -567,6 +567,36 @@ __device__ int wg1024_exclusive(int x, int* tmp, int& total) {
   return pre + inc - x;
 }
 
+// Three such scans behind one pair of barriers; `tmp` needs 3 x 16 ints.
+__device__ void wg1024_exclusive3(int (&x)[3], int (&tmp)[3][16], int (&total)[3]) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  int inc[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    inc[k] = x[k];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(inc[k], o, 64);
+      if (lane >= o) inc[k] += y;
+    }
+    if (lane == 63) tmp[k][wid] = inc[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    int pre = 0;
+    total[k] = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int t = tmp[k][v];
+      if (v < wid) pre += t;
+      total[k] += t;
+    }
+    x[k] = pre + inc[k] - x[k];
+  }
+  __syncthreads();  // tmp is free for the next scan
+}
+
 // Work list of the float64 pass over the listed rows.  Each row is cut into
 // items of m chunks of 64 queries, m the smallest power of two for which the
 // extra partial-sum rows (one per item after the first of a row) fit in
@@ -574,7 +604,10 @@ __device__ int wg1024_exclusive(int x, int* tmp, int& total) {
 // first chunk, end chunk, slot}: slot -1 finishes the row, -2 leaves the raw
 // column sums in the row's W64 slot, s >= 0 in part[s].  srows[j] = {h CQ +
 // u, first part slot, number of part slots, n_u} for every split row, in row
-// order.  cnt = {items, split rows, queue head, 0}.  One workgroup.
+// order.  cnt = {items, split rows, queue head, 0}.  One workgroup, bounded by
+// its chain of dependent loads and barriers: up to 1024 rows are looked up once
+// and kept for the second pass, and the three scans of a step share their
+// barriers (20 -> 15 us at 5 heads of 137 blocks, 41 -> 35 us at 24 x 1861).
 __global__ __launch_bounds__(1024) void k_p64_plan(const int* __restrict__ q_offsets,
                                                    const int* __restrict__ rows,
                                                    const int* __restrict__ nrows, int H, int N,
@@ -582,7 +615,7 @@ __global__ __launch_bounds__(1024) void k_p64_plan(const int* __restrict__ q_off
                                                    int4* __restrict__ srows, int* __restrict__ cnt) {
   constexpr int NM = 16;    // candidate m = 1, 2, 4, ..., 2^15
   constexpr int HG = 4096;  // heads per group (the listed rows are walked group by group)
-  __shared__ int tmp[16];
+  __shared__ int tmp[16], tmp3[3][16];
   __shared__ long long red[16][NM];
   __shared__ int hp[HG + 1];
   __shared__ int m_s;
@@ -623,12 +656,13 @@ __global__ __launch_bounds__(1024) void k_p64_plan(const int* __restrict__ q_off
   long long e[NM];
 #pragma unroll
   for (int j = 0; j < NM; ++j) e[j] = 0;
+  int h = 0, u = -1, nu = 0, U = 0;  // (after the loop: this thread's last row)
   for (int h0 = 0; h0 < H; h0 += HG) {
     const int nh = min(HG, H - h0);
-    const int U = head_prefix(h0, nh);
+    U = head_prefix(h0, nh);
     for (int j = tid; j < U; j += 1024) {
-      int h, u;
-      const int nch = (row_at(h0, nh, j, h, u) + 63) >> 6;
+      nu = row_at(h0, nh, j, h, u);
+      const int nch = (nu + 63) >> 6;
 #pragma unroll
       for (int k = 0; k < NM; ++k) e[k] += nch > 0 ? ((nch - 1) >> k) : 0;
     }
@@ -652,28 +686,30 @@ __global__ __launch_bounds__(1024) void k_p64_plan(const int* __restrict__ q_off
   }
   __syncthreads();
   const int m = m_s;
+  const bool once = H <= HG && U <= 1024;  // every row is still at hand
   int ib = 0, sb = 0, rb = 0;  // items, part slots and split rows so far (uniform)
   for (int h0 = 0; h0 < H; h0 += HG) {
     const int nh = min(HG, H - h0);
-    const int U = head_prefix(h0, nh);
+    if (!once) U = head_prefix(h0, nh);
     for (int j0 = 0; j0 < U; j0 += 1024) {
-      int h = 0, u = -1, nu = 0;
-      if (j0 + tid < U) nu = row_at(h0, nh, j0 + tid, h, u);
+      if (!once) {
+        h = nu = 0;
+        u = -1;
+        if (j0 + tid < U) nu = row_at(h0, nh, j0 + tid, h, u);
+      }
       const int nch = (nu + 63) >> 6;
       const int ns = u < 0 ? 0 : (nch > 0 ? (nch - 1) / m + 1 : 1);
-      int t1, t2, t3;
-      const int x1 = wg1024_exclusive(ns, tmp, t1);
-      const int x2 = wg1024_exclusive(ns > 1 ? ns - 1 : 0, tmp, t2);
-      const int x3 = wg1024_exclusive(ns > 1 ? 1 : 0, tmp, t3);
+      int x[3] = {ns, ns > 1 ? ns - 1 : 0, ns > 1 ? 1 : 0}, tot[3];
+      wg1024_exclusive3(x, tmp3, tot);
       const int rid = h * CQ + u;
       for (int k = 0; k < ns; ++k) {
-        const int sl = ns == 1 ? -1 : (k == 0 ? -2 : sb + x2 + k - 1);
-        items[ib + x1 + k] = make_int4(rid, k * m, k + 1 < ns ? (k + 1) * m : nch, sl);
+        const int sl = ns == 1 ? -1 : (k == 0 ? -2 : sb + x[1] + k - 1);
+        items[ib + x[0] + k] = make_int4(rid, k * m, k + 1 < ns ? (k + 1) * m : nch, sl);
       }
-      if (ns > 1) srows[rb + x3] = make_int4(rid, sb + x2, ns - 1, nu);
-      ib += t1;
-      sb += t2;
-      rb += t3;
+      if (ns > 1) srows[rb + x[2]] = make_int4(rid, sb + x[1], ns - 1, nu);
+      ib += tot[0];
+      sb += tot[1];
+      rb += tot[2];
     }
   }
   if (tid == 0) {
@@ -1182,11 +1218,13 @@ __global__ __launch_bounds__(1024) void k_pama_plan(const int* __restrict__ q_of
                                                     int CQ, int icap, int4* __restrict__ items,
                                                     int* __restrict__ nitem,
                                                     int* __restrict__ pstart,
-                                                    float* __restrict__ delta) {
+                                                    float* __restrict__ delta,
+                                                    int* __restrict__ nrows) {
   __shared__ int st[MAXC + 1];
   __shared__ int ps[MAXC + 1];
   const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int* off = q_offsets + (size_t)h * (CQ + 1);
+  if (tid == 0) nrows[h] = 0;  // the selection's list of uncertified rows
   // two blocks per thread: chunks, then a workgroup scan
   int c[2];
 #pragma unroll
@@ -2263,7 +2301,7 @@ park_status launch_retrieve(const void* Qp, const int* q_offsets, const float* c
   const unsigned nwg = 8u * ((((unsigned)icap + 7u) / 8u * (unsigned)H + 7u) / 8u);
   float* part = (float*)rb.W64;  // free until the float64 rows are computed
   PARK_LAUNCH("pama_plan", k_pama_plan, dim3(H), dim3(1024), 0, st, q_offsets, N, CQ, icap,
-              rb.qitems, rb.nitem, rb.qstart, rb.delta);
+              rb.qitems, rb.nitem, rb.qstart, rb.delta, rb.nrows);
   // at most FULLK_NT centroid tiles: the single-sweep (Full-K) retrieval,
   // one chunk per wavefront, four per workgroup
   const bool fullk = CK <= 32 * FULLK_NT;
@@ -2301,7 +2339,6 @@ park_status launch_retrieve(const void* Qp, const int* q_offsets, const float* c
   }
   PARK_LAUNCH("pama_combine", k_pama_combine, dim3(CQ, H), dim3(256), 0, st, q_offsets,
               (const int*)rb.qstart, H, N, CQ, CK, (const float*)part, pcap, W32, rb.delta);
-  PARK_LAUNCH("pama_reset", k_zero_counts, dim3((H + 63) / 64), dim3(64), 0, st, rb.nrows, H);
   // top-k rows the bound cannot settle are settled by their band of
   // ambiguous blocks (float64 weights of those blocks only); not when the
   // caller asked for W^ (its float64 rows are then written whole)

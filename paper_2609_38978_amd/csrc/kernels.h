@@ -107,7 +107,7 @@ struct RetrieveBufs {
   uint16_t* c2;   // [2][H][CK][D] centroids as two f16 parts
   float* nv;      // [H][CKpad]  n_v as floats, 0 past the last block
   float* tsc;     // [H][ceil(CK / 32)] inverse scale of each centroid tile
-  float* bmax;    // [H][ceil(CK/16)][2] per-block max |c_v|, |log n_v|
+  float* bmax;    // [H][ceil(CK / 32)][2] per-tile max |c_v|, n_v
   int4* qitems;   // [H][pama_icap] fast-retrieval work list (chunks of 32 queries)
   int* nitem;     // [H] items per head
   int* qstart;    // [H][CQ+1] first item of each query block

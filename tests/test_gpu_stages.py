@@ -865,6 +865,26 @@ def test_kmeans_candidate_filter_matches_oracle_and_dense(name, grid, C, side):
         assert np.array_equal(perm[h], p2) and np.array_equal(off[h], o2)
 
 
+# float32 points: assignment tiles of 32 tokens below 256 tiles of 64, of 64
+# from there on, with short last tiles and centroid tiles.
+@pytest.mark.parametrize("H,N,C,d", [(1, 33, 9, 64), (2, 1000, 65, 128), (3, 5440, 64, 64),
+                                     (4, 4033, 70, 64)])
+def test_float32_assignment_tiles(H, N, C, d):
+    T = 2
+    g = torch.Generator().manual_seed(17)
+    X = torch.randn(H, N, d, generator=g)
+    print(f"[float32 assignment {H} {N} {C} {d}]", flush=True)
+    o = P.park_cluster_keys(X.cuda(), C, T, seed=3, side=0, metric=P.PARK_METRIC_EUCLID)
+    P.park_check(o["ws"])
+    lab = o["labels"].cpu().numpy()
+    for h in range(H):
+        x = X[h].numpy().astype(np.float64)
+        res = O.cluster_queries(x, C, T, 3, h)
+        n_mis, n_bad, worst = PT.label_flips(x, res["mu"], lab[h], res["labels"])
+        print(f"  head {h}: mismatches={n_mis} not-exempt={n_bad} worst-gap={worst:.3g}", flush=True)
+        assert n_bad == 0
+
+
 # Both group sizes of the candidate kernel (many heads or few), centroid tiles
 # and tile groups cut short, the most centroids: whichever centroids the filter
 # leaves, the labels, order and offsets are those of scoring every centroid.

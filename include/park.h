@@ -237,7 +237,10 @@ park_status park_retrieve_blocks(const void* Qp, const int32_t* q_offsets, const
  *   Qp, Kp, Vp [H][N][d] dtype;  O [H][N][d] out_dtype (PARK_F32 or PARK_BF16,
  *   bf16 by round-to-nearest-even).  Rows of empty query blocks do not exist;
  *   every token is written exactly once; the rows of a query block with
- *   kv_count = 0 are written as zeros.
+ *   kv_count = 0 are written as zeros.  A key outside the selection has weight
+ *   0 whatever its (finite) score.  With bf16 inputs the exponents are formed
+ *   by one rounding to float, which holds scores up to
+ *   |q_i . k_j| log2(e) / sqrt(d) < 2^30.
  *   lse [H][N] float (may be NULL): the natural-log normaliser of each row,
  *   log sum_j exp(q_i . k_j / sqrt(d)) over the same keys, in the original
  *   token order like O (lse[h][q_perm[h][i]]); -inf for a row whose query

@@ -764,7 +764,7 @@ __global__ __launch_bounds__(2 * ATTN_R, D == 128 ? 2 : 3) void k_attn_grp(
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   bf16_t* Ks = (bf16_t*)smem;                        // [NSK][KT][D], swizzled chunks
   bf16_t* Vs = Ks + NSK * TS::ELEMS;                 // [NSV][KT][D], swizzled chunks
-  bf16_t* bias = Vs + NSV * TS::ELEMS;               // [NSK][KT][ATTN_LB]: 0 or -3.4e38
+  bf16_t* bias = Vs + NSV * TS::ELEMS;               // [NSK][KT][ATTN_LB]: 0 or -3.39e38
   int2* ut = (int2*)(bias + NSK * KT * ATTN_LB);     // [ATTN_UCAP + 1]
   uint16_t* selw = (uint16_t*)(ut + ATTN_UCAP + 1);  // [ATTN_UCAP]
   int* srow = (int*)(selw + ATTN_UCAP);              // [2 * ATTN_SEG] rows of Kp
@@ -823,12 +823,13 @@ __global__ __launch_bounds__(2 * ATTN_R, D == 128 ? 2 : 3) void k_attn_grp(
     qf[s2] = __builtin_bit_cast(bf16x8_t, raw);
   }
   const int dst = qvalid ? q_perm[(size_t)h * N + qr] : -1;
-  // one-hot of the query block (the B operand of the bias product): lanes of
-  // half hf hold blocks 8 hf .. 8 hf + 7
+  // one-hot of the query block (the B operand of the bias product), the one
+  // being 2^127, so that the product with a bias of -3.39e38 overflows to -inf
+  // (and with 0 is 0): lanes of half hf hold blocks 8 hf .. 8 hf + 7
   const int oe = (qvalid ? bq : 0) - 8 * hf;
   uint32_t ow[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) ow[k] = (oe >> 1) == k ? 0x3f80u << (16 * (oe & 1)) : 0u;
+  for (int k = 0; k < 4; ++k) ow[k] = (oe >> 1) == k ? 0x7f00u << (16 * (oe & 1)) : 0u;
   const bf16x8_t hot = __builtin_bit_cast(bf16x8_t, make_uint4(ow[0], ow[1], ow[2], ow[3]));
 
   // LDS read offsets (bytes, relative to a slot).  The swizzle only flips
@@ -845,10 +846,10 @@ __global__ __launch_bounds__(2 * ATTN_R, D == 128 ? 2 : 3) void k_attn_grp(
   const int vcol = 16 * (G & 1) + 4 * (jg & 3);
   const uint32_t vofs = vr0 * (2 * D) + 16 * ((vcol >> 3) ^ swz_v32<D>(vr0)) + 2 * (vcol & 7);
 
-  // reference maximum: at the start a bound that any real score exceeds and
-  // the score of a key the row's block did not select (S - 3.4e38) does not,
-  // so such keys have probability 0 also before the first selected one
-  constexpr float NOKEY = -1.7014118e38f;  // -2^127
+  // reference maximum: no finite score is below the start, and a key the row's
+  // block did not select has score -inf, so its probability is 0 at any (finite)
+  // reference, also before the first selected key
+  constexpr float NOKEY = -3.4028235e38f;  // -FLT_MAX
   float m = NOKEY, lpart = 0.0f, tmax = NOKEY;
   f32x16_t acc[DB];
 #pragma unroll
@@ -999,7 +1000,7 @@ __global__ __launch_bounds__(2 * ATTN_R, D == 128 ? 2 : 3) void k_attn_grp(
         lds_dma16(Vh, (uint32_t)srcv[i] * (2 * D) + 16 * (pch ^ swz_v32<D>(rr[i])), vs + 1024 * i);
     };
     // operands of tile T's scores: the K fragments, and the bias rows (key c32,
-    // blocks 8 hf ..): bias x one-hot adds 0 or -3.4e38 to a score exactly
+    // blocks 8 hf ..): bias x one-hot starts a score from 0 or -inf
     bf16x8_t kf[KS], bf;
     auto load_k = [&](int T) {
       const int sk = T % NSK;

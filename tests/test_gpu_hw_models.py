@@ -100,3 +100,30 @@ def test_mfma_bf16_chain_error_model(kind, K):
     print(f"[mfma {kind} K={K}] worst error {float(ratio.max()):.3f} x 2^-23 (|C0| + sum|ab|); "
           f"model allows {K + 1}")
     assert np.all(err <= (K + 1) * U23 * mag)
+
+
+def test_mfma_overflow_masks_scores():
+    # attention masks a key by one bf16 MFMA before its score's chain: -3.39e38
+    # (or 0) times 2^127 in the row's own column, every other column 0.  The
+    # product must overflow to -inf, the zeros must not turn into NaN, and no
+    # finite score may bring the sum back
+    rng = np.random.default_rng(5)
+    big = float(np.finfo(np.float32).max)
+    A = np.zeros((4, 32, 32), np.float32)
+    B = np.zeros((4, 32, 32), np.float32)
+    masked = rng.random((4, 32, 16)) < 0.5
+    A[:, :, :16] = np.where(masked, -(2.0 - 2.0 ** -7) * 2.0 ** 127, 0.0)
+    own = rng.integers(0, 16, (4, 32))
+    np.put_along_axis(B, own[:, :, None], 2.0 ** 127, axis=2)
+    A[:, :, 16:] = _bf16(rng.standard_normal((4, 32, 16)) * 2.0 ** rng.integers(-60, 50, (4, 32, 16)))
+    B[:, :, 16:] = _bf16(rng.standard_normal((4, 32, 16)) * 2.0 ** rng.integers(-60, 50, (4, 32, 16)))
+    A[0, :, 31], B[0, :, 31] = 2.0 ** 64, (2.0 - 2.0 ** -7) * 2.0 ** 63  # next to FLT_MAX
+    C0 = np.zeros((4, 32, 32), np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    got = P.park_probe_mfma_bf16(t(A).to(torch.bfloat16), t(B).to(torch.bfloat16),
+                                 t(C0)).cpu().numpy().astype(np.float64)
+    want = np.take_along_axis(masked, np.broadcast_to(own[:, None, :], (4, 32, 32)), axis=2)
+    exact, mag = _exact_chain(A[:, :, 16:], B[:, :, 16:], C0)
+    assert mag.max() <= big
+    assert np.all(np.isneginf(got[want]))
+    assert np.all(np.abs(got[~want] - exact[~want]) <= (17 * U23 * mag)[~want])

@@ -476,6 +476,47 @@ def test_attention_pipeline_fill_and_stream_tables(d, shape):
         assert ok, (h, worst)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["unselected", "low", "wide"])
+def test_attention_scores_near_the_float_range(d, kind):
+    # two query blocks share a key stream and each must see its own keys only,
+    # whatever the others score.  Queries of block 0 score (2 - 2^-8) 2^127 (next
+    # to FLT_MAX) on key block 1, which only block 1 selects; their own scores are
+    # ordinary, all -2^127 (in float and float64 alike: a uniform softmax), or
+    # multiples of 2^26 up to +-2^29
+    rng = np.random.default_rng(29)
+    N, CQ, CK = 96, 2, 3
+    q, k, v = (synth.bf16_round(rng.standard_normal((N, d)).astype(np.float32)) for _ in range(3))
+    qoff, koff = np.array([0, 40, N]), np.array([0, 32, 64, N])
+    rows = [np.array([0, 2]), np.array([1, 2])]
+    q[:40, :2] = 2.0 ** 64, 2.0 ** 63
+    q[40:, :2] = 2.0 ** -70
+    k[:, :2] = 0.0
+    k[32:64, :2] = (2 - 2.0 ** -7) * 2.0 ** 63, 2.0 ** 56
+    own = np.r_[0:32, 64:96]
+    if kind == "low":
+        k[own, 0] = -2.0 ** 63
+    elif kind == "wide":
+        k[own] = 0.0
+        k[own, 0] = rng.integers(-8, 9, 64) * 2.0 ** -38
+    perm = rng.permutation(N)
+    kvc = np.array([[2, 2]])
+    kvi = np.array([[[0, 2, 0], [1, 2, 0]]])
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).cuda()
+    Ot, Lt = P.park_block_sparse_attn(*(PT.to_dev(a[None], "bf16") for a in (q, k, v)),
+                                      t(qoff[None]), t(koff[None]), t(kvc), t(kvi), t(perm[None]),
+                                      CQ, CK, P.PARK_F32, want_lse=True)
+    Og, Lg = PT.np64(Ot)[0], Lt.double().cpu().numpy()[0]
+    args = (qoff, koff, rows, perm)
+    ref = O.block_sparse_attention(q, k, v, *args)
+    # a bf16 probability is off by at most 2^-8 of itself; float32 sums add far less than 1e-3
+    bound = 2.0 ** -8 * O.block_sparse_attention(q, k, np.abs(v), *args) + 1e-3
+    assert np.all(np.abs(Og - ref) <= bound), (kind, np.abs(Og - ref).max())
+    lref = O.block_sparse_lse(q, k, *args)
+    ok, worst = PT.lse_ok(Lg, lref, PT.lse_tol(q, k, *args, lref))
+    assert ok, (kind, worst)
+
+
 def test_attention_plan_selection_families():
     # query blocks drawn from a few families of nearly equal selections: the
     # plan's family of block u is the smallest v <= u with Jaccard(S_u, S_v)

@@ -1390,18 +1390,14 @@ park_status launch_segment_mean(const void* X, const int* perm, const int* offse
   return PARK_OK;
 }
 
-// PARK_KMEANS_FILTER=0 runs every assignment round dense (the same labels;
-// for timing the filter against the dense sweep)
-static bool kmeans_filter_enabled() {
-  const char* e = getenv("PARK_KMEANS_FILTER");
-  return !(e && e[0] == '0');
-}
-
-// PARK_KFILTER_EXACT_RADIUS=1 measures every round's radii with k_radius
-// instead of bounding them from the previous assignment (the same labels)
-static bool kfilter_exact_radius() {
-  const char* e = getenv("PARK_KFILTER_EXACT_RADIUS");
-  return e && e[0] == '1';
+// PARK_KMEANS_FILTER=0 runs every assignment round dense, and
+// PARK_KFILTER_EXACT_RADIUS=1 measures every round's radii with k_radius instead
+// of bounding them from the previous assignment (the same labels; for timing)
+void kmeans_options(KmeansBufs& kb) {
+  const char* f = getenv("PARK_KMEANS_FILTER");
+  const char* r = getenv("PARK_KFILTER_EXACT_RADIUS");
+  kb.filter = !(f && f[0] == '0');
+  kb.exact_radius = r && r[0] == '1';
 }
 
 // One part of the k-means: -1 the starting centroids, t in [0, T) the t-th
@@ -1421,8 +1417,7 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
   // the exact candidate filter for the rounds after the first (bf16 points),
   // where the dense sweep is MFMA-bound (C >= 512); below that the dense
   // round is a few tens of microseconds and the filter's passes cost more
-  const bool filt = fast && kb.kf != nullptr && C >= 512 && kmeans_filter_enabled();
-  const bool exact_radius = kfilter_exact_radius();
+  const bool filt = fast && kb.kf != nullptr && C >= 512 && kb.filter;
   if (part < 0) {
     if (kb.mu_init) {  // warm start: the caller's centroids (the previous recompute's means)
       PARK_LAUNCH("kmeans_warm", k_copy64, dim3((unsigned)((ncen + 255) / 256)), dim3(256), 0, st,
@@ -1443,7 +1438,7 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     const int nbm = (C + 15) / 16;
     // radii: round 1 measures them (k_radius); later rounds bound them from
     // the previous assignment's distances and the centroids' moves
-    const int rmode = !filt || t == 0 ? 0 : (t == 1 || exact_radius ? 1 : 2);
+    const int rmode = !filt || t == 0 ? 0 : (t == 1 || kb.exact_radius ? 1 : 2);
     double* r2 = filt ? kb.kf->r2 : nullptr;
     unsigned long long* dmax = filt ? kb.kf->dmax : nullptr;
     PARK_LAUNCH("kmeans_prep", k_prep<D>, dim3(nbm, H), dim3(4 * D), 0, st,

@@ -87,7 +87,13 @@ struct KmeansBufs {
   const KfilterBufs* kf = nullptr;  // candidate filter (bf16 points; null: every round dense)
   const double* mu_init = nullptr;  // [H][C][D] starting centroids (null: seeded init)
   double* mu_out = nullptr;         // [H][C][D] receives the means of the final clusters
+  // options, the same for all parts of a call: a filtered round reads what the
+  // setup and the round before it left
+  bool filter = true;         // rounds after the first by the candidate filter
+  bool exact_radius = false;  // every filtered round's radii measured
 };
+// fills the options (from the environment)
+void kmeans_options(KmeansBufs& kb);
 // One part: -1 the starting centroids, t in [0, T) round t, T the permutation
 // (parts -1 .. T in order are the whole k-means).
 park_status launch_kmeans(const void* X, const double* Gbar /* null = Euclidean */, int H, int N,

@@ -384,6 +384,7 @@ static KmeansBufs kmeans_bufs(ClusterWs& cw, int* labels, int* perm, int* offset
   kb.kf = &cw.kf;
   kb.mu_init = mu_init;
   kb.mu_out = mu_out;
+  kmeans_options(kb);
   return kb;
 }
 

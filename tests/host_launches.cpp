@@ -1,0 +1,171 @@
+// What the library enqueues, seen from the host: this program stands in for
+// the HIP runtime calls that libpark.so makes (a symbol of the executable comes
+// before the runtime's), records every kernel launch and runs no device code,
+// so no GPU is needed.  It also stands in for getenv, whose answers a check can
+// change from one read to the next.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "park.h"
+
+extern "C" char** environ;
+
+// ---------------------------------------------------------------- stand-ins
+static std::map<const void*, std::string>& kernel_names() {  // (used before main)
+  static std::map<const void*, std::string> names;
+  return names;
+}
+
+struct Launch {
+  std::string name;  // mangled kernel name
+  int device;
+  size_t lds;  // dynamic LDS bytes
+};
+static std::vector<Launch> launches;
+static std::map<std::string, std::vector<std::string>> env_script;  // answers, the last one repeated
+static std::map<std::string, int> env_reads;
+
+static struct {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t stream;
+} config;
+
+extern "C" {
+
+char* getenv(const char* name) {
+  const auto it = env_script.find(name);
+  if (it != env_script.end()) {
+    const int k = env_reads[name]++;
+    const auto& a = it->second;
+    const std::string& v = a[k < (int)a.size() ? k : (int)a.size() - 1];
+    return v.empty() ? nullptr : const_cast<char*>(v.c_str());
+  }
+  const size_t n = std::strlen(name);
+  for (char** e = environ; e && *e; ++e)
+    if (!std::strncmp(*e, name, n) && (*e)[n] == '=') return *e + n + 1;
+  return nullptr;
+}
+
+void** __hipRegisterFatBinary(const void*) {
+  static void* module;
+  return &module;
+}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*,
+                           void*, void*, int*) {
+  kernel_names()[host] = name;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void**) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  config = {grid, block, lds, stream};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* stream) {
+  *grid = config.grid;
+  *block = config.block;
+  *lds = config.lds;
+  *stream = config.stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
+  launches.push_back({kernel_names()[f], 0, lds});
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = (hipStream_t)(uintptr_t)64;
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  *e = (hipEvent_t)(uintptr_t)128;
+  return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+
+}  // extern "C"
+
+// ------------------------------------------------------------------- checks
+static int failures = 0;
+
+#define EXPECT(cond)                                                          \
+  do {                                                                        \
+    if (!(cond)) {                                                            \
+      std::fprintf(stderr, "%s:%d: failed: %s\n", __FILE__, __LINE__, #cond); \
+      ++failures;                                                             \
+    }                                                                         \
+  } while (0)
+
+static void* const FAKE = (void*)(uintptr_t)(1u << 20);  // 256-byte aligned, never read
+
+static int count(const char* kernel) {
+  int n = 0;
+  for (const Launch& l : launches) n += l.name.find(kernel) != std::string::npos;
+  return n;
+}
+
+static park_status cluster(int N, int C, int T) {
+  const park_dims d = {2, N, 128, PARK_BF16};
+  launches.clear();
+  return park_cluster_keys(FAKE, FAKE, &d, C, T, 0, 1, PARK_METRIC_QRKC, 0.05, 1e-6, 1e-12, nullptr,
+                           (int32_t*)FAKE, (int32_t*)FAKE, nullptr, nullptr, FAKE, (size_t)1 << 40,
+                           nullptr);
+}
+
+// The options of the candidate filter hold for a whole k-means: its rounds read
+// what the setup and the rounds before them left.
+static void kmeans_options() {
+  const int T = 6;
+  // the filter switched on or off between any two reads
+  for (int flip = 1; flip < 10; ++flip)
+    for (const char* first : {"", "0"}) {
+      std::vector<std::string> a(flip, first);
+      a.push_back(*first ? "" : "0");
+      env_script["PARK_KMEANS_FILTER"] = a;
+      env_reads.clear();
+      EXPECT(cluster(4096, 600, T) == PARK_OK);
+      const int setup = count("k_xnorm"), rounds = count("k_cand"), dense = count("k_assign_fast");
+      EXPECT(rounds + dense == T);
+      EXPECT(setup ? rounds == T - 1 : rounds == 0);
+    }
+  env_script.clear();
+  // the radii: of the second round only, or of all from the second on
+  for (int flip = 1; flip < 10; ++flip) {
+    std::vector<std::string> a(flip, "");
+    a.push_back("1");
+    env_script["PARK_KFILTER_EXACT_RADIUS"] = a;
+    env_reads.clear();
+    EXPECT(cluster(4096, 600, T) == PARK_OK);
+    const int radii = count("k_radius");
+    EXPECT(radii == 1 || radii == T - 1);
+  }
+  env_script.clear();
+}
+
+int main() {
+  kmeans_options();
+  if (failures) {
+    std::fprintf(stderr, "%d host check(s) failed\n", failures);
+    return 1;
+  }
+  std::printf("host launch checks passed\n");
+  return 0;
+}

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/park.h"
 
 namespace park {
@@ -77,6 +79,13 @@ park_status fail(park_status st, const char* fmt, ...);
     if (e_ != hipSuccess)                                                             \
       return ::park::fail(PARK_ERR_HIP, "%s: %s", name, hipGetErrorString(e_));       \
   } while (0)
+
+// Allows `kernel` up to `bytes` of dynamic LDS on the current device, where it
+// has not been allowed them yet: `done` (one per kernel, zero at first) has a
+// bit for each device that has.  The limit belongs to the device, so a process
+// that uses several sets it on each.
+park_status reserve_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done,
+                        const char* what);
 
 #define PARK_TRY(expr)                 \
   do {                                 \

@@ -1196,11 +1196,9 @@ static park_status attn_grp_launch(const void* Qp, const void* Kp, const void* V
                          (size_t)ATTN_KSLOTS * ATTN_LB * 32 * 2 +
                          (size_t)(ATTN_UCAP + 1) * sizeof(int2) + (size_t)ATTN_UCAP * 2 +
                          (size_t)2 * ATTN_SEG * 6;
-  static const hipError_t attr = hipFuncSetAttribute(
-      (const void*)k_attn_grp<OT, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (attr != hipSuccess)
-    return fail(PARK_ERR_HIP, "attention: cannot reserve %zu bytes of LDS", lds);
-  // 8 * ceil(items / 8) workgroups: every item owns one (see the remap in the kernel)
+  static std::atomic<uint64_t> done{0};
+  PARK_TRY(reserve_lds((const void*)k_attn_grp<OT, D>, lds, done, "attention"));
+  // one workgroup per item, rounded up to whole turns over the 8 XCDs
   const unsigned nwg = 8u * (((unsigned)H * (unsigned)GPH + 7u) / 8u);
   PARK_LAUNCH("attn_mfma", (k_attn_grp<OT, D>), dim3(nwg), dim3(2 * ATTN_R), lds, st,
               (const bf16_t*)Qp, (const bf16_t*)Kp, (const bf16_t*)Vp, qo, ko, bits, qp, order, spre,

@@ -2382,14 +2382,11 @@ static park_status pama64_launch(const char* nm, unsigned nwg, size_t lds, const
                                  float* W32, const int* bandc, const int* kv_index,
                                  const float* wfast, const float* dfast, int plist,
                                  int* status, hipStream_t st) {
-  // reserved once for the largest CK (2048), outside any stream capture that may follow
-  static const int lds_max = (int)(MAXC * (sizeof(double) + sizeof(int)));
-  static const hipError_t a1 = hipFuncSetAttribute(
-      (const void*)k_pama64<bf16_t, D, W2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-  static const hipError_t a2 = hipFuncSetAttribute(
-      (const void*)k_pama64<float, D, W2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-  if (a1 != hipSuccess || a2 != hipSuccess)
-    return fail(PARK_ERR_HIP, "retrieval: cannot reserve %zu bytes of LDS", lds);
+  // reserved for the largest CK (2048)
+  constexpr size_t lds_max = MAXC * (sizeof(double) + sizeof(int));
+  static std::atomic<uint64_t> done_bf16{0}, done_f32{0};
+  PARK_TRY(reserve_lds((const void*)k_pama64<bf16_t, D, W2>, lds_max, done_bf16, "retrieval"));
+  PARK_TRY(reserve_lds((const void*)k_pama64<float, D, W2>, lds_max, done_f32, "retrieval"));
   if (dtype == PARK_BF16)
     PARK_LAUNCH(nm, (k_pama64<bf16_t, D, W2>), dim3(nwg), dim3(256), lds, st, (const bf16_t*)Qp,
                 q_offsets, cen, k_sizes, H, N, CQ, CK, items, cnt, part, W64, W32, bandc, kv_index,

@@ -225,10 +225,9 @@ park_status launch_count_sort(const int* labels, int H, int N, int C, int* thist
     PARK_LAUNCH("sort_hist", k_sort_hist, dim3(nt, H), dim3(SORT_NT), (size_t)C * sizeof(int), st,
                 labels, N, C, tsz, thist);
   const size_t lds = (size_t)SORT_NW * ((C + 1) / 2) * 4 + (size_t)C * 4;
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)k_sort_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          SORT_NW * SORT_MAXC / 2 * 4 + SORT_MAXC * 4);
-  if (attr != hipSuccess) return fail(PARK_ERR_HIP, "sort: cannot reserve %zu bytes of LDS", lds);
+  static std::atomic<uint64_t> done{0};
+  PARK_TRY(reserve_lds((const void*)k_sort_scatter, SORT_NW * SORT_MAXC / 2 * 4 + SORT_MAXC * 4,
+                       done, "sort"));
   PARK_LAUNCH("sort_scatter", k_sort_scatter, dim3(nt, H), dim3(SORT_NT), lds, st, labels, N, C,
               nbits, tsz, (const int*)(nt > 1 ? thist : nullptr), perm, offsets);
   return PARK_OK;

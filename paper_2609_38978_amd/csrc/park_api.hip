@@ -74,6 +74,23 @@ park_status launch_clear_status(int* status, hipStream_t st) {
   return PARK_OK;
 }
 
+park_status reserve_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done,
+                        const char* what) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  const uint64_t bit = e == hipSuccess && dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+  if (done.load(std::memory_order_relaxed) & bit) return PARK_OK;
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // (reported here, not by the next launch)
+    return fail(PARK_ERR_HIP, "%s: cannot reserve %zu bytes of LDS: %s", what, bytes,
+                hipGetErrorString(e));
+  }
+  done.fetch_or(bit, std::memory_order_relaxed);
+  return PARK_OK;
+}
+
 // ------------------------------------------------------------ validation
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 

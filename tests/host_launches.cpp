@@ -10,6 +10,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "park.h"
@@ -24,12 +25,14 @@ static std::map<const void*, std::string>& kernel_names() {  // (used before mai
 
 struct Launch {
   std::string name;  // mangled kernel name
-  int device;
-  size_t lds;  // dynamic LDS bytes
+  bool lds_ok;       // its dynamic LDS is within 64 KB or what this device was told
 };
 static std::vector<Launch> launches;
 static std::map<std::string, std::vector<std::string>> env_script;  // answers, the last one repeated
 static std::map<std::string, int> env_reads;
+static int device = 0;
+static int attribute_failures = 0;  // hipFuncSetAttribute calls that will fail
+static std::map<std::pair<int, const void*>, size_t> lds_allowed;  // per device and kernel
 
 static struct {
   dim3 grid, block;
@@ -75,15 +78,21 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
-  launches.push_back({kernel_names()[f], 0, lds});
+  const auto it = lds_allowed.find({device, f});
+  launches.push_back({kernel_names()[f], lds <= (it == lds_allowed.end() ? 65536u : it->second)});
   return hipSuccess;
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipGetDevice(int* d) {
-  *d = 0;
+  *d = device;
   return hipSuccess;
 }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int bytes) {
+  if (attribute_failures > 0) return --attribute_failures, hipErrorUnknown;
+  lds_allowed[{device, f}] = bytes;
+  return hipSuccess;
+}
+const char* hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
   *s = hipStreamCaptureStatusNone;
   return hipSuccess;
@@ -160,7 +169,43 @@ static void kmeans_options() {
   env_script.clear();
 }
 
+static park_status attention(int dtype, int d) {
+  const park_dims dims = {1, 4096, d, dtype};
+  launches.clear();
+  return park_block_sparse_attn(FAKE, FAKE, FAKE, (int32_t*)FAKE, (int32_t*)FAKE, (int32_t*)FAKE,
+                                (int32_t*)FAKE, (int32_t*)FAKE, &dims, 64, 2048, FAKE, PARK_F32,
+                                nullptr, FAKE, (size_t)1 << 40, nullptr);
+}
+
+// A kernel with more than 64 KB of dynamic LDS is allowed it on every device it
+// runs on, and a failure to allow it is no answer for later calls.
+static void lds_reservations() {
+  auto all_ok = [] {
+    for (const Launch& l : launches)
+      if (!l.lds_ok) {
+        std::fprintf(stderr, "device %d: %s\n", device, l.name.c_str());
+        return false;
+      }
+    return true;
+  };
+  lds_allowed.clear();
+  for (device = 0; device < 3; ++device) {
+    attribute_failures = 1;
+    EXPECT(cluster(4096, 2048, 2) == PARK_ERR_HIP);
+    EXPECT(attribute_failures == 0);
+    EXPECT(cluster(4096, 2048, 2) == PARK_OK && all_ok());
+    for (int d : {64, 128}) {
+      attribute_failures = 1;
+      EXPECT(attention(PARK_BF16, d) == PARK_ERR_HIP);
+      EXPECT(attention(PARK_BF16, d) == PARK_OK && all_ok());
+    }
+    EXPECT(attention(PARK_F32, 128) == PARK_OK && all_ok());
+  }
+  device = 0;
+}
+
 int main() {
+  lds_reservations();
   kmeans_options();
   if (failures) {
     std::fprintf(stderr, "%d host check(s) failed\n", failures);

@@ -316,13 +316,17 @@ park_status park_schedule_step(int32_t step, const int32_t* steps, int32_t n_ste
  *     and attention kernels use;  x, y [n] float, n >= 0.
  *   park_probe_mfma_bf16: for each of nprob problems, C = C0 + A B as a chain
  *     of K/16 v_mfma_f32_32x32x16_bf16 in increasing k (the score chains of
- *     the k-means and PAMA kernels);  A [nprob][32][K] and Bt [nprob][32][K]
- *     bf16 (Bt holds the columns of B), C0, C [nprob][32][32] float;  K a
- *     positive multiple of 16, at most 4096.
+ *     the k-means);  A [nprob][32][K] and Bt [nprob][32][K] bf16 (Bt holds the
+ *     columns of B), C0, C [nprob][32][32] float;  K a positive multiple of 16,
+ *     at most 4096.
+ *   park_probe_mfma_f16: the same with v_mfma_f32_32x32x16_f16 and f16 operands
+ *     (the score chains of PAMA).
  * PARK_ERR_INVALID_ARG for a null or misaligned pointer or a bad size. */
 park_status park_probe_exp2(const float* x, float* y, int64_t n, void* stream);
 park_status park_probe_mfma_bf16(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
                                  int32_t nprob, int32_t K, void* stream);
+park_status park_probe_mfma_f16(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
+                                int32_t nprob, int32_t K, void* stream);
 
 /* Synchronises `stream`, returns the sticky device status recorded in the
  * workspace `ws` (PARK_OK or PARK_ERR_NUMERIC) and clears it. */

@@ -171,8 +171,8 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
 
 // k_probe.hip ---------------------------------------------------------------
 park_status launch_probe_exp2(const float* x, float* y, long n, hipStream_t st);
-park_status launch_probe_mfma(const bf16_t* A, const bf16_t* Bt, const float* C0, float* C,
-                              int nprob, int K, hipStream_t st);
+park_status launch_probe_mfma(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
+                              int nprob, int K, bool f16, hipStream_t st);
 
 // misc ----------------------------------------------------------------------
 park_status launch_clear_status(int* status, hipStream_t st);

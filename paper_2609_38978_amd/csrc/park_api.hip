@@ -821,8 +821,8 @@ park_status park_probe_exp2(const float* x, float* y, int64_t n, void* stream) {
   return launch_probe_exp2(x, y, (long)n, (hipStream_t)stream);
 }
 
-park_status park_probe_mfma_bf16(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
-                                 int32_t nprob, int32_t K, void* stream) {
+static park_status probe_mfma(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
+                              int32_t nprob, int32_t K, bool f16, void* stream) {
   g_err[0] = 0;
   if (nprob < 0) return fail(PARK_ERR_INVALID_ARG, "nprob = %d", nprob);
   if (K < 16 || K > 4096 || K % 16)
@@ -833,7 +833,17 @@ park_status park_probe_mfma_bf16(const uint16_t* A, const uint16_t* Bt, const fl
     PARK_TRY(check_ptr(C0, "C0"));
     PARK_TRY(check_ptr(C, "C"));
   }
-  return launch_probe_mfma(A, Bt, C0, C, nprob, K, (hipStream_t)stream);
+  return launch_probe_mfma(A, Bt, C0, C, nprob, K, f16, (hipStream_t)stream);
+}
+
+park_status park_probe_mfma_bf16(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
+                                 int32_t nprob, int32_t K, void* stream) {
+  return probe_mfma(A, Bt, C0, C, nprob, K, false, stream);
+}
+
+park_status park_probe_mfma_f16(const uint16_t* A, const uint16_t* Bt, const float* C0, float* C,
+                                int32_t nprob, int32_t K, void* stream) {
+  return probe_mfma(A, Bt, C0, C, nprob, K, true, stream);
 }
 
 park_status park_check(void* ws, void* stream) {

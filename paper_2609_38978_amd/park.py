@@ -32,7 +32,7 @@ EXPORTS = (
     "park_retrieve_blocks", "park_block_sparse_attn", "park_forward", "park_check",
     "park_status_string", "park_last_error", "park_profile_enable", "park_profile_reset",
     "park_profile_read", "park_schedule_step", "park_state_sizes", "park_probe_exp2",
-    "park_probe_mfma_bf16", "park_block_sparse_attn_static",
+    "park_probe_mfma_bf16", "park_probe_mfma_f16", "park_block_sparse_attn_static",
 )
 
 
@@ -90,6 +90,7 @@ def lib():
         "park_check": [vp, vp],
         "park_probe_exp2": [vp, vp, C.c_int64, vp],
         "park_probe_mfma_bf16": [vp, vp, vp, vp, i32, i32, vp],
+        "park_probe_mfma_f16": [vp, vp, vp, vp, i32, i32, vp],
         "park_schedule_step": [i32, C.POINTER(C.c_int32), i32, C.POINTER(C.c_int32)],
         "park_status_string": [i32],
         "park_last_error": [],
@@ -316,13 +317,21 @@ def park_probe_exp2(x):
     return y
 
 
-def park_probe_mfma_bf16(A, Bt, C0):
-    """C0 + A Bt^T by a chain of 32x32x16 bf16 MFMAs (A, Bt: [P, 32, K] bf16, C0: [P, 32, 32])."""
+def _probe_mfma(fn, A, Bt, C0):
     A, Bt, C0 = A.contiguous(), Bt.contiguous(), C0.contiguous()
     out = torch.empty_like(C0)
-    _check(lib().park_probe_mfma_bf16(_ptr(A), _ptr(Bt), _ptr(C0), _ptr(out), A.shape[0],
-                                      A.shape[2], _stream()))
+    _check(fn(_ptr(A), _ptr(Bt), _ptr(C0), _ptr(out), A.shape[0], A.shape[2], _stream()))
     return out
+
+
+def park_probe_mfma_bf16(A, Bt, C0):
+    """C0 + A Bt^T by a chain of 32x32x16 bf16 MFMAs (A, Bt: [P, 32, K] bf16, C0: [P, 32, 32])."""
+    return _probe_mfma(lib().park_probe_mfma_bf16, A, Bt, C0)
+
+
+def park_probe_mfma_f16(A, Bt, C0):
+    """The same by 32x32x16 f16 MFMAs (A, Bt: [P, 32, K] f16)."""
+    return _probe_mfma(lib().park_probe_mfma_f16, A, Bt, C0)
 
 
 def park_check(ws):

@@ -190,3 +190,6 @@ def test_probe_argument_errors():
         assert L.park_probe_mfma_bf16(FAKE, FAKE, FAKE, FAKE, 1, K, None) == P.PARK_ERR_INVALID_ARG
     assert L.park_probe_mfma_bf16(FAKE, FAKE, FAKE + 8, FAKE, 1, 32, None) == P.PARK_ERR_INVALID_ARG
     assert L.park_probe_mfma_bf16(FAKE, FAKE, FAKE, FAKE, -1, 32, None) == P.PARK_ERR_INVALID_ARG
+    for K in (0, 8, 24, 4112):
+        assert L.park_probe_mfma_f16(FAKE, FAKE, FAKE, FAKE, 1, K, None) == P.PARK_ERR_INVALID_ARG
+    assert L.park_probe_mfma_f16(None, FAKE, FAKE, FAKE, 1, 32, None) == P.PARK_ERR_INVALID_ARG

@@ -1040,8 +1040,8 @@ __global__ __launch_bounds__(256) void k_refine_cand(const bf16_t* __restrict__ 
 }
 
 // Float64 assignment of the listed tokens against every centroid, on
-// v_mfma_f64_16x16x4_f64: the tokens the fast pass could not certify when the
-// head has few centroids of 64 dimensions.  A workgroup takes 16 listed
+// v_mfma_f64_16x16x4_f64: the tokens the fast pass could not certify when there
+// are few tokens and few centroids of 64 dimensions.  A workgroup takes 16 listed
 // tokens, wavefront w the 16-centroid tiles w, w + 8, ...; lane l holds the
 // scores of token l % 16, so each keeps a running minimum (ties to the lowest
 // id) and the lanes and wavefronts are merged at the end.
@@ -1052,6 +1052,17 @@ __global__ __launch_bounds__(256) void k_refine_cand(const bf16_t* __restrict__ 
 // chain list, tokens, ring of tiles, candidates; this 13.5 us.  At d = 128 the
 // float64 tiles cost twice as much and the sweep is the better one (8 x 16384,
 // C = 256: 20.1 us against 26.1).
+//
+// Its work grows with the listed tokens times all centroids, so the sweep also
+// wins on larger layers (us a round, this : the sweep, d = 64):
+//   1 x 4032, C = 64    6.3 :  7.2     16 x 32148, C = 504   30.5 : 22.9
+//  12 x 16830, C = 133 11.6 : 15.3     24 x 29970, C = 133   20.1 : 15.2
+//  12 x 16830, C = 511 20.6 : 23.7     40 x 64521, C = 325  113.5 : 32.1
+//   1 x 118260, C = 500 15.9 : 24.0     3 x 118260, C = 500  30.6 : 25.5
+//  12 x 23760, C = 500 23.5 : 24.3     40 x 64521, C = 64    30.0 : 13.9
+// The line at 2^18 tokens is where the two meet (285120 and 150336 tokens at
+// C = 500: 23.5 : 24.3 and 22.7 : 21.9).
+constexpr long kRefineAllTokens = 1l << 18;
 template <int D>
 __global__ __launch_bounds__(512) void k_refine_all(const bf16_t* __restrict__ X,
                                                     const double* __restrict__ w64,
@@ -1453,7 +1464,8 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
                     dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
                     (const float*)kb.b32, kmeans_cpad(C), (const float*)kb.wn, (const float*)kb.eb,
                     (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, kb.flagu, kb.nflag);
-      if (D == 64 && C < 512)  // few, short centroids: every one in float64 (see k_refine_all)
+      // few listed tokens and few, short centroids: every one in float64 (see k_refine_all)
+      if (D == 64 && C < 512 && (long)H * N <= kRefineAllTokens)
         PARK_LAUNCH("kmeans_refine64", k_refine_all<D>, dim3(std::min((N + 255) / 256, 1024), H),
                     dim3(512), 0, st, (const bf16_t*)X, (const double*)kb.w, (const double*)kb.b, N,
                     C, (const int*)kb.flags, (const int*)kb.nflag, kb.labels, status);

@@ -131,8 +131,8 @@ static int count(const char* kernel) {
   return n;
 }
 
-static park_status cluster(int N, int C, int T) {
-  const park_dims d = {2, N, 128, PARK_BF16};
+static park_status cluster(int N, int C, int T, int H = 2, int dim = 128) {
+  const park_dims d = {H, N, dim, PARK_BF16};
   launches.clear();
   return park_cluster_keys(FAKE, FAKE, &d, C, T, 0, 1, PARK_METRIC_QRKC, 0.05, 1e-6, 1e-12, nullptr,
                            (int32_t*)FAKE, (int32_t*)FAKE, nullptr, nullptr, FAKE, (size_t)1 << 40,
@@ -167,6 +167,20 @@ static void kmeans_options() {
     EXPECT(radii == 1 || radii == T - 1);
   }
   env_script.clear();
+}
+
+// The refinement against every centroid takes small clusterings of 64-dimension
+// heads only: its work grows with the listed tokens times all centroids.
+static void refine_routes() {
+  struct { int H, N, C, d, all; } cases[] = {
+      {1, 4096, 64, 64, 1},   {12, 17019, 266, 64, 1},  {8, 32768, 511, 64, 1},
+      {8, 32769, 511, 64, 0}, {24, 30000, 133, 64, 0},  {40, 64521, 64, 64, 0},
+      {1, 4096, 64, 128, 0},  {12, 17019, 512, 64, 0}};
+  for (const auto& c : cases) {
+    EXPECT(cluster(c.N, c.C, 3, c.H, c.d) == PARK_OK);
+    EXPECT(count("k_refine_all") == (c.all ? 3 : 0));
+    EXPECT(count("k_refine_cand") == (c.all ? 0 : 3));
+  }
 }
 
 static park_status attention(int dtype, int d) {
@@ -207,6 +221,7 @@ static void lds_reservations() {
 int main() {
   lds_reservations();
   kmeans_options();
+  refine_routes();
   if (failures) {
     std::fprintf(stderr, "%d host check(s) failed\n", failures);
     return 1;

@@ -146,8 +146,8 @@ __global__ void k_seed_centroids(const T* __restrict__ X, const int* __restrict_
 // Large layers are near the memory's rate (71 -> 65 us at 40 x 75600: 200 MB).
 typedef double f64x4k_t __attribute__((ext_vector_type(4)));
 
-template <int D>
-__global__ __launch_bounds__(4 * D) void k_prep(const double* __restrict__ mu,
+template <int D, int NT>
+__global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
                                               const double* __restrict__ Gbar, int C,
                                               double* __restrict__ w, double* __restrict__ b,
                                               bf16_t* __restrict__ w3,
@@ -158,12 +158,12 @@ __global__ __launch_bounds__(4 * D) void k_prep(const double* __restrict__ mu,
                                               const int* __restrict__ offsets,
                                               double* __restrict__ r2,
                                               unsigned long long* __restrict__ dmax, int rmode) {
-  constexpr int CB = 16, NT = 4 * D;
+  constexpr int CB = 16;
   __shared__ double ms[CB][D];
   __shared__ double ws[CB][D + 1];
   __shared__ float fnl[CB], fel[CB];
   const int h = blockIdx.y, v0 = blockIdx.x * CB, tid = threadIdx.x;
-  if (Gbar) {
+  if (NT == 4 * D && Gbar) {
     // operand k-index: steps 2 j and 2 j + 1 take dimensions 8 j + 2 (l / 16)
     // and the next one of both operands
     const int w16 = 16 * (tid >> 6), c = tid & 15, kq = (tid >> 4) & 3;
@@ -1452,10 +1452,19 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     const int rmode = !filt || t == 0 ? 0 : (t == 1 || kb.exact_radius ? 1 : 2);
     double* r2 = filt ? kb.kf->r2 : nullptr;
     unsigned long long* dmax = filt ? kb.kf->dmax : nullptr;
-    PARK_LAUNCH("kmeans_prep", k_prep<D>, dim3(nbm, H), dim3(4 * D), 0, st,
-                (const double*)kb.mu, Gbar, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
-                fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
-                fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax, rmode);
+    auto prep = [&](auto kernel, int nt) -> park_status {
+      PARK_LAUNCH("kmeans_prep", kernel, dim3(nbm, H), dim3(nt), 0, st, (const double*)kb.mu, Gbar,
+                  C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane, fast ? kb.b32 : nullptr,
+                  kmeans_cpad(C), fast ? kb.wn : nullptr, fast ? kb.eb : nullptr, kb.hmax, m2, mn,
+                  (const int*)kb.offsets, r2, dmax, rmode);
+      return PARK_OK;
+    };
+    // without a metric the work is elementwise: while a workgroup per CU or two
+    // holds the grid, 1024 threads shorten it (us a round, 4 D threads : 1024:
+    // 1 x 8073, d = 128, C = 128 6.1 : 5.0; 8 x 16335, C = 256 5.6 : 4.6;
+    // 12 x 16830, d = 64, C = 266 5.9 : 4.6)
+    if (!Gbar && (long)nbm * H < 512) PARK_TRY(prep(k_prep<D, 1024>, 1024));
+    else PARK_TRY(prep(k_prep<D, 4 * D>, 4 * D));
     if constexpr (fast) {
       if (filt && t > 0)
         PARK_TRY(launch_kfilter_round((const bf16_t*)X, H, N, D, C, kb, *kb.kf, rmode == 1, st));

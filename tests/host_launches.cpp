@@ -131,10 +131,11 @@ static int count(const char* kernel) {
   return n;
 }
 
-static park_status cluster(int N, int C, int T, int H = 2, int dim = 128) {
+static park_status cluster(int N, int C, int T, int H = 2, int dim = 128,
+                           int metric = PARK_METRIC_QRKC) {
   const park_dims d = {H, N, dim, PARK_BF16};
   launches.clear();
-  return park_cluster_keys(FAKE, FAKE, &d, C, T, 0, 1, PARK_METRIC_QRKC, 0.05, 1e-6, 1e-12, nullptr,
+  return park_cluster_keys(FAKE, FAKE, &d, C, T, 0, 1, metric, 0.05, 1e-6, 1e-12, nullptr,
                            (int32_t*)FAKE, (int32_t*)FAKE, nullptr, nullptr, FAKE, (size_t)1 << 40,
                            nullptr);
 }
@@ -167,6 +168,22 @@ static void kmeans_options() {
     EXPECT(radii == 1 || radii == T - 1);
   }
   env_script.clear();
+}
+
+// Without a metric the centroids' preparation uses 1024 threads on small grids,
+// with one the four wavefronts per 64 columns that its product is laid out for.
+static void prep_routes() {
+  struct { int H, C, d, metric; const char* kernel; } cases[] = {
+      {1, 128, 128, PARK_METRIC_EUCLID, "k_prepILi128ELi1024E"},
+      {1, 128, 64, PARK_METRIC_EUCLID, "k_prepILi64ELi1024E"},
+      {32, 256, 128, PARK_METRIC_EUCLID, "k_prepILi128ELi512E"},
+      {32, 256, 64, PARK_METRIC_EUCLID, "k_prepILi64ELi256E"},
+      {1, 128, 128, PARK_METRIC_QRKC, "k_prepILi128ELi512E"},
+      {1, 128, 64, PARK_METRIC_QRKC, "k_prepILi64ELi256E"}};
+  for (const auto& c : cases) {
+    EXPECT(cluster(4096, c.C, 3, c.H, c.d, c.metric) == PARK_OK);
+    EXPECT(count("k_prep") == 3 && count(c.kernel) == 3);
+  }
 }
 
 // The refinement against every centroid takes small clusterings of 64-dimension
@@ -222,6 +239,7 @@ int main() {
   lds_reservations();
   kmeans_options();
   refine_routes();
+  prep_routes();
   if (failures) {
     std::fprintf(stderr, "%d host check(s) failed\n", failures);
     return 1;

@@ -111,12 +111,103 @@ __global__ __launch_bounds__(256) void k_copy64(const double* __restrict__ src,
   if (i < n) dst[i] = src[i];
 }
 
-template <typename T>
-__global__ void k_seed_centroids(const T* __restrict__ X, const int* __restrict__ init, int N, int D,
-                                 int C, double* __restrict__ mu) {
-  const int h = blockIdx.y, v = blockIdx.x, a = threadIdx.x;
-  const int idx = init[(size_t)h * C + v];
-  mu[((size_t)h * C + v) * D + a] = (double)to_f(X[((size_t)h * N + idx) * D + a]);
+typedef double f64x4k_t __attribute__((ext_vector_type(4)));
+
+// Reference of the fast scores: ref[h] = {w_c [D], D / 32 parts of b_c, as many of
+// |w_c|^2} with c the mean of up to 64 of the starting centroids, w_c = Gbar c
+// (or c), b_c = c . w_c.  Scores against w_v - w_c and b_v - b_c differ from
+// those against w_v and b_v by the same amount for every centroid of a token,
+// so the argmin is the same, and the error bound of the fast scores (relative to
+// |x| |w_v - w_c|) does not grow with what all tokens have in common.  Any c will
+// do; one that is not finite is replaced by zero.  Without it, tokens with a
+// common offset of four times their spread took 635 us a round to refine at
+// 24 x 29970, d = 128, C = 469 and 82 at 12 x 16830, d = 64, C = 500, with it 74
+// and 28 (at an offset of sixteen times, 7.1 ms in place of 339 for the whole
+// call of the former).
+// D / 32 workgroups of 256 threads per head, 32 columns each, once per k-means
+// (one workgroup took 9 us longer at d = 128: it reads the metric alone);
+// row(r, a): element a of centroid r.
+constexpr int ref_parts(int D) { return D / 32; }
+constexpr int ref_stride(int D) { return D + 2 * ref_parts(D); }
+template <int D, class Row>
+__device__ void write_reference(Row row, const double* Gbar, int h, int p, int C, double* ref) {
+  constexpr int R = 64, NG = 256 / D;  // groups of D threads, sharing the rows
+  constexpr int KC = D / 8;            // rows of the metric per thread (8 threads a column)
+  __shared__ double part[NG][D], cs[D], ps[8][32];
+  const int tid = threadIdx.x, a = tid % D, g = tid / D, n = min(C, R), step = C / n;
+  const int col = 32 * p + (tid & 31), q8 = tid >> 5;
+  double x[R / NG], y[KC], s = 0.0;
+#pragma unroll
+  for (int k = 0; k < R / NG; ++k) x[k] = row(min(g + NG * k, n - 1) * step, a);
+  if (Gbar) {
+#pragma unroll
+    for (int k = 0; k < KC; ++k) y[k] = Gbar[((size_t)h * D + q8 * KC + k) * D + col];
+  }
+#pragma unroll
+  for (int k = 0; k < R / NG; ++k) s += g + NG * k < n ? x[k] : 0.0;
+  part[g][a] = s;
+  __syncthreads();
+  s = 0.0;
+#pragma unroll
+  for (int q = 0; q < NG; ++q) s += part[q][a];
+  s /= n;
+  const bool ok = __syncthreads_and(isfinite(s));
+  if (g == 0) cs[a] = ok ? s : 0.0;
+  __syncthreads();
+  double t = 0.0;
+  if (Gbar) {
+#pragma unroll
+    for (int k = 0; k < KC; ++k) t = fma(y[k], cs[q8 * KC + k], t);
+  } else if (q8 == 0) {
+    t = cs[col];
+  }
+  ps[q8][tid & 31] = t;
+  __syncthreads();
+  if (tid < 64) {  // (lanes 32 .. 63 repeat the columns and add nothing to the sums)
+    double wc = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) wc += ps[q][tid & 31];
+    double b = tid < 32 ? cs[col] * wc : 0.0, n2 = tid < 32 ? wc * wc : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      b += __shfl_xor(b, o, 64);
+      n2 += __shfl_xor(n2, o, 64);
+    }
+    double* out = ref + (size_t)h * ref_stride(D);
+    if (tid < 32) out[col] = wc;
+    if (tid == 0) {
+      out[D + p] = b;
+      out[D + ref_parts(D) + p] = n2;
+    }
+  }
+}
+
+// starting centroids from the seeded tokens, 256 / D per workgroup; the first
+// workgroups of a head also write the reference
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_seed_centroids(const T* __restrict__ X,
+                                                        const int* __restrict__ init, int N, int C,
+                                                        double* __restrict__ mu,
+                                                        const double* __restrict__ Gbar,
+                                                        double* __restrict__ ref) {
+  const int h = blockIdx.y, p = blockIdx.x, a = threadIdx.x % D;
+  const int v = p * (256 / D) + threadIdx.x / D;
+  const T* Xh = X + (size_t)h * N * D;
+  const int* ih = init + (size_t)h * C;
+  if (v < C) mu[((size_t)h * C + v) * D + a] = (double)to_f(Xh[(size_t)ih[v] * D + a]);
+  if (ref && p < ref_parts(D))
+    write_reference<D>([&](int r, int e) { return (double)to_f(Xh[(size_t)ih[r] * D + e]); }, Gbar, h,
+                       p, C, ref);
+}
+
+// the reference of given starting centroids (warm start)
+template <int D>
+__global__ __launch_bounds__(256) void k_reference(const double* __restrict__ mu,
+                                                   const double* __restrict__ Gbar, int C,
+                                                   double* __restrict__ ref) {
+  const int h = blockIdx.y;
+  const double* m = mu + (size_t)h * C * D;
+  write_reference<D>([&](int r, int e) { return m[(size_t)r * D + e]; }, Gbar, h, blockIdx.x, C, ref);
 }
 
 // w_v = Gbar mu_v (or mu_v), b_v = mu_v . w_v;  16 centroids per workgroup.
@@ -124,7 +215,8 @@ __global__ void k_seed_centroids(const T* __restrict__ X, const int* __restrict_
 // applies each element to 16 / (256 / D) centroids.  When `w3` is given the
 // fast-path operands are written too: w_v split into three bf16 parts (three
 // planes of H*C*D), b_v in float, |w_v| rounded up and the |b_v| term of the
-// error bound (see k_assign_fast); `m2`/`mn` give the candidate filter the
+// error bound (see k_assign_fast); with `ref` all of these are of w_v - w_c and
+// b_v - b_c (see write_reference).  `m2`/`mn` give the candidate filter the
 // centroids in two bf16 parts and |mu_v|.
 //
 // Cluster radii for the candidate filter (rmode 2): the previous assignment
@@ -144,11 +236,10 @@ __global__ void k_seed_centroids(const T* __restrict__ X, const int* __restrict_
 // D columns that it replaces were chains of dependent batches of loads:
 // 39 -> 19 us at 3 x 119056 tokens, C = 1861; 12 -> 8 us at 8 x 16384, C = 256.
 // Large layers are near the memory's rate (71 -> 65 us at 40 x 75600: 200 MB).
-typedef double f64x4k_t __attribute__((ext_vector_type(4)));
-
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
-                                              const double* __restrict__ Gbar, int C,
+                                              const double* __restrict__ Gbar,
+                                              const double* __restrict__ ref, int C,
                                               double* __restrict__ w, double* __restrict__ b,
                                               bf16_t* __restrict__ w3,
                                               size_t plane, float* __restrict__ b32, int Cpad,
@@ -161,8 +252,10 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
   constexpr int CB = 16;
   __shared__ double ms[CB][D];
   __shared__ double ws[CB][D + 1];
+  __shared__ double rs[ref_stride(D)];  // w_c, b_c, |w_c|^2 (0 without a reference)
   __shared__ float fnl[CB], fel[CB];
   const int h = blockIdx.y, v0 = blockIdx.x * CB, tid = threadIdx.x;
+  const double rv = ref && tid < ref_stride(D) ? ref[(size_t)h * ref_stride(D) + tid] : 0.0;
   if (NT == 4 * D && Gbar) {
     // operand k-index: steps 2 j and 2 j + 1 take dimensions 8 j + 2 (l / 16)
     // and the next one of both operands
@@ -194,19 +287,21 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     ms[r][a] = m;
     if (!Gbar) ws[r][a] = m;
   }
+  if (tid < ref_stride(D)) rs[tid] = rv;
   __syncthreads();
-  // (w itself is written at the end: the radius bound reads the old w)
-  if (w3 || m2)
+  // (under rmode 2 w itself is written at the end: the radius bound reads the old w)
+  if (w3 || m2 || rmode != 2)
     for (int e = 2 * tid; e < CB * D; e += 2 * NT) {
       const int r = e / D, a = e % D;
       if (v0 + r >= C) break;
       const size_t o = ((size_t)h * C + v0 + r) * D + a;
+      if (rmode != 2) *(double2*)(w + o) = make_double2(ws[r][a], ws[r][a + 1]);
       if (w3) {
         // w = w1 + w2 + w3 + r with bf16 parts and |r| <= 2^-24 |w| (1 + 2^-7)
         uint32_t p1 = 0u, p2 = 0u, p3 = 0u;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-          const double x = ws[r][a + k];
+          const double x = ws[r][a + k] - rs[a + k];
           const bf16_t q1 = f2bf((float)x);
           const double r1 = x - (double)bf2f(q1);
           const bf16_t q2 = f2bf((float)r1);
@@ -246,7 +341,8 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     for (int j = 0; j < D / LPC; ++j) {
       const int c = sub + LPC * j;
       s = fma(ms[r][c], ws[r][c], s);
-      n2 = fma(ws[r][c], ws[r][c], n2);
+      const double u = ws[r][c] - rs[c];
+      n2 = fma(u, u, n2);
       m2s = fma(ms[r][c], ms[r][c], m2s);
       if (rmode == 2) {
         dso = fma(ms[r][c], wo[j], dso);
@@ -286,9 +382,21 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     if (sub == 0 && v0 + r < C) {
       b[(size_t)h * C + v0 + r] = s;
       if (b32) {
-        fnr = (float)(sqrt(n2) * (1.0 + 1e-6));
-        fer = (float)(fabs(s) * (2.0 * 1.1 * 5.9604644775390625e-08) * (1.0 + 1e-6));
-        b32[(size_t)h * Cpad + v0 + r] = (float)s;
+        // with a reference, a floor well above the rounding of a float64 score
+        // of w_v and b_v themselves, so that what is certified is also their
+        // float64 argmin (2^-30 of |w_v| <= |w_v - w_c| + |w_c| is 2^-44 |x| |w_v|
+        // of a bound)
+        double bc = 0.0, nc = 0.0;
+#pragma unroll
+        for (int q = 0; q < ref_parts(D); ++q) {
+          bc += rs[D + q];
+          nc += rs[D + ref_parts(D) + q];
+        }
+        const double fl = ref ? 1.0 : 0.0, sr = s - bc, un = sqrt(n2);
+        fnr = (float)((un + fl * 9.3132257e-10 * (un + sqrt(nc))) * (1.0 + 1e-6));
+        fer = (float)((fabs(sr) * (2.0 * 1.1 * 5.9604644775390625e-08) + fl * 5.6843419e-14 * fabs(s)) *
+                      (1.0 + 1e-6));
+        b32[(size_t)h * Cpad + v0 + r] = (float)sr;
         wn[(size_t)h * Cpad + v0 + r] = fnr;
         eb[(size_t)h * Cpad + v0 + r] = fer;
       }
@@ -299,11 +407,11 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     }
   }
   __syncthreads();
-  // w itself (the reduction above has read the old values)
-  for (int e = tid; e < CB * D; e += NT) {
-    const int r = e / D, a = e % D;
-    if (v0 + r < C) w[((size_t)h * C + v0 + r) * D + a] = ws[r][a];
-  }
+  if (rmode == 2)  // w itself (the reduction above has read the old values)
+    for (int e = tid; e < CB * D; e += NT) {
+      const int r = e / D, a = e % D;
+      if (v0 + r < C) w[((size_t)h * C + v0 + r) * D + a] = ws[r][a];
+    }
   float fn = tid < CB ? fnl[tid] : 0.0f, fe = tid < CB ? fel[tid] : 0.0f;
   if (b32 && blockIdx.x == gridDim.x - 1)  // padding centroids: score +inf, no error term
     for (int v = C + tid; v < Cpad; v += NT) {
@@ -327,7 +435,8 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
 // ---------------------------------------------------------------------------
 // Fast assignment on bf16 MFMA with certification.
 //
-// For a bf16 point x the score s_v = b_v - 2 x.w_v is evaluated with w_v
+// For a bf16 point x the score s_v = b_v - 2 x.w_v (of w_v - w_c and b_v - b_c
+// where there is a reference, see write_reference) is evaluated with w_v
 // split into NP bf16 parts, w = w1 + w2 (+ w3) + r, with |r| <= 2^-16 (1.01)
 // |w| for two parts (here) and 2^-24 (1 + 2^-7)|w| for three (the refinement).
 // All products are bf16 x bf16, exact in float.  With delta = 2^-23 per addition inside an
@@ -342,8 +451,8 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
 // most (1 + 2^-8 1.01)(1 + 2^-7) sum_a |x_a w_a|, i.e. D delta (1.012) in
 // place of (D+1) delta (1 + 2^-7) + 2^-24 1.01.  Two parts take 2/3 of the MFMA
 // work of three and double the bound, half of which is the additions' share
-// either way; the tokens that leaves uncertified cost the refinement less than
-// the third part did at any size (8 x 16384, d = 128, C = 256: 28.5 -> 21.5 us
+// either way; with the reference the tokens that leaves uncertified cost the
+// refinement less than the third part did (8 x 16384, d = 128, C = 256: 28.5 -> 21.5 us
 // and the refinement 20 us as before; 12 x 17019, d = 64, C = 266: 32.6 -> 28.8
 // and 13.3 -> 14.1 us),
 // and with sum_a |x_a w_a| <= |x| |w_v|, the float roundings of b_v and of
@@ -1429,14 +1538,20 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
   // where the dense sweep is MFMA-bound (C >= 512); below that the dense
   // round is a few tens of microseconds and the filter's passes cost more
   const bool filt = fast && kb.kf != nullptr && C >= 512 && kb.filter;
+  // dense rounds score against a reference (the filter's kernels read w itself)
+  double* ref = fast && !filt ? kb.ref : nullptr;
   if (part < 0) {
     if (kb.mu_init) {  // warm start: the caller's centroids (the previous recompute's means)
       PARK_LAUNCH("kmeans_warm", k_copy64, dim3((unsigned)((ncen + 255) / 256)), dim3(256), 0, st,
                   kb.mu_init, kb.mu, ncen);
+      if (ref)
+        PARK_LAUNCH("kmeans_ref", k_reference<D>, dim3(ref_parts(D), H), dim3(256), 0, st,
+                    kb.mu_init, Gbar, C, ref);
     } else {
       PARK_LAUNCH("kmeans_init", k_init_idx, dim3(H), dim3(1024), 0, st, N, C, seed, side, kb.init);
-      PARK_LAUNCH("kmeans_seed", k_seed_centroids<T>, dim3(C, H), dim3(D), 0, st, X,
-                  (const int*)kb.init, N, D, C, kb.mu);
+      PARK_LAUNCH("kmeans_seed", (k_seed_centroids<T, D>),
+                  dim3(std::max((C * D + 255) / 256, ref_parts(D)), H), dim3(256), 0, st, X,
+                  (const int*)kb.init, N, C, kb.mu, Gbar, ref);
     }
     if constexpr (fast)
       if (filt) PARK_TRY(launch_kfilter_setup((const bf16_t*)X, Gbar, H, N, D, *kb.kf, st));
@@ -1454,9 +1569,9 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     unsigned long long* dmax = filt ? kb.kf->dmax : nullptr;
     auto prep = [&](auto kernel, int nt) -> park_status {
       PARK_LAUNCH("kmeans_prep", kernel, dim3(nbm, H), dim3(nt), 0, st, (const double*)kb.mu, Gbar,
-                  C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane, fast ? kb.b32 : nullptr,
-                  kmeans_cpad(C), fast ? kb.wn : nullptr, fast ? kb.eb : nullptr, kb.hmax, m2, mn,
-                  (const int*)kb.offsets, r2, dmax, rmode);
+                  (const double*)ref, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
+                  fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
+                  fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax, rmode);
       return PARK_OK;
     };
     // without a metric the work is elementwise: while a workgroup per CU or two

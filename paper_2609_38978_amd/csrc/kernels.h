@@ -70,6 +70,7 @@ struct KmeansBufs {
   double* mu;     // [H][C][D] centroids in the input space
   double* w;      // [H][C][D] metric applied to the centroids
   double* b;      // [H][C]    mu^T w
+  double* ref;    // [H][D + D / 16] reference of the fast scores (bf16 points)
   int* labels;    // [H][N]
   int* thist;     // sort tile histograms
   int* perm;      // [H][N]

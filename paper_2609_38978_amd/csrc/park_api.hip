@@ -140,6 +140,7 @@ struct ClusterWs {
   double* mu;
   double* w;
   double* b;
+  double* ref;
   int* labels;
   int* thist;
   bf16_t* w3;
@@ -162,6 +163,7 @@ static ClusterWs carve_cluster(Carver& cv, int H, int N, int D, int C) {
   c.mu = cv.take<double>((size_t)H * C * D);
   c.w = cv.take<double>((size_t)H * C * D);
   c.b = cv.take<double>((size_t)H * C);
+  c.ref = cv.take<double>((size_t)H * (D + D / 16));
   c.labels = cv.take<int>((size_t)H * N);
   c.thist = cv.take<int>((size_t)H * C * sort_tiles(H, N, C));
   c.w3 = cv.take<bf16_t>((size_t)3 * H * C * D);
@@ -385,6 +387,7 @@ static KmeansBufs kmeans_bufs(ClusterWs& cw, int* labels, int* perm, int* offset
   kb.mu = cw.mu;
   kb.w = cw.w;
   kb.b = cw.b;
+  kb.ref = cw.ref;
   kb.labels = labels ? labels : cw.labels;
   kb.thist = cw.thist;
   kb.perm = perm;

@@ -428,6 +428,58 @@ def test_sort_tiles_and_listed_tokens(N, C):
     assert np.array_equal(off, np.concatenate([[0], np.cumsum(np.bincount(z, minlength=C))]))
 
 
+def _offset_tokens(H, N, d, offset, seed):
+    # clusters of N(0, 2^2) centres, N(0, 0.5^2) around them, and one N(0, (2 offset)^2)
+    # vector that all tokens of the layer have in common
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    c = n(H, 64, d)[:, torch.randint(64, (N,), generator=g, device="cuda")]
+    return (2 * c + 0.5 * n(H, N, d) + 2 * offset * n(1, 1, d)).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("d,H,N,C", [(64, 2, 2999, 7), (64, 2, 3000, 300), (128, 2, 2999, 64),
+                                     (128, 2, 3000, 401), (64, 3, 700, 65), (128, 1, 300, 1)])
+@pytest.mark.parametrize("offset", [1.0, 16.0, 1000.0])
+def test_kmeans_labels_of_tokens_with_a_common_offset(d, H, N, C, offset):
+    # the fast scores are taken against a reference near the offset: labels of
+    # both metrics as the oracle's, up to offsets that bf16 tokens barely survive
+    X, Qm = _offset_tokens(H, N, d, offset, 1), _offset_tokens(H, N, d, 0.0, 2)
+    x, q = PT.np64(X), PT.np64(Qm)
+    T = 3
+    for side in (0, 1):
+        kw = dict(metric=P.PARK_METRIC_EUCLID) if side == 0 else \
+            dict(metric=P.PARK_METRIC_QRKC, Qmetric=Qm)
+        r = P.park_cluster_keys(X, C, T, seed=7, side=side, **kw)
+        P.park_check(r["ws"])
+        lab = r["labels"].cpu().numpy()
+        for h in range(H):
+            ref = O.cluster_queries(x[h], C, T, 7, h) if side == 0 else \
+                O.cluster_keys(x[h], q[h], C, T, 7, h)
+            n_mis, n_bad, worst = PT.label_flips(x[h] if side == 0 else ref["Kt"], ref["mu"],
+                                                 lab[h], ref["labels"])
+            assert n_bad == 0, (side, h, n_mis, worst)
+
+
+@pytest.mark.parametrize("H,N,C,d", [(12, 16830, 266, 64), (8, 16335, 256, 128)])
+def test_kmeans_offset_does_not_flood_the_refinement(H, N, C, d):
+    # without a reference the error bound grows with the offset and most tokens
+    # are listed: 15 and 118 times the assignment's time in the refinement, 3 with it
+    X = _offset_tokens(H, N, d, 16.0, 3)
+    ws = P.workspace(X, C, C)
+    for prof in (False, True):
+        P.park_profile_reset()
+        P.park_profile_enable(prof)
+        try:
+            P.park_cluster_keys(X, C, 10, side=0, metric=P.PARK_METRIC_EUCLID, ws=ws)
+            P.park_check(ws)
+        finally:
+            P.park_profile_enable(False)
+    t = P.park_profile_read()
+    ratio = t["kmeans_refine64"]["ms"] / t["kmeans_assign_fast"]["ms"]
+    print(f"[offset tokens d={d}] refinement / assignment {ratio:.2f}")
+    assert ratio < 8.0
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("shape", ["tiles", "chunks"])
 def test_attention_pipeline_fill_and_stream_tables(d, shape):

@@ -213,8 +213,8 @@ __global__ __launch_bounds__(256) void k_reference(const double* __restrict__ mu
 // w_v = Gbar mu_v (or mu_v), b_v = mu_v . w_v;  16 centroids per workgroup.
 // Gbar is symmetric, so thread (a, group) reads column a of it coalesced and
 // applies each element to 16 / (256 / D) centroids.  When `w3` is given the
-// fast-path operands are written too: w_v split into three bf16 parts (three
-// planes of H*C*D), b_v in float, |w_v| rounded up and the |b_v| term of the
+// fast-path operands are written too: w_v split into two bf16 parts, or three
+// with `third` (planes of H*C*D), b_v in float, |w_v| rounded up and the |b_v| term of the
 // error bound (see k_assign_fast); with `ref` all of these are of w_v - w_c and
 // b_v - b_c (see write_reference).  `m2`/`mn` give the candidate filter the
 // centroids in two bf16 parts and |mu_v|.
@@ -241,8 +241,8 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
                                               const double* __restrict__ Gbar,
                                               const double* __restrict__ ref, int C,
                                               double* __restrict__ w, double* __restrict__ b,
-                                              bf16_t* __restrict__ w3,
-                                              size_t plane, float* __restrict__ b32, int Cpad,
+                                              bf16_t* __restrict__ w3, size_t plane, bool third,
+                                              float* __restrict__ b32, int Cpad,
                                               float* __restrict__ wn, float* __restrict__ eb,
                                               float* __restrict__ bmax, bf16_t* __restrict__ m2,
                                               float* __restrict__ mn,
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
         }
         *(uint32_t*)(w3 + o) = p1;
         *(uint32_t*)(w3 + o + plane) = p2;
-        *(uint32_t*)(w3 + o + 2 * plane) = p3;
+        if (third) *(uint32_t*)(w3 + o + 2 * plane) = p3;
       }
       if (m2) {  // the centroid itself in two bf16 parts (candidate filter)
         uint32_t p1 = 0u, p2 = 0u;
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict
       if (fl[tb]) {
         const int slot = base + __popcll(bal[tb] & below);
         flags[(size_t)h * N + slot] = t0 + 32 * tb + c32;
-        flagu[(size_t)h * N + slot] = ubv[tb];
+        if (flagu) flagu[(size_t)h * N + slot] = ubv[tb];
       }
       base += __popcll(bal[tb]);
     }
@@ -1567,9 +1567,12 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     const int rmode = !filt || t == 0 ? 0 : (t == 1 || kb.exact_radius ? 1 : 2);
     double* r2 = filt ? kb.kf->r2 : nullptr;
     unsigned long long* dmax = filt ? kb.kf->dmax : nullptr;
+    // few listed tokens and few, short centroids: every one in float64 (see
+    // k_refine_all), without the third parts and the score bounds of the sweep
+    const bool all = fast && D == 64 && C < 512 && (long)H * N <= kRefineAllTokens;
     auto prep = [&](auto kernel, int nt) -> park_status {
       PARK_LAUNCH("kmeans_prep", kernel, dim3(nbm, H), dim3(nt), 0, st, (const double*)kb.mu, Gbar,
-                  (const double*)ref, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane,
+                  (const double*)ref, C, kb.w, kb.b, fast ? kb.w3 : nullptr, plane, !all,
                   fast ? kb.b32 : nullptr, kmeans_cpad(C), fast ? kb.wn : nullptr,
                   fast ? kb.eb : nullptr, kb.hmax, m2, mn, (const int*)kb.offsets, r2, dmax, rmode);
       return PARK_OK;
@@ -1587,9 +1590,9 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
         PARK_LAUNCH("kmeans_assign_fast", k_assign_fast<D>, dim3((N + kmeans_tile - 1) / kmeans_tile, H),
                     dim3(256), 0, st, (const bf16_t*)X, (const bf16_t*)kb.w3, plane,
                     (const float*)kb.b32, kmeans_cpad(C), (const float*)kb.wn, (const float*)kb.eb,
-                    (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, kb.flagu, kb.nflag);
-      // few listed tokens and few, short centroids: every one in float64 (see k_refine_all)
-      if (D == 64 && C < 512 && (long)H * N <= kRefineAllTokens)
+                    (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, all ? nullptr : kb.flagu,
+                    kb.nflag);
+      if (all)
         PARK_LAUNCH("kmeans_refine64", k_refine_all<D>, dim3(std::min((N + 255) / 256, 1024), H),
                     dim3(512), 0, st, (const bf16_t*)X, (const double*)kb.w, (const double*)kb.b, N,
                     C, (const int*)kb.flags, (const int*)kb.nflag, kb.labels, status);

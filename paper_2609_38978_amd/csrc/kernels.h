@@ -77,7 +77,7 @@ struct KmeansBufs {
   int* offsets;   // [H][C+1]
   int* status;    // sticky device status word
   // fast path (bf16 points)
-  bf16_t* w3;     // [3][H][C][D] w as three bf16 parts
+  bf16_t* w3;     // [3][H][C][D] w as three bf16 parts (less the reference's)
   float* b32;     // [H][kmeans_cpad(C)], padding +inf
   float* wn;      // [H][kmeans_cpad(C)] |w_v| (rounded up), padding 0
   float* eb;      // [H][kmeans_cpad(C)] |b_v| term of the fast-path bound, padding 0

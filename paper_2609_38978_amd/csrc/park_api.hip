@@ -198,7 +198,7 @@ static RetrieveBufs carve_retrieve(Carver& cv, int H, int N, int D, int CQ, int 
   r.c2 = cv.take<uint16_t>((size_t)2 * H * CK * D);
   r.nv = cv.take<float>((size_t)H * pama_ckpad(CK));
   r.tsc = cv.take<float>((size_t)H * ((CK + 31) / 32));
-  r.bmax = cv.take<float>((size_t)2 * H * ((CK + 15) / 16));
+  r.bmax = cv.take<float>((size_t)2 * H * ((CK + 31) / 32));
   r.qitems = cv.take<int4>((size_t)H * pama_icap(N, CQ));
   r.nitem = cv.take<int>((size_t)H);
   r.qstart = cv.take<int>((size_t)H * (CQ + 1));

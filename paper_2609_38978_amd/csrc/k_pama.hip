@@ -926,15 +926,20 @@ __global__ __launch_bounds__(256) void k_select_band(const double* __restrict__ 
 // Fast PAMA on f16 MFMA (bf16 queries), with a per-row error bound.
 //
 // Centroids (float) are split into two f16 parts, c = c1 + c2 + r with
-// |r| <= 2^-22 |c|: eleven significand bits each, so two parts hold what took
-// three bf16 parts (the sweep was bound by its MFMAs and vector operations
-// together: 24 MFMAs per 32 x 32 tile, 8.78 ms at 24 x 119056 tokens,
-// C = 1861; 16 take 7.3 ms, and 4.44 -> 3.3 ms at 24 x 115200, C = 1024).  The range of f16 is met by powers of two:
-// every tile of 32 centroids is scaled so that its largest element lies in
-// [2^14, 2^15), every chunk of 32 queries likewise (a bf16 value has eight
-// bits, exact in f16), and the logit's factor takes both back.  Elements below
-// 2^-28 of the largest may lose bits or flush to zero: an error of at most
-// 2^-28 of the largest element each, 2^-28 sqrt(D) of the norm together.
+// |r| <= 2^-22 |c|: eleven significand bits each, against the eight of the bf16
+// parts, of which it took three (they held every bit of a float; two f16 parts
+// drop the last in part of the cases, far below the additions' share of the
+// bound).  The sweep was bound by its MFMAs and vector operations together: 24
+// MFMAs per 32 x 32 tile, 8.78 ms at 24 x 119056 tokens, C = 1861; 16 take 7.3
+// ms, and 4.44 -> 3.3 ms at 24 x 115200, C = 1024.
+// The range of f16 is met by powers of two: every tile of 32 centroids is scaled
+// so that its largest element lies in [2^14, 2^15), every chunk of 32 queries
+// likewise (a bf16 value has eight bits, exact in f16), and the logit's factor
+// takes both back.  Elements below 2^-28 of the largest may lose bits or flush to
+// zero (this card keeps subnormal operands; the bound does not rely on it): an
+// error of at most 2^-28 of the largest element each, 2^-28 sqrt(D) of the norm
+// together.  The scale stops at 2^120, so below 2^-106 the largest element is
+// less than that; the bound then takes 2^-105 in place of the norm.
 //   t = q.c is accumulated as q.c2 in one chain over
 // all dimensions plus q.c1 in 32-dimension segments, each a fresh
 // accumulator except the last, which starts from the finished c2 chain;
@@ -945,8 +950,8 @@ __global__ __launch_bounds__(256) void k_select_band(const double* __restrict__ 
 //        + 2^-11 1.01 (D + 32) 2^-23 + 2^-28 sqrt(D) 1.01
 // (residual r; the c1 segments and their sum; the c2 chain and the last
 // segment's 32 additions onto it; flushed centroid elements; qmax the largest
-// norm of the query's chunk: flushed query elements).  Tiles or chunks whose
-// largest element is below 2^-100 or not finite get an infinite bound.
+// norm of the query's chunk: flushed query elements).  Tiles or chunks with an
+// element that is not finite get an infinite bound.
 //
 // Softmax in base 2 with the sizes as weights: P_iv = n_v 2^(x_iv) / z_i,
 //   x_iv = t_iv f - R_i + B,  f = log2(e)/sqrt(d) and the scales' inverse,
@@ -974,20 +979,24 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 
-// power of two that brings a largest element mx (> 0, finite) into [2^14, 2^15)
+// power of two that brings a largest element mx into [2^14, 2^15), at most 2^120
+// (1 for zero and for what is not finite)
 __device__ __forceinline__ float f16_scale(float mx) {
-  const int e = (int)((__float_as_uint(mx) >> 23) & 255u) - 127;  // mx >= 2^-100: normal
+  if (!(mx > 0.0f && mx <= 3.4028235e38f)) return 1.0f;
+  const int e = (int)((__float_as_uint(mx) >> 23) & 255u) - 127;
   return __uint_as_float((uint32_t)(127 + min(14 - e, 120)) << 23);
 }
-// whether a tile or chunk with largest element mx can be scaled
-__device__ __forceinline__ bool f16_scalable(float mx) {
-  return mx >= 7.8886091e-31f && mx <= 3.4028235e38f;  // 2^-100 .. FLT_MAX
+// the norm that the bound takes for a tile or chunk with largest element mx and
+// largest norm n
+__device__ __forceinline__ float f16_norm(float mx, float n) {
+  if (!(mx <= 3.4028235e38f)) return INFINITY;
+  return mx > 0.0f && mx < 1.2325952e-32f ? fmaxf(n, 2.4651903e-32f) : n;  // 2^-106, 2^-105
 }
 
 // Splits the centroids into two f16 planes (scaled by their 32-centroid tile's
 // power of two, whose inverse goes to tsc) and records the weights n_v (0 for
 // empty blocks and the padding) and per-tile maxima of |c_v| (rounded up;
-// infinite for a tile that cannot be scaled) and n_v.  An empty block takes
+// infinite for a tile with an element that is not finite) and n_v.  An empty block takes
 // the row of the head's first nonempty one: with weight 0 it adds nothing, and
 // the largest logit is that of a block that counts.
 template <int D>
@@ -1041,7 +1050,7 @@ __global__ __launch_bounds__(256) void k_cen_prep(const float* __restrict__ cen,
   if ((tid & 63) == 0) wmax[tid >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-  const float sc = f16_scalable(mx) ? f16_scale(mx) : 1.0f;
+  const float sc = f16_scale(mx);
 #pragma unroll
   for (int e = 0; e < EPT; ++e) ss = fmaf(x[e] * sc, x[e] * sc, ss);  // (squares in range)
   part[r][j] = ss;
@@ -1085,8 +1094,7 @@ __global__ __launch_bounds__(256) void k_cen_prep(const float* __restrict__ cen,
       fl = fmaxf(fl, __shfl_xor(fl, w, 64));
     }
     if (tid == 0) {
-      if (mx > 0.0f && !f16_scalable(mx)) fn = INFINITY;
-      bmax[((size_t)h * gridDim.x + blockIdx.x) * 2] = fn;
+      bmax[((size_t)h * gridDim.x + blockIdx.x) * 2] = f16_norm(mx, fn);
       bmax[((size_t)h * gridDim.x + blockIdx.x) * 2 + 1] = fl;
       tsc[(size_t)h * gridDim.x + blockIdx.x] = 1.0f / sc;
     }
@@ -1096,7 +1104,7 @@ __global__ __launch_bounds__(256) void k_cen_prep(const float* __restrict__ cen,
 // A chunk of queries as f16 operands: the lane's bf16 fragments (query c32,
 // dims 16 s + 8 hf ..) scaled by one power of two for the 64 lanes' 32 queries.
 // inv: its inverse; qn: the query's norm rounded up; qmax: the chunk's largest
-// (infinite when the chunk cannot be scaled).
+// (infinite when an element is not finite).
 template <int KS>
 __device__ __forceinline__ void f16_queries(const uint4 (&raw)[KS], f16x8_t (&qf)[KS], float& inv,
                                             float& qn, float& qmax) {
@@ -1115,7 +1123,7 @@ __device__ __forceinline__ void f16_queries(const uint4 (&raw)[KS], f16x8_t (&qf
   if (!fin) mx = INFINITY;
 #pragma unroll
   for (int w = 32; w > 0; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w, 64));
-  const float sc = f16_scalable(mx) ? f16_scale(mx) : 1.0f;
+  const float sc = f16_scale(mx);
   inv = 1.0f / sc;
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
@@ -1133,7 +1141,7 @@ __device__ __forceinline__ void f16_queries(const uint4 (&raw)[KS], f16x8_t (&qf
   qmax = qn;
 #pragma unroll
   for (int w = 16; w > 0; w >>= 1) qmax = fmaxf(qmax, __shfl_xor(qmax, w, 64));
-  if (mx > 0.0f && !f16_scalable(mx)) qmax = INFINITY;
+  qmax = f16_norm(mx, qmax);
 }
 
 // The relative error bound of one query's probabilities (see above).

@@ -199,6 +199,38 @@ def test_retrieval_operand_ranges(d, CK, qexp, kexp):
                                     b[0].cpu().numpy())[1] == 0
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("CK", [96, 300])
+@pytest.mark.parametrize("exp", [-99, -104, -108, -125, -145])
+def test_retrieval_tiny_centroid_tile_and_query_chunk(d, CK, exp):
+    # one tile of 32 centroids and one chunk of queries far below the others (down
+    # to subnormal floats) must not send the rest of the head to the float64 pass:
+    # its rows are float64 values rounded once, those of the fast pass are not
+    rng = np.random.default_rng(2000 + d + CK - exp)
+    N, CQ = 1500, 20
+    off = np.concatenate([[0, 40], np.sort(rng.choice(np.arange(41, N), CQ - 2, False)), [N]])
+    Qp = 1.5 * rng.standard_normal((N, d))
+    c = 1.5 * rng.standard_normal((CK, d))
+    Qp[:40] *= 2.0 ** max(exp, -125)
+    c[32:64] *= 2.0 ** exp
+    Qp = synth.bf16_round(Qp.astype(np.float32))
+    c = c.astype(np.float32)
+    n = rng.integers(1, 40, CK)
+    W = O.pama(Qp, off, c, n)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)[None]).cuda()
+    kc, ki, Wg = P.park_retrieve_blocks(PT.to_dev(Qp[None], "bf16"), t(off.astype(np.int32)), t(c),
+                                        t(n.astype(np.int32)), CQ, CK, P.PARK_SELECT_TOPK, 0.2,
+                                        want_W=True)
+    Wg = Wg[0].cpu().numpy()
+    ok, err = PT.w_error_ok("bf16", Wg, W)
+    assert ok, err
+    assert PT.compare_masks(W, n, np.diff(off), "topk", 0.2, kc[0].cpu().numpy(),
+                            ki[0].cpu().numpy())[1] == 0
+    rounded = (Wg == W.astype(np.float32)).mean(axis=1)
+    print(f"[tiny tile d={d} CK={CK} 2^{exp}] rows in float64: {int((rounded > 0.95).sum())} of {CQ}")
+    assert (rounded > 0.95).sum() <= CQ // 2
+
+
 @pytest.mark.parametrize("mode", ["topk", "topp"])
 def test_retrieval_small_query_blocks(mode):
     # query blocks of 0-40 rows and a few of 100-300 (bf16): a wavefront's

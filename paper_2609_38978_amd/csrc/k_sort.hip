@@ -10,10 +10,9 @@
 
 namespace park {
 
-constexpr int SORT_NW = 16, SORT_NT = 64 * SORT_NW;  // wavefronts, threads of a scatter workgroup
 constexpr int SORT_MAXC = 2048;
 
-// Tokens per sort tile: 4096 (four steps of 64 per wavefront), doubled until a
+// Tokens per sort tile: 4096 (four steps of 64 for each of 16 wavefronts), doubled until a
 // head has at most 32 tiles, so that a scatter workgroup reads its column of
 // the histogram table in one or two round trips of loads; at most 32768, since
 // the counts inside a tile are 16 bits wide.
@@ -31,20 +30,21 @@ int sort_tiles(int H, int N, int C) {
 }
 
 // thist[h][tile][v] = #{ i in tile : z_i = v }
-__global__ __launch_bounds__(SORT_NT) void k_sort_hist(const int* __restrict__ labels, int N, int C,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_sort_hist(const int* __restrict__ labels, int N, int C,
                                                        int tile_sz, int* __restrict__ thist) {
   extern __shared__ int hist[];
   const int h = blockIdx.y, tile = blockIdx.x, nt = gridDim.x;
-  for (int v = threadIdx.x; v < C; v += SORT_NT) hist[v] = 0;
+  for (int v = threadIdx.x; v < C; v += NT) hist[v] = 0;
   __syncthreads();
   const int i0 = tile * tile_sz, i1 = min(N, i0 + tile_sz);
   const int* z = labels + (size_t)h * N;
   // four loads in flight per thread
-  for (int c0 = i0; c0 < i1; c0 += 4 * SORT_NT) {
+  for (int c0 = i0; c0 < i1; c0 += 4 * NT) {
     int v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int i = c0 + SORT_NT * k + threadIdx.x;
+      const int i = c0 + NT * k + threadIdx.x;
       v[k] = i < i1 ? z[i] : -1;
     }
 #pragma unroll
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_hist(const int* __restrict__ l
   }
   __syncthreads();
   int* out = thist + ((size_t)h * nt + tile) * C;
-  for (int v = threadIdx.x; v < C; v += SORT_NT) out[v] = hist[v];
+  for (int v = threadIdx.x; v < C; v += NT) out[v] = hist[v];
 }
 
 // Stable scatter of one tile (grid: tiles x heads; thist may be null when a
@@ -70,25 +70,29 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_hist(const int* __restrict__ l
 // What bounds it: a chain of round trips, not the bytes.  One wavefront per
 // tile walking 64 steps alone, after 40 dependent batches of table loads per
 // thread, took 66 us at 3 x 119056 tokens, C = 1861 (14 us at 12 x 17019,
-// C = 266; 14.5 us at 1 x 4096; 51 us at 40 x 75600, C = 1182); sixteen
-// wavefronts with four steps each and 30-row tables take 14.6 us (8, 6.5, 35).
-__global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict__ labels, int N, int C,
+// C = 266; 14.5 us at 1 x 4096; 51 us at 40 x 75600, C = 1182) as one launch on
+// an otherwise idle chip; sixteen wavefronts with four steps each and 30-row
+// tables take 14.6 us (8, 6.5, and 26 with eight wavefronts, see
+// launch_count_sort).
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_sort_scatter(const int* __restrict__ labels, int N, int C,
                                                           int nbits, int tile_sz,
                                                           const int* __restrict__ thist,
                                                           int* __restrict__ perm,
                                                           int* __restrict__ offsets) {
+  constexpr int NT = 64 * NW;
   extern __shared__ uint32_t sort_lds[];
   const int C2 = (C + 1) / 2;       // 32-bit words of one wavefront's counts
-  uint32_t* cnt = sort_lds;         // [SORT_NW][C2]: two clusters per word
-  int* base = (int*)(cnt + SORT_NW * C2);  // [C]
-  __shared__ int wsum[SORT_NW];
+  uint32_t* cnt = sort_lds;         // [NW][C2]: two clusters per word
+  int* base = (int*)(cnt + NW * C2);  // [C]
+  __shared__ int wsum[NW];
   const int h = blockIdx.y, tile = blockIdx.x, nt = gridDim.x, tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int* z = labels + (size_t)h * N;
   const int i0 = tile * tile_sz, i1 = min(N, i0 + tile_sz);
-  const int share = tile_sz / SORT_NW;  // tokens of a wavefront (a multiple of 256)
+  const int share = tile_sz / NW;  // tokens of a wavefront (a multiple of 256)
   const int j0 = i0 + wid * share, j1 = min(i1, j0 + share);
-  for (int e = tid; e < SORT_NW * C2; e += SORT_NT) cnt[e] = 0u;
+  for (int e = tid; e < NW * C2; e += NT) cnt[e] = 0u;
   __syncthreads();
   uint32_t* cw = cnt + wid * C2;
   for (int c0 = j0; c0 < j1; c0 += 256) {
@@ -102,12 +106,12 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
     for (int k = 0; k < 4; ++k)
       if ((unsigned)v[k] < (unsigned)C) atomicAdd(&cw[v[k] >> 1], 1u << (16 * (v[k] & 1)));
   }
-  // thread tid owns clusters tid and tid + SORT_NT in the table, and the
+  // thread tid owns clusters tid and tid + NT in the table, and the
   // consecutive ones tid * per + k in the scan
-  int before[SORT_MAXC / SORT_NT], all[SORT_MAXC / SORT_NT];
+  int before[SORT_MAXC / NT], all[SORT_MAXC / NT];
 #pragma unroll
-  for (int q = 0; q < SORT_MAXC / SORT_NT; ++q) {
-    const int v = tid + q * SORT_NT;
+  for (int q = 0; q < SORT_MAXC / NT; ++q) {
+    const int v = tid + q * NT;
     before[q] = all[q] = 0;
     if (v < C && thist) {
       const int* b = thist + (size_t)h * nt * C + v;
@@ -126,10 +130,10 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
   __syncthreads();
   // counts -> tokens of earlier wavefronts (two 16-bit clusters per word: a
   // tile's 32768 tokens never carry from one into the other)
-  for (int e = tid; e < C2; e += SORT_NT) {
+  for (int e = tid; e < C2; e += NT) {
     uint32_t run = 0u;
 #pragma unroll
-    for (int w = 0; w < SORT_NW; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const uint32_t x = cnt[w * C2 + e];
       cnt[w * C2 + e] = run;
       run += x;
@@ -141,13 +145,13 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
   }
   if (thist)
 #pragma unroll
-    for (int q = 0; q < SORT_MAXC / SORT_NT; ++q)
-      if (tid + q * SORT_NT < C) base[tid + q * SORT_NT] = all[q];
+    for (int q = 0; q < SORT_MAXC / NT; ++q)
+      if (tid + q * NT < C) base[tid + q * NT] = all[q];
   __syncthreads();
-  const int per = (C + SORT_NT - 1) / SORT_NT;
-  int s = 0, tv[SORT_MAXC / SORT_NT];
+  const int per = (C + NT - 1) / NT;
+  int s = 0, tv[SORT_MAXC / NT];
 #pragma unroll
-  for (int k = 0; k < SORT_MAXC / SORT_NT; ++k) {
+  for (int k = 0; k < SORT_MAXC / NT; ++k) {
     const int v = tid * per + k;
     tv[k] = k < per && v < C ? base[v] : 0;
     s += tv[k];
@@ -162,10 +166,10 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
   __syncthreads();
   int pre = inc - s;
 #pragma unroll
-  for (int q = 0; q < SORT_NW; ++q) pre += q < wid ? wsum[q] : 0;
+  for (int q = 0; q < NW; ++q) pre += q < wid ? wsum[q] : 0;
   int* off = offsets + (size_t)h * (C + 1);
 #pragma unroll
-  for (int k = 0; k < SORT_MAXC / SORT_NT; ++k) {
+  for (int k = 0; k < SORT_MAXC / NT; ++k) {
     const int v = tid * per + k;
     if (k < per && v < C) {
       base[v] = pre;
@@ -176,8 +180,8 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
   if (tile == 0 && tid == 0) off[C] = N;
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < SORT_MAXC / SORT_NT; ++q)
-    if (tid + q * SORT_NT < C) base[tid + q * SORT_NT] += before[q];
+  for (int q = 0; q < SORT_MAXC / NT; ++q)
+    if (tid + q * NT < C) base[tid + q * NT] += before[q];
   __syncthreads();
   int* p = perm + (size_t)h * N;
   uint16_t* cw16 = (uint16_t*)cw;
@@ -214,23 +218,40 @@ __global__ __launch_bounds__(SORT_NT) void k_sort_scatter(const int* __restrict_
   }
 }
 
-park_status launch_count_sort(const int* labels, int H, int N, int C, int* thist, int* perm,
+template <int NW>
+static park_status count_sort(const int* labels, int H, int N, int C, int* thist, int* perm,
                               int* offsets, hipStream_t st) {
+  constexpr int NT = 64 * NW;
   const int tsz = sort_tile(H, N, C);
   const int nt = (N + tsz - 1) / tsz;
   int nbits = 1;
   while ((1 << nbits) < C) ++nbits;
   // one tile per head: the scatter counts for itself
   if (nt > 1)
-    PARK_LAUNCH("sort_hist", k_sort_hist, dim3(nt, H), dim3(SORT_NT), (size_t)C * sizeof(int), st,
+    PARK_LAUNCH("sort_hist", k_sort_hist<NT>, dim3(nt, H), dim3(NT), (size_t)C * sizeof(int), st,
                 labels, N, C, tsz, thist);
-  const size_t lds = (size_t)SORT_NW * ((C + 1) / 2) * 4 + (size_t)C * 4;
+  const size_t lds = (size_t)NW * ((C + 1) / 2) * 4 + (size_t)C * 4;
   static std::atomic<uint64_t> done{0};
-  PARK_TRY(reserve_lds((const void*)k_sort_scatter, SORT_NW * SORT_MAXC / 2 * 4 + SORT_MAXC * 4,
-                       done, "sort"));
-  PARK_LAUNCH("sort_scatter", k_sort_scatter, dim3(nt, H), dim3(SORT_NT), lds, st, labels, N, C,
-              nbits, tsz, (const int*)(nt > 1 ? thist : nullptr), perm, offsets);
+  PARK_TRY(reserve_lds((const void*)k_sort_scatter<NW>, NW * SORT_MAXC / 2 * 4 + SORT_MAXC * 4, done,
+                       "sort"));
+  PARK_LAUNCH("sort_scatter", k_sort_scatter<NW>, dim3(nt, H), dim3(NT), lds, st, labels, N, C, nbits,
+              tsz, (const int*)(nt > 1 ? thist : nullptr), perm, offsets);
   return PARK_OK;
+}
+
+// Sixteen wavefronts a workgroup finish a tile soonest.  With more workgroups
+// than CUs eight serve better: twice as many fit beside each other and beside
+// what the other stream runs, where a 1024-thread workgroup waits for a CU to
+// clear (launch times, scatter + histogram, eight : sixteen; both sides of a
+// layer in flight: 24 x 119056 75 + 18 : 117 + 34 us, 40 x 75600 95 + 13 :
+// 109 + 48, the layers themselves equal within noise; 40 x 75600 queries alone
+// 26 + 5 : 35 + 6; below the line, 16 x 21600, C = 340 9.8 : 7.8, 3 x 119056
+// 16.7 : 14.7, 12 x 17019, d = 64 calls 1443 : 1410 us).
+park_status launch_count_sort(const int* labels, int H, int N, int C, int* thist, int* perm,
+                              int* offsets, hipStream_t st) {
+  if ((long)H * sort_tiles(H, N, C) > 256)
+    return count_sort<8>(labels, H, N, C, thist, perm, offsets, st);
+  return count_sort<16>(labels, H, N, C, thist, perm, offsets, st);
 }
 
 // Xp[h][i] = X[h][perm[h][i]], 16-byte vectors.

@@ -170,6 +170,19 @@ static void kmeans_options() {
   env_script.clear();
 }
 
+// The counting sort takes sixteen wavefronts a tile up to 256 workgroups and
+// eight beyond, and no histogram pass for heads of one tile.
+static void sort_routes() {
+  struct { int H, N, nw, hist; } cases[] = {{1, 4096, 16, 0},   {1, 4097, 16, 2},  {256, 4096, 16, 0},
+                                            {257, 4096, 8, 0},  {86, 8193, 8, 2},  {85, 8193, 16, 2},
+                                            {24, 119056, 8, 2}, {3, 119056, 16, 2}};
+  for (const auto& c : cases) {
+    EXPECT(cluster(c.N, 300, 2, c.H) == PARK_OK);
+    EXPECT(count(c.nw == 8 ? "k_sort_scatterILi8E" : "k_sort_scatterILi16E") == 2);
+    EXPECT(count("k_sort_scatter") == 2 && count("k_sort_hist") == c.hist);
+  }
+}
+
 // Without a metric the centroids' preparation uses 1024 threads on small grids,
 // with one the four wavefronts per 64 columns that its product is laid out for.
 static void prep_routes() {
@@ -240,6 +253,7 @@ int main() {
   kmeans_options();
   refine_routes();
   prep_routes();
+  sort_routes();
   if (failures) {
     std::fprintf(stderr, "%d host check(s) failed\n", failures);
     return 1;

@@ -460,6 +460,22 @@ def test_sort_tiles_and_listed_tokens(N, C):
     assert np.array_equal(off, np.concatenate([[0], np.cumsum(np.bincount(z, minlength=C))]))
 
 
+@pytest.mark.parametrize("H,N,C", [(64, 16384, 67), (65, 16384, 67), (90, 9001, 2048),
+                                   (257, 100, 33), (9, 131071, 300)])
+def test_sort_of_many_tiles(H, N, C):
+    # on either side of 256 sort workgroups, which sort with sixteen wavefronts a
+    # tile or eight; heads of one tile, of three, of more than 32 x 4096 tokens
+    g = torch.Generator(device="cuda").manual_seed(H)
+    X = torch.randn(H, N, 64, generator=g, device="cuda").to(torch.bfloat16)
+    r = P.park_cluster_keys(X, C, 1, seed=3, side=0, metric=P.PARK_METRIC_EUCLID)
+    P.park_check(r["ws"])
+    z, perm, off = (r[n].cpu().numpy() for n in ("labels", "perm", "offsets"))
+    for h in range(H):
+        assert np.array_equal(perm[h], np.argsort(z[h], kind="stable"))
+        assert np.array_equal(off[h], np.concatenate([[0], np.cumsum(np.bincount(z[h],
+                                                                                 minlength=C))]))
+
+
 def _offset_tokens(H, N, d, offset, seed):
     # clusters of N(0, 2^2) centres, N(0, 0.5^2) around them, and one N(0, (2 offset)^2)
     # vector that all tokens of the layer have in common

@@ -378,8 +378,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 //    beside them, and one table segment expanded before the first tile:
 //    1970 -> 1670 us.
 
-// neighbouring groups that run on one XCD at a time (1, 2, 4, 8: 1950, 1921,
-// 1890, 1864 us at 40 x 75600, top-p; 28.0, 28.4, 28.2, 28.6 ms at 24 x 119056)
+// neighbouring groups that run on one XCD at a time; 4 loses nowhere much (1, 2,
+// 4, 8: 1806, 1786, 1723, 1778 us at 40 x 75600, top-p; 28.6, 29.0, 28.7, 28.9 ms
+// at 24 x 119056; 9.69, 9.82, 9.71, 9.92 at 8 x 119056; 1386, 1375, 1353, 1371 us
+// at 16 x 32227, d = 64; 491, 503, 509, 503 at 8 x 16384; equal at 40 x 75600 in
+// blocks of 128 and 3 x 6000)
 constexpr int ATTN_BUN = 4;
 constexpr int ATTN_R = 128;  // rows per group (32 per wavefront)
 constexpr int ATTN_KSLOTS = 3;  // K tiles in LDS (V: one more)

@@ -1129,8 +1129,10 @@ park_status launch_kfilter_round(const bf16_t* X, int H, int N, int D, int C,
   const int nbm = (C + 15) / 16;
   const int NT = (N + kmeans_tile - 1) / kmeans_tile;
   // k_cand: half as many tiles a workgroup where that leaves most of the 768
-  // workgroups the chip holds idle (3 heads, C = 1861: 23 us with 8, 19 with 4;
-  // 40 heads, C = 1182: 49 and 55)
+  // workgroups the chip holds idle (us with 8 tiles : 4; below the line 3 heads,
+  // C = 1861 23.5 : 18.8; 5, 1182 20.0 : 15.4; 24, 700 22.3 : 18.4; 40, 600,
+  // d = 64 19.4 : 16.4; 12, 1000, d = 64 18.2 : 14.4; above it 8, 1861 31.1 :
+  // 30.4; 16, 1182 27.4 : 28.4; 16, 1861 48.2 : 49.8; 40, 1182 49 : 55)
   const int nvt = (C + 31) / 32, ngrp = (nvt + 3) / 4;
   const int vc = H * ngrp * ((nvt + kCandTiles - 1) / kCandTiles) >= 768 ? kCandTiles
                                                                            : kCandTiles / 2;

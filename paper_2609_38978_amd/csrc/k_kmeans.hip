@@ -182,22 +182,26 @@ __device__ void write_reference(Row row, const double* Gbar, int h, int p, int C
   }
 }
 
-// starting centroids from the seeded tokens, 256 / D per workgroup; the first
-// workgroups of a head also write the reference
-template <typename T, int D>
-__global__ __launch_bounds__(256) void k_seed_centroids(const T* __restrict__ X,
-                                                        const int* __restrict__ init, int N, int C,
-                                                        double* __restrict__ mu,
-                                                        const double* __restrict__ Gbar,
-                                                        double* __restrict__ ref) {
-  const int h = blockIdx.y, p = blockIdx.x, a = threadIdx.x % D;
-  const int v = p * (256 / D) + threadIdx.x / D;
+// starting centroids from the seeded tokens, one per workgroup of D threads; with
+// REF 256 / D per workgroup of 256, and the first workgroups of a head also write
+// the reference (apart, as the wavefronts of the plain kernel, which need next
+// to no registers and no LDS, find room beside the other side's Gram kernel:
+// 40 x 75600 498 -> 44 us a launch)
+template <typename T, int D, bool REF>
+__global__ __launch_bounds__(REF ? 256 : D) void k_seed_centroids(const T* __restrict__ X,
+                                                                  const int* __restrict__ init, int N,
+                                                                  int C, double* __restrict__ mu,
+                                                                  const double* __restrict__ Gbar,
+                                                                  double* __restrict__ ref) {
+  constexpr int RW = REF ? 256 / D : 1;
+  const int h = blockIdx.y, p = blockIdx.x, a = threadIdx.x % D, v = p * RW + threadIdx.x / D;
   const T* Xh = X + (size_t)h * N * D;
   const int* ih = init + (size_t)h * C;
   if (v < C) mu[((size_t)h * C + v) * D + a] = (double)to_f(Xh[(size_t)ih[v] * D + a]);
-  if (ref && p < ref_parts(D))
-    write_reference<D>([&](int r, int e) { return (double)to_f(Xh[(size_t)ih[r] * D + e]); }, Gbar, h,
-                       p, C, ref);
+  if constexpr (REF)
+    if (p < ref_parts(D))
+      write_reference<D>([&](int r, int e) { return (double)to_f(Xh[(size_t)ih[r] * D + e]); }, Gbar,
+                         h, p, C, ref);
 }
 
 // the reference of given starting centroids (warm start)
@@ -1549,9 +1553,13 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
                     kb.mu_init, Gbar, C, ref);
     } else {
       PARK_LAUNCH("kmeans_init", k_init_idx, dim3(H), dim3(1024), 0, st, N, C, seed, side, kb.init);
-      PARK_LAUNCH("kmeans_seed", (k_seed_centroids<T, D>),
-                  dim3(std::max((C * D + 255) / 256, ref_parts(D)), H), dim3(256), 0, st, X,
-                  (const int*)kb.init, N, C, kb.mu, Gbar, ref);
+      if (ref)
+        PARK_LAUNCH("kmeans_seed", (k_seed_centroids<T, D, true>),
+                    dim3(std::max((C * D + 255) / 256, ref_parts(D)), H), dim3(256), 0, st, X,
+                    (const int*)kb.init, N, C, kb.mu, Gbar, ref);
+      else
+        PARK_LAUNCH("kmeans_seed", (k_seed_centroids<T, D, false>), dim3(C, H), dim3(D), 0, st, X,
+                    (const int*)kb.init, N, C, kb.mu, Gbar, ref);
     }
     if constexpr (fast)
       if (filt) PARK_TRY(launch_kfilter_setup((const bf16_t*)X, Gbar, H, N, D, *kb.kf, st));

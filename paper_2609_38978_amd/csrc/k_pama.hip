@@ -1294,21 +1294,21 @@ __global__ __launch_bounds__(1024) void k_pama_plan(const int* __restrict__ q_of
   }
 }
 
-// Fast retrieval.  A workgroup takes four items of one head (one round of 64
-// queries of a query block per wavefront, from the plan) and streams the
+// Fast retrieval.  A workgroup takes eight items of one head (chunks of 32
+// queries of a query block, two per wavefront, from the plan) and streams the
 // head's key-block centroids through an NS-slot LDS ring (32 rows of the
 // two f16 parts per tile, LDS DMA, rows swizzled in 16-byte chunks),
 // twice: pass 1 builds each query's normaliser, pass 2 sums the
-// probabilities over the round's queries.  Every tile serves 256 queries.
+// probabilities over each chunk's queries.  Every tile serves 256 queries.
 //
-// MFMA 32x32x16 on two 32-query groups per wavefront.  The query fragment
+// MFMA 32x32x16 on the two chunks of a wavefront.  The query fragment
 // (query l%32, dims 16 s + 8 (l/32) ..) and the centroid fragment (centroid
 // l%32, same dims) serve as either operand, so pass 1 computes S^T (lane:
 // one query, centroids 8b + 4(l/32) + r) and pass 2 computes S (lane: one
 // centroid, queries 8b + 4(l/32) + r); each pass then reduces within lanes.
-// Accuracy as in the float error bound below: the c1 part is accumulated in
-// 32-dimension segments (two MFMAs from zero) added in float, the two small
-// part in one chain over all dimensions.
+// Accuracy as in the float error bound above: the c1 part is accumulated in
+// 32-dimension segments (two MFMAs from zero) added in float, the c2 part in
+// one chain over all dimensions.
 //
 // Scores are kept in log2 units; pass 1 keeps per query the reference R and
 // z (tile terms added in a tree), pass 2 recomputes 2^x and weights it with
@@ -2225,8 +2225,8 @@ __device__ void select_topp_radix(const float* __restrict__ w, const int* __rest
   if (tid == 0) *kv_count = m;
 }
 
-// Certified selection on the float W^: sort (W^ descending, id ascending),
-// take the cut, and accept the row only if the cut is robust to the row's
+// Certified selection on the float W^: find the cut (W^ descending, id
+// ascending) by radix selection, and accept the row only if the cut is robust to the row's
 // relative error delta_u plus an absolute error for values below float's
 // normal range: the last kept block's lower bound must exceed the first
 // dropped block's upper bound and, for top-p, the kept set's bounds must

@@ -128,8 +128,8 @@ struct RetrieveBufs {
   // row of kv_index until the float64 selection writes it
   int* bandc;
 };
-// fast retrieval: items (rounds of 64 queries) per head, and rows of round
-// partial sums per head (every round after a block's first), kept in the
+// fast retrieval: items (chunks of 32 queries) per head, and rows of chunk
+// partial sums per head (every chunk after a block's first), kept in the
 // float64 W^ buffer, which is free until the float64 rows are computed
 inline int pama_icap(int N, int CQ) { return (N + 31) / 32 + CQ + 8; }
 inline int pama_pcap(int N) { return (N + 31) / 32 + 1; }

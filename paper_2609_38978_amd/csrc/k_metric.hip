@@ -37,8 +37,12 @@ __global__ __launch_bounds__(256) void k_gram_mfma(const T* __restrict__ X, int 
   // 4 x U rows of raw elements per stage; the next stage's loads are in flight
   // while this one is multiplied (one step of look-ahead covered a tenth of a
   // load's latency: 2.02 -> 1.57 ms at 40 x 75600, d = 128;
-  // 373 -> 259 us at 3 x 119056)
-  constexpr int U = sizeof(T) == 2 ? 8 : 4, RW = E * (int)sizeof(T) / 4;  // words per lane and row
+  // 373 -> 259 us at 3 x 119056).  At d = 64 a step has a quarter of the products
+  // and more wavefronts fit with fewer rows in registers, so one step of
+  // look-ahead is the fastest (us with U = 1, 2, 4, 8: 40 x 75600 932, 1209, 1257,
+  // 1502; 12 x 16830 59, 87, 92, 109; 3 x 119056 203, 212, 218, 224; 1 x 4096
+  // float32 19, 32, 32, 33; at d = 128 40 x 75600 1578, 1507, 1481, 1463)
+  constexpr int U = D == 64 ? 1 : sizeof(T) == 2 ? 8 : 4, RW = E * (int)sizeof(T) / 4;  // words per lane and row
   auto load = [&](int rb, uint32_t (&raw)[U][RW]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {

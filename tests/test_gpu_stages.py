@@ -66,6 +66,28 @@ def test_metric_factor_and_transform(case):
         assert np.all(err <= 2.0 ** -23 * np.abs(ref) + 1e-30), (tag, err.max())
 
 
+def test_metric_time_follows_the_head_dimension():
+    # half the dimensions are a quarter of the Gram products; rows held ahead as
+    # at d = 128 made them cost the same (353 and 359 us at this size)
+    t = {}
+    for d in (64, 128):
+        Q = torch.randn(24, 30000, d, generator=torch.Generator(device="cuda").manual_seed(d),
+                        device="cuda").to(torch.bfloat16)
+        ws = P.workspace(Q, 16, 16)
+        for prof in (False, True):
+            P.park_profile_reset()
+            P.park_profile_enable(prof)
+            try:
+                for _ in range(5):
+                    P.park_cluster_keys(Q, 16, 1, side=1, metric=P.PARK_METRIC_QRKC, Qmetric=Q, ws=ws)
+                P.park_check(ws)
+            finally:
+                P.park_profile_enable(False)
+        t[d] = P.park_profile_read()["gram_partial"]["ms"]
+    print(f"[gram] d = 64 / d = 128: {t[64] / t[128]:.2f}")
+    assert t[64] < 0.75 * t[128]
+
+
 @pytest.mark.parametrize("side", [0, 1])
 def test_kmeans_labels_permutation_offsets(case, side):
     tag, cfg, q, k, v = case

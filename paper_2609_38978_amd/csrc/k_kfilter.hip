@@ -710,8 +710,10 @@ __global__ __launch_bounds__(256, 3) void k_assign_cand(
         const int v = bidx[tb];
         e1 = fmaf(kx[tb], wn[(size_t)h * Cpad + v], eb[(size_t)h * Cpad + v]);
         const float emax = fmaf(kx[tb], nmax, ebmax) * 1.0001f;
-        ubv[tb] = best[tb] + e1;
-        ok = (L[tb] - emax) > ubv[tb];
+        if (emax < kmeans_emax) {
+          ubv[tb] = best[tb] + e1;
+          ok = (L[tb] - emax) > ubv[tb];
+        }
       }
       if (ok) {
         const int v = bidx[tb];

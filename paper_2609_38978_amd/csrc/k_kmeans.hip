@@ -468,8 +468,8 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
 // Certification: with v1 the fast argmin and L the smallest fast score of
 // every other centroid, v1 is the exact argmin when
 //   L - Emax > s^_v1 + E_v1,   Emax = Kx max_v |w_v| + max_v eb_v >= E_v.
-// Otherwise (near-ties, exact ties) the token is listed for the float64
-// refinement.
+// Otherwise (near-ties, exact ties, scores near the end of the float range: see
+// kmeans_emax) the token is listed for the float64 refinement.
 //
 // Bookkeeping per lane and token (the lane sees half of the centroids): the
 // two smallest fast scores (best <= L) and the id of the smallest, three VALU
@@ -736,8 +736,10 @@ __global__ __launch_bounds__(256, 2) void k_assign_fast(const bf16_t* __restrict
         const int v = bidx[tb];
         const float e1 = fmaf(kx[tb], wn[(size_t)h * Cpad + v], eb[(size_t)h * Cpad + v]);
         const float emax = fmaf(kx[tb], nmax, ebmax) * 1.0001f;
-        ubv[tb] = best[tb] + e1;
-        ok = (L[tb] - emax) > ubv[tb];
+        if (emax < kmeans_emax) {
+          ubv[tb] = best[tb] + e1;
+          ok = (L[tb] - emax) > ubv[tb];
+        }
       }
       if (ok) labels[(size_t)h * N + tok] = bidx[tb];
       fl[tb] = !ok;

@@ -41,6 +41,13 @@ inline int kmeans_cpad(int C) { return (C + 63) / 64 * 64; }
 #define PARK_KM_TB 2
 #endif
 constexpr int kmeans_tile = 128 * PARK_KM_TB;
+// The fast assignments certify a token only while the error bound Emax of its
+// scores is below this: it holds 1.3e-7 |b_v| and at least 5e-5 |x| |w_v| of
+// every centroid, so no score, product or partial sum is near float's largest
+// (a centroid whose b_v overflowed to infinity would look far away).  Other
+// tokens are listed with an infinite bound, which makes every centroid a
+// candidate of the refinement.
+constexpr float kmeans_emax = 1e31f;
 
 // key-block count padded to the fast retrieval's tile multiple
 inline int pama_ckpad(int CK) { return (CK + 63) / 64 * 64; }

@@ -530,6 +530,26 @@ def test_kmeans_labels_of_tokens_with_a_common_offset(d, H, N, C, offset):
             assert n_bad == 0, (side, h, n_mis, worst)
 
 
+@pytest.mark.parametrize("N,C,d", [(2000, 40, 64), (2000, 40, 128), (4000, 600, 128)])
+@pytest.mark.parametrize("side,xe,qe", [(0, 59, 0), (0, 60, 0), (0, 61, 0), (0, 63, 0), (0, -49, 0),
+                                        (1, 29, 29), (1, 30, 30), (1, 31, 31), (1, 34, 34),
+                                        (1, 10, 50), (1, -44, -18), (1, -48, -25)])
+def test_kmeans_labels_at_the_ends_of_the_float_range(N, C, d, side, xe, qe):
+    # scores near and past both ends of the float range (their float64 values are
+    # ordinary): no token may be certified on scores that overflowed or vanished
+    X = _offset_tokens(1, N, d, 1.0, 5) * 2.0 ** xe
+    Qm = _offset_tokens(1, N, d, 0.0, 6) * 2.0 ** qe
+    x, q, T = PT.np64(X)[0], PT.np64(Qm)[0], 3
+    kw = dict(metric=P.PARK_METRIC_EUCLID) if side == 0 else \
+        dict(metric=P.PARK_METRIC_QRKC, Qmetric=Qm)
+    r = P.park_cluster_keys(X, C, T, seed=7, side=side, **kw)
+    P.park_check(r["ws"])
+    ref = O.cluster_queries(x, C, T, 7, 0) if side == 0 else O.cluster_keys(x, q, C, T, 7, 0)
+    n_mis, n_bad, worst = PT.label_flips(x if side == 0 else ref["Kt"], ref["mu"],
+                                         r["labels"].cpu().numpy()[0], ref["labels"])
+    assert n_bad == 0, (n_mis, worst)
+
+
 @pytest.mark.parametrize("H,N,C,d", [(12, 16830, 266, 64), (8, 16335, 256, 128)])
 def test_kmeans_offset_does_not_flood_the_refinement(H, N, C, d):
     # without a reference the error bound grows with the offset and most tokens

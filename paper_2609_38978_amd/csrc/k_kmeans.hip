@@ -113,9 +113,9 @@ __global__ __launch_bounds__(256) void k_copy64(const double* __restrict__ src,
 
 typedef double f64x4k_t __attribute__((ext_vector_type(4)));
 
-// Reference of the fast scores: ref[h] = {w_c [D], D / 32 parts of b_c, as many of
-// |w_c|^2} with c the mean of up to 64 of the starting centroids, w_c = Gbar c
-// (or c), b_c = c . w_c.  Scores against w_v - w_c and b_v - b_c differ from
+// Reference of the fast scores: ref[h] = {w_c [D], b_c in D / 32 parts, the norms of
+// w_c's D / 32 parts} with c the mean of up to 64 of the starting centroids,
+// w_c = Gbar c (or c), b_c = c . w_c.  Scores against w_v - w_c and b_v - b_c differ from
 // those against w_v and b_v by the same amount for every centroid of a token,
 // so the argmin is the same, and the error bound of the fast scores (relative to
 // |x| |w_v - w_c|) does not grow with what all tokens have in common.  Any c will
@@ -177,7 +177,7 @@ __device__ void write_reference(Row row, const double* Gbar, int h, int p, int C
     if (tid < 32) out[col] = wc;
     if (tid == 0) {
       out[D + p] = b;
-      out[D + ref_parts(D) + p] = n2;
+      out[D + ref_parts(D) + p] = sqrt(n2);
     }
   }
 }
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_reference(const double* __restrict__ mu
 // D columns that it replaces were chains of dependent batches of loads:
 // 39 -> 19 us at 3 x 119056 tokens, C = 1861; 12 -> 8 us at 8 x 16384, C = 256.
 // Large layers are near the memory's rate (71 -> 65 us at 40 x 75600: 200 MB).
-template <int D, int NT>
+template <int D, int NT, bool REF>
 __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
                                               const double* __restrict__ Gbar,
                                               const double* __restrict__ ref, int C,
@@ -256,10 +256,10 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
   constexpr int CB = 16;
   __shared__ double ms[CB][D];
   __shared__ double ws[CB][D + 1];
-  __shared__ double rs[ref_stride(D)];  // w_c, b_c, |w_c|^2 (0 without a reference)
+  __shared__ double rs[REF ? ref_stride(D) : 1];  // the reference
   __shared__ float fnl[CB], fel[CB];
   const int h = blockIdx.y, v0 = blockIdx.x * CB, tid = threadIdx.x;
-  const double rv = ref && tid < ref_stride(D) ? ref[(size_t)h * ref_stride(D) + tid] : 0.0;
+  const double rv = REF && tid < ref_stride(D) ? ref[(size_t)h * ref_stride(D) + tid] : 0.0;
   if (NT == 4 * D && Gbar) {
     // operand k-index: steps 2 j and 2 j + 1 take dimensions 8 j + 2 (l / 16)
     // and the next one of both operands
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     ms[r][a] = m;
     if (!Gbar) ws[r][a] = m;
   }
-  if (tid < ref_stride(D)) rs[tid] = rv;
+  if (REF && tid < ref_stride(D)) rs[tid] = rv;
   __syncthreads();
   // (under rmode 2 w itself is written at the end: the radius bound reads the old w)
   if (w3 || m2 || rmode != 2)
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
         uint32_t p1 = 0u, p2 = 0u, p3 = 0u;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-          const double x = ws[r][a + k] - rs[a + k];
+          const double x = ws[r][a + k] - (REF ? rs[a + k] : 0.0);
           const bf16_t q1 = f2bf((float)x);
           const double r1 = x - (double)bf2f(q1);
           const bf16_t q2 = f2bf((float)r1);
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
     for (int j = 0; j < D / LPC; ++j) {
       const int c = sub + LPC * j;
       s = fma(ms[r][c], ws[r][c], s);
-      const double u = ws[r][c] - rs[c];
+      const double u = ws[r][c] - (REF ? rs[c] : 0.0);
       n2 = fma(u, u, n2);
       m2s = fma(ms[r][c], ms[r][c], m2s);
       if (rmode == 2) {
@@ -390,16 +390,20 @@ __global__ __launch_bounds__(NT) void k_prep(const double* __restrict__ mu,
         // of w_v and b_v themselves, so that what is certified is also their
         // float64 argmin (2^-30 of |w_v| <= |w_v - w_c| + |w_c| is 2^-44 |x| |w_v|
         // of a bound)
-        double bc = 0.0, nc = 0.0;
+        double sr = s, un = sqrt(n2), fn = 0.0, fe = 0.0;
+        if constexpr (REF) {
+          double bc = 0.0, nc = 0.0;
 #pragma unroll
-        for (int q = 0; q < ref_parts(D); ++q) {
-          bc += rs[D + q];
-          nc += rs[D + ref_parts(D) + q];
+          for (int q = 0; q < ref_parts(D); ++q) {
+            bc += rs[D + q];
+            nc += rs[D + ref_parts(D) + q];  // (the parts' norms: their sum is at least |w_c|)
+          }
+          sr = s - bc;
+          fn = 9.3132257e-10 * (un + nc);
+          fe = 5.6843419e-14 * fabs(s);
         }
-        const double fl = ref ? 1.0 : 0.0, sr = s - bc, un = sqrt(n2);
-        fnr = (float)((un + fl * 9.3132257e-10 * (un + sqrt(nc))) * (1.0 + 1e-6));
-        fer = (float)((fabs(sr) * (2.0 * 1.1 * 5.9604644775390625e-08) + fl * 5.6843419e-14 * fabs(s)) *
-                      (1.0 + 1e-6));
+        fnr = (float)((un + fn) * (1.0 + 1e-6));
+        fer = (float)((fabs(sr) * (2.0 * 1.1 * 5.9604644775390625e-08) + fe) * (1.0 + 1e-6));
         b32[(size_t)h * Cpad + v0 + r] = (float)sr;
         wn[(size_t)h * Cpad + v0 + r] = fnr;
         eb[(size_t)h * Cpad + v0 + r] = fer;
@@ -1591,8 +1595,11 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
     // holds the grid, 1024 threads shorten it (us a round, 4 D threads : 1024:
     // 1 x 8073, d = 128, C = 128 6.1 : 5.0; 8 x 16335, C = 256 5.6 : 4.6;
     // 12 x 16830, d = 64, C = 266 5.9 : 4.6)
-    if (!Gbar && (long)nbm * H < 512) PARK_TRY(prep(k_prep<D, 1024>, 1024));
-    else PARK_TRY(prep(k_prep<D, 4 * D>, 4 * D));
+    const bool wide = !Gbar && (long)nbm * H < 512;
+    if (ref)
+      PARK_TRY(wide ? prep(k_prep<D, 1024, fast>, 1024) : prep(k_prep<D, 4 * D, fast>, 4 * D));
+    else
+      PARK_TRY(wide ? prep(k_prep<D, 1024, false>, 1024) : prep(k_prep<D, 4 * D, false>, 4 * D));
     if constexpr (fast) {
       if (filt && t > 0)
         PARK_TRY(launch_kfilter_round((const bf16_t*)X, H, N, D, C, kb, *kb.kf, rmode == 1, st));

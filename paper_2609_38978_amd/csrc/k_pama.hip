@@ -972,7 +972,11 @@ __global__ __launch_bounds__(256) void k_select_band(const double* __restrict__ 
 // A term below 2^-126 before the weight may flush to zero: at most
 // 1.5 2^-126 of P, since z >= 2^(B - 1/2).  Values below float's normal range
 // carry such an absolute error, handled by the selection.  Rows whose
-// selection this bound cannot certify are recomputed in float64.
+// selection this bound cannot certify are recomputed in float64.  A bound of 1
+// or more certifies nothing and is made infinite, which also keeps every block
+// of the row in the float64 pass: below it isd |q_i| cmax is less than 2^21, so
+// R_i is an exact integer and x within what is assumed; above about 2^28 R_i
+// rounds, 2^x may overflow and the row hold NaN or zeros.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -1154,7 +1158,7 @@ __device__ __forceinline__ float pama_bound(float isd, float qn, float qmax, flo
   const float xm = 2.01f * isd * qn * cmax * L2E + 36.0f;
   const float ei = isd * ((ET + 2.1f * U24) * qn + FL * 1.01f * qmax) * cmax + 0.71f * U24 * xm;
   const float b = 2.02f * (1.01f * ei + DEL * (2.0f + 1.5f * xm)) + U24 * ((float)(CK / 32) + 31.0f);
-  return b == b ? b : INFINITY;  // (0 x inf: nothing is known)
+  return b < 1.0f ? b : INFINITY;  // (also 0 x inf: nothing is known)
 }
 
 // B and the two scalings of the sums (see above): 2^B >= n_max
@@ -1972,7 +1976,7 @@ __device__ void select_topk_radix(const float* __restrict__ w, const int* __rest
   __syncthreads();
   lt = max(max((uint32_t)tmp[0], (uint32_t)tmp[1]), max((uint32_t)tmp[2], (uint32_t)tmp[3]));
   const double eps = 4.0 * 1.1754943508222875e-38;  // absolute error near underflow
-  bool ok = cnt_ge == m;
+  bool ok = cnt_ge == m && dl < INFINITY;
   if (ok && m < nvalid) {
     const double a = (double)__uint_as_float(a_bits) * (1.0 - dl) - eps;
     const double b = (double)__uint_as_float(lt) * (1.0 + dl) + eps;

@@ -221,6 +221,35 @@ def test_retrieval_operand_ranges(d, CK, qexp, kexp):
                                     b[0].cpu().numpy())[1] == 0
 
 
+@pytest.mark.parametrize("d,exps", [(64, (8, 11, 13, 14, 16, 20, 25, 50)), (128, (8, 11, 13, 14, 16, 17))])
+@pytest.mark.parametrize("CK", [33, 256, 300])
+def test_retrieval_logits_beyond_the_float_reference(d, CK, exps):
+    # logits from 2^18 to far past 2^28, where the fast path's integer reference
+    # rounds and its exponentials overflow: nothing of such rows may be used (the
+    # float64 pass itself is exact at d = 64, where the scale is a power of two,
+    # and to about 2^45 at d = 128); every block kept (ratio 1) as well
+    for e in exps:
+        rng = np.random.default_rng(3000 + d + CK + e)
+        N, CQ = 1500, 20
+        off = np.concatenate([[0], np.sort(rng.choice(np.arange(1, N), CQ - 1, False)), [N]])
+        Qp = synth.bf16_round((2.0 ** (e + 1) * rng.standard_normal((N, d))).astype(np.float32))
+        c = (2.0 ** (e + 1) * rng.standard_normal((CK, d))).astype(np.float32)
+        n = rng.integers(0, 40, CK)
+        W = O.pama(Qp, off, c, n)
+        t = lambda a: torch.from_numpy(np.ascontiguousarray(a)[None]).cuda()
+        for mode, param in (("topk", 0.2), ("topk", 1.0), ("topp", 0.8737)):
+            sel = P.PARK_SELECT_TOPK if mode == "topk" else P.PARK_SELECT_TOPP
+            args = (PT.to_dev(Qp[None], "bf16"), t(off.astype(np.int32)), t(c),
+                    t(n.astype(np.int32)), CQ, CK, sel, param)
+            kc, ki, Wg = P.park_retrieve_blocks(*args, want_W=True)
+            ok, err = PT.w_error_ok("bf16", Wg[0].cpu().numpy(), W)
+            assert ok, (e, mode, err)
+            kc2, ki2, _ = P.park_retrieve_blocks(*args)
+            for a, b in ((kc, ki), (kc2, ki2)):
+                assert PT.compare_masks(W, n, np.diff(off), mode, param, a[0].cpu().numpy(),
+                                        b[0].cpu().numpy())[1] == 0, (e, mode, param)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("CK", [96, 300])
 @pytest.mark.parametrize("exp", [-99, -104, -108, -125, -145])

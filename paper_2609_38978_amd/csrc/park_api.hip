@@ -242,6 +242,14 @@ static QcenBufs carve_qcen(Carver& cv, int H, int D, int CQ) {
   return q;
 }
 
+// one side's clustering: the status word, then its region
+static size_t cluster_ws_end(int H, int N, int D, int C) {
+  Carver a(nullptr);
+  a.take<int>(64);
+  carve_cluster(a, H, N, D, C);
+  return a.off;
+}
+
 // status word first, then the largest of the cluster, retrieval and attention regions
 static size_t ws_bytes_for(int H, int N, int D, int CQ, int CK) {
   Carver a(nullptr);
@@ -554,7 +562,7 @@ park_status park_cluster_keys(const void* X, const void* Qmetric, const park_dim
   } else if (R_out || Xt_out) {
     return fail(PARK_ERR_INVALID_ARG, "R_out / Xt_out need the QRKC metric");
   }
-  PARK_TRY(check_ws(ws, ws_bytes, ws_bytes_for(dims->H, dims->N, dims->d, C, C)));
+  PARK_TRY(check_ws(ws, ws_bytes, cluster_ws_end(dims->H, dims->N, dims->d, C) + 256));
   hipStream_t st = (hipStream_t)stream;
   Carver cv(ws);
   PARK_TRY(launch_clear_status(cv.take<int>(64), st));

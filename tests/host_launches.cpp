@@ -132,12 +132,28 @@ static int count(const char* kernel) {
 }
 
 static park_status cluster(int N, int C, int T, int H = 2, int dim = 128,
-                           int metric = PARK_METRIC_QRKC) {
-  const park_dims d = {H, N, dim, PARK_BF16};
+                           int metric = PARK_METRIC_QRKC, size_t ws_bytes = (size_t)1 << 40,
+                           int dtype = PARK_BF16) {
+  const park_dims d = {H, N, dim, dtype};
   launches.clear();
   return park_cluster_keys(FAKE, FAKE, &d, C, T, 0, 1, metric, 0.05, 1e-6, 1e-12, nullptr,
-                           (int32_t*)FAKE, (int32_t*)FAKE, nullptr, nullptr, FAKE, (size_t)1 << 40,
-                           nullptr);
+                           (int32_t*)FAKE, (int32_t*)FAKE, nullptr, nullptr, FAKE, ws_bytes, nullptr);
+}
+
+// A workspace for CQ and CK serves the clustering of either side.
+static void workspace_of_unequal_sides() {
+  struct { int H, N, CQ, CK, d, dtype; } cases[] = {{1, 4096, 16, 64, 64, PARK_F32},
+                                                    {3, 6001, 1, 2048, 128, PARK_BF16},
+                                                    {40, 75600, 295, 1182, 128, PARK_BF16},
+                                                    {2, 4096, 600, 32, 64, PARK_BF16},
+                                                    {2, 4096, 256, 256, 128, PARK_BF16}};
+  for (const auto& c : cases) {
+    const park_dims d = {c.H, c.N, c.d, c.dtype};
+    size_t bytes = 0;
+    EXPECT(park_workspace_size(&d, c.CQ, c.CK, &bytes) == PARK_OK);
+    for (int C : {c.CQ, c.CK})
+      EXPECT(cluster(c.N, C, 2, c.H, c.d, PARK_METRIC_QRKC, bytes, c.dtype) == PARK_OK);
+  }
 }
 
 // The options of the candidate filter hold for a whole k-means: its rounds read
@@ -250,6 +266,7 @@ static void lds_reservations() {
 
 int main() {
   lds_reservations();
+  workspace_of_unequal_sides();
   kmeans_options();
   refine_routes();
   prep_routes();

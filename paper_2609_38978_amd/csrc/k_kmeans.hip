@@ -1167,20 +1167,28 @@ __global__ __launch_bounds__(256) void k_refine_cand(const bf16_t* __restrict__ 
 //
 // What bounds it: latency, then the float64 matrix rate.  k_refine_cand sweeps
 // the centroids once more in bf16 to find each token's candidates, then scores
-// those: 17.0 us a round at 12 x 17019 tokens, d = 64, C = 266, most of it the
-// chain list, tokens, ring of tiles, candidates; this 13.5 us.  At d = 128 the
-// float64 tiles cost twice as much and the sweep is the better one (8 x 16384,
-// C = 256: 20.1 us against 26.1).
+// those: 18.7 us a round at 12 x 16830 tokens, d = 64, C = 266, most of it the
+// chain list, tokens, ring of tiles, candidates; this 13.2 us.  At d = 128 the
+// float64 tiles cost twice as much and the sweep is taken (this : the sweep,
+// 8 x 16384, C = 256 18.6 : 19.3; 1 x 8073, C = 128 12.3 : 14.7; 3 x 30000,
+// C = 400 29.6 : 26.7).
 //
-// Its work grows with the listed tokens times all centroids, so the sweep also
-// wins on larger layers (us a round, this : the sweep, d = 64):
-//   1 x 4032, C = 64    6.3 :  7.2     16 x 32148, C = 504   30.5 : 22.9
-//  12 x 16830, C = 133 11.6 : 15.3     24 x 29970, C = 133   20.1 : 15.2
-//  12 x 16830, C = 511 20.6 : 23.7     40 x 64521, C = 325  113.5 : 32.1
-//   1 x 118260, C = 500 15.9 : 24.0     3 x 118260, C = 500  30.6 : 25.5
-//  12 x 23760, C = 500 23.5 : 24.3     40 x 64521, C = 64    30.0 : 13.9
-// The line at 2^18 tokens is where the two meet (285120 and 150336 tokens at
-// C = 500: 23.5 : 24.3 and 22.7 : 21.9).
+// The chunks of one rank of all heads lie side by side in the grid (heads in x):
+// only a head's first ones hold tokens, and with the heads in y a grid 32 chunks
+// wide put those on the same CUs, head after head (24 x 8136, C = 266: 31.6 us, 15
+// at widths of 31 and 33, now 12.9; 12 x 16830, C = 266: 13.2).
+//
+// Its work grows with the listed tokens times all centroids, so the sweep wins
+// on larger layers (us a round, this : the sweep, d = 64):
+//   1 x 4032, C = 64    7.4 :  9.9     24 x 29970, C = 133   26.6 : 15.7
+//  12 x 16830, C = 133 10.5 : 15.4     16 x 32148, C = 504   30.5 : 23.5
+//  12 x 16830, C = 511 16.4 : 24.0      3 x 118260, C = 500  34.4 : 26.6
+//  24 x 8136, C = 266  12.5 : 18.2     40 x 16200, C = 254   22.8 : 19.3
+//   1 x 118260, C = 500 17.6 : 23.7     40 x 64521, C = 325  134.3 : 39.9
+//  12 x 23760, C = 500 20.2 : 26.2     40 x 64521, C = 64    56.1 : 22.6
+// The line is at 2^18 tokens, up to which it never lost (8 x 32768, C = 64 to
+// 500: 0 to 4 us better; 285120 tokens in 12 heads 6 better, 355000 in 3 eight
+// worse).
 constexpr long kRefineAllTokens = 1l << 18;
 template <int D>
 __global__ __launch_bounds__(512) void k_refine_all(const bf16_t* __restrict__ X,
@@ -1193,7 +1201,7 @@ __global__ __launch_bounds__(512) void k_refine_all(const bf16_t* __restrict__ X
   __shared__ int wsc[NW], spos[TC];
   __shared__ double rb[NW][TC];
   __shared__ int ri[NW][TC];
-  const int h = blockIdx.y, tid = threadIdx.x, l = tid & 63, c = l & 15, kq = l >> 4;
+  const int h = blockIdx.x, tid = threadIdx.x, l = tid & 63, c = l & 15, kq = l >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // thread tid: list lengths of tiles tid * per .. ; pre: listed tokens before them
   const int NT = (N + kmeans_tile - 1) / kmeans_tile, per = (NT + 64 * NW - 1) / (64 * NW);
@@ -1219,7 +1227,7 @@ __global__ __launch_bounds__(512) void k_refine_all(const bf16_t* __restrict__ X
   const double* wh = w64 + (size_t)h * C * D;
   const double* bh = b64 + (size_t)h * C;
   const int ntile = (C + 15) / 16;
-  for (int lo = blockIdx.x * TC; lo < cnt; lo += gridDim.x * TC) {
+  for (int lo = blockIdx.y * TC; lo < cnt; lo += gridDim.y * TC) {
     __syncthreads();  // the previous chunk's slots and minima are read
     if (tid < TC) spos[tid] = -1;
     __syncthreads();
@@ -1610,7 +1618,7 @@ static park_status kmeans_impl(const T* X, const double* Gbar, int H, int N, int
                     (const float*)kb.hmax, nbm, N, C, kb.labels, kb.flags, all ? nullptr : kb.flagu,
                     kb.nflag);
       if (all)
-        PARK_LAUNCH("kmeans_refine64", k_refine_all<D>, dim3(std::min((N + 255) / 256, 1024), H),
+        PARK_LAUNCH("kmeans_refine64", k_refine_all<D>, dim3(H, std::min((N + 255) / 256, 1024)),
                     dim3(512), 0, st, (const bf16_t*)X, (const double*)kb.w, (const double*)kb.b, N,
                     C, (const int*)kb.flags, (const int*)kb.nflag, kb.labels, status);
       else

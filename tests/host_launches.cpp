@@ -26,6 +26,7 @@ static std::map<const void*, std::string>& kernel_names() {  // (used before mai
 struct Launch {
   std::string name;  // mangled kernel name
   bool lds_ok;       // its dynamic LDS is within 64 KB or what this device was told
+  dim3 grid;
 };
 static std::vector<Launch> launches;
 static std::map<std::string, std::vector<std::string>> env_script;  // answers, the last one repeated
@@ -77,9 +78,10 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *stream = config.stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t lds, hipStream_t) {
   const auto it = lds_allowed.find({device, f});
-  launches.push_back({kernel_names()[f], lds <= (it == lds_allowed.end() ? 65536u : it->second)});
+  launches.push_back({kernel_names()[f], lds <= (it == lds_allowed.end() ? 65536u : it->second),
+                      grid});
   return hipSuccess;
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
@@ -220,12 +222,15 @@ static void prep_routes() {
 static void refine_routes() {
   struct { int H, N, C, d, all; } cases[] = {
       {1, 4096, 64, 64, 1},   {12, 17019, 266, 64, 1},  {8, 32768, 511, 64, 1},
+      {24, 8136, 266, 64, 1},
       {8, 32769, 511, 64, 0}, {24, 30000, 133, 64, 0},  {40, 64521, 64, 64, 0},
       {1, 4096, 64, 128, 0},  {12, 17019, 512, 64, 0}};
   for (const auto& c : cases) {
     EXPECT(cluster(c.N, c.C, 3, c.H, c.d) == PARK_OK);
     EXPECT(count("k_refine_all") == (c.all ? 3 : 0));
     EXPECT(count("k_refine_cand") == (c.all ? 0 : 3));
+    for (const Launch& l : launches)  // chunks of one rank side by side, whatever the chunks a head has
+      if (l.name.find("k_refine_all") != std::string::npos) EXPECT((int)l.grid.x == c.H);
   }
 }
 

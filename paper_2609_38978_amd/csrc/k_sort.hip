@@ -12,14 +12,22 @@ namespace park {
 
 constexpr int SORT_MAXC = 2048;
 
-// Tokens per sort tile: 4096 (four steps of 64 for each of 16 wavefronts), doubled until a
-// head has at most 32 tiles, so that a scatter workgroup reads its column of
-// the histogram table in one or two round trips of loads; at most 32768, since
-// the counts inside a tile are 16 bits wide.
+// Tokens per sort tile.  Every wavefront of a scatter workgroup ranks at least
+// four steps of 64: a head of up to 4096 tokens is one tile (no histogram pass) of
+// eight or sixteen wavefronts, up to 8192 tokens four wavefronts take 1024 and
+// beyond that eight take 2048, doubled until a head has at most 32 tiles, so that a
+// scatter workgroup reads its column of the histogram table in one or two round
+// trips of loads; at most 32768, since the counts inside a tile are 16 bits wide.
+// Sixteen wavefronts on 4096 tokens, eight on 2048 and four on 1024 (us a call of
+// 10 rounds, d = 64): 1 x 2000 259, 255, 274; 24 x 2100 303, 333, 325; 1 x 4157
+// 337, 313, 309 (one wavefront on tiles of 256: 346); 24 x 4157 416, 391, 387
+// (387); 24 x 6500 514, 496, 490 (517); 1 x 17019 446, 432, 443; 24 x 12000 707,
+// 691, 693; 5 x 64000 1057, 1046, 1085.
 int sort_tile(int H, int N, int C) {
   (void)H;
   (void)C;
-  int t = 4096;
+  if (N > 2048 && N <= 4096) return 4096;
+  int t = N > 4096 && N <= 8192 ? 1024 : 2048;
   while ((N + t - 1) / t > 32 && t < 32768) t *= 2;
   return t;
 }
@@ -239,17 +247,19 @@ static park_status count_sort(const int* labels, int H, int N, int C, int* thist
   return PARK_OK;
 }
 
-// Sixteen wavefronts a workgroup finish a tile soonest.  With more workgroups
-// than CUs eight serve better: twice as many fit beside each other and beside
-// what the other stream runs, where a 1024-thread workgroup waits for a CU to
-// clear (launch times, scatter + histogram, eight : sixteen; both sides of a
-// layer in flight: 24 x 119056 75 + 18 : 117 + 34 us, 40 x 75600 95 + 13 :
-// 109 + 48, the layers themselves equal within noise; 40 x 75600 queries alone
-// 26 + 5 : 35 + 6; below the line, 16 x 21600, C = 340 9.8 : 7.8, 3 x 119056
-// 16.7 : 14.7, 12 x 17019, d = 64 calls 1443 : 1410 us).
+// Four and eight wavefronts for the tiles of 1024 and 2048.  Of larger ones, sixteen
+// finish a tile soonest; with more workgroups than CUs eight serve better: twice
+// as many fit beside each other and beside what the other stream runs, where a
+// 1024-thread workgroup waits for a CU to clear (launch times, scatter +
+// histogram, eight : sixteen; both sides of a layer in flight: 24 x 119056 75 + 18 :
+// 117 + 34 us, 40 x 75600 95 + 13 : 109 + 48, the layers themselves equal within
+// noise; 40 x 75600 queries alone 26 + 5 : 35 + 6; below the line, 3 x 119056
+// 16.7 : 14.7).
 park_status launch_count_sort(const int* labels, int H, int N, int C, int* thist, int* perm,
                               int* offsets, hipStream_t st) {
-  if ((long)H * sort_tiles(H, N, C) > 256)
+  const int t = sort_tile(H, N, C);
+  if (t == 1024) return count_sort<4>(labels, H, N, C, thist, perm, offsets, st);
+  if (t == 2048 || (long)H * sort_tiles(H, N, C) > 256)
     return count_sort<8>(labels, H, N, C, thist, perm, offsets, st);
   return count_sort<16>(labels, H, N, C, thist, perm, offsets, st);
 }

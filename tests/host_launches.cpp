@@ -188,15 +188,18 @@ static void kmeans_options() {
   env_script.clear();
 }
 
-// The counting sort takes sixteen wavefronts a tile up to 256 workgroups and
-// eight beyond, and no histogram pass for heads of one tile.
+// The counting sort takes four wavefronts on tiles of 1024 tokens, eight on 2048,
+// and of larger ones sixteen up to 256 workgroups and eight beyond; no histogram
+// pass for heads of one tile.
 static void sort_routes() {
-  struct { int H, N, nw, hist; } cases[] = {{1, 4096, 16, 0},   {1, 4097, 16, 2},  {256, 4096, 16, 0},
-                                            {257, 4096, 8, 0},  {86, 8193, 8, 2},  {85, 8193, 16, 2},
+  struct { int H, N, nw, hist; } cases[] = {{1, 300, 8, 0},     {1, 2048, 8, 0},   {1, 2049, 16, 0},
+                                            {1, 4096, 16, 0},   {1, 4097, 4, 2},   {1, 8192, 4, 2},
+                                            {1, 8193, 8, 2},    {256, 4096, 16, 0}, {257, 4096, 8, 0},
+                                            {1, 65536, 8, 2},   {1, 65537, 16, 2}, {16, 65537, 8, 2},
                                             {24, 119056, 8, 2}, {3, 119056, 16, 2}};
   for (const auto& c : cases) {
     EXPECT(cluster(c.N, 300, 2, c.H) == PARK_OK);
-    EXPECT(count(c.nw == 8 ? "k_sort_scatterILi8E" : "k_sort_scatterILi16E") == 2);
+    EXPECT(count(("k_sort_scatterILi" + std::to_string(c.nw) + "E").c_str()) == 2);
     EXPECT(count("k_sort_scatter") == 2 && count("k_sort_hist") == c.hist);
   }
 }

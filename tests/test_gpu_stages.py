@@ -512,10 +512,11 @@ def test_sort_tiles_and_listed_tokens(N, C):
 
 
 @pytest.mark.parametrize("H,N,C", [(64, 16384, 67), (65, 16384, 67), (90, 9001, 2048),
-                                   (257, 100, 33), (9, 131071, 300)])
+                                   (257, 100, 33), (9, 131071, 300), (2, 2048, 300), (2, 2049, 300),
+                                   (3, 4097, 33), (2, 8192, 2048), (1, 8193, 511), (1, 65537, 67)])
 def test_sort_of_many_tiles(H, N, C):
-    # on either side of 256 sort workgroups, which sort with sixteen wavefronts a
-    # tile or eight; heads of one tile, of three, of more than 32 x 4096 tokens
+    # tiles of 1024 to 4096 tokens by four, eight and sixteen wavefronts, on either
+    # side of 256 workgroups; heads of one tile, of a few, of more than 32 x 4096 tokens
     g = torch.Generator(device="cuda").manual_seed(H)
     X = torch.randn(H, N, 64, generator=g, device="cuda").to(torch.bfloat16)
     r = P.park_cluster_keys(X, C, 1, seed=3, side=0, metric=P.PARK_METRIC_EUCLID)

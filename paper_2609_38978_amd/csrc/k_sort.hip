@@ -80,8 +80,8 @@ __global__ __launch_bounds__(NT) void k_sort_hist(const int* __restrict__ labels
 // thread, took 66 us at 3 x 119056 tokens, C = 1861 (14 us at 12 x 17019,
 // C = 266; 14.5 us at 1 x 4096; 51 us at 40 x 75600, C = 1182) as one launch on
 // an otherwise idle chip; sixteen wavefronts with four steps each and 30-row
-// tables take 14.6 us (8, 6.5, and 26 with eight wavefronts, see
-// launch_count_sort).
+// tables take 14.6 us (6.5 at 1 x 4096), eight take 7.2 at 12 x 17019 and 26 at
+// 40 x 75600 (see launch_count_sort).
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void k_sort_scatter(const int* __restrict__ labels, int N, int C,
                                                           int nbits, int tile_sz,
